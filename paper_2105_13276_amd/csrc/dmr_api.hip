@@ -89,7 +89,7 @@ struct Layout {
   size_t plane0 = 0, plane1 = 0;
   int pitch0 = 0, pitch1 = 0;
   size_t off_l1 = 0, off_flag = 0, off_scan = 0, off_list = 0, off_desc = 0,
-         off_err = 0, off_stage = 0, total = 0;
+         off_err = 0, off_stage = 0, off_hzp = 0, total = 0;
   int NB = 0;
   // union-of-blocks fine level: two block maps, two tile lists (64 x 4 tiles
   // at most over the fine domain)
@@ -120,6 +120,7 @@ Layout layout_of(const dmr_params* p) {
   L.off_desc = off;  off += 256;
   L.off_err = off;   off += 256;
   L.off_stage = off; off += align256(stage * sizeof(float));
+  L.off_hzp = off;   off += align256(L.plane0 * sizeof(float));
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
     L.max_tiles = (size_t)((p->r * p->nx + 1 + kTX - 1) / kTX) * ((p->r * p->ny + 1 + 3) / 4);
     L.off_act = off;   off += 2 * align256(nb);
@@ -272,6 +273,8 @@ struct dmr_sim {
   int* d_desc = nullptr;
   int* d_err = nullptr;
   float* stage = nullptr;
+  float* hzp = nullptr;  // base level: third Hz plane (the half level before, multi_steps)
+  int multi_t = kMultiSteps, multi_w = 0;  // DMR_MULTI (waves 0: by size)
   int h_desc[16] = {};
   // patch built at t = 0, and whether its density came from a fine seed
   bool had0 = false, keep_n0 = false;
@@ -416,10 +419,11 @@ void ev_close(dmr_sim* s) {
 
 // a launch of class cls follows: extend the open group if it is of the same
 // class, else start a new group
-void ev_begin(dmr_sim* s, int cls) {
+// (steps: the base steps it takes, which is what the count of a class means)
+void ev_begin(dmr_sim* s, int cls, int steps = 1) {
   if (!s->timing) return;
   if (s->ev_open && s->evs[s->ev_used].cls == cls) {
-    s->evs[s->ev_used].n++;
+    s->evs[s->ev_used].n += steps;
     return;
   }
   ev_close(s);
@@ -430,7 +434,7 @@ void ev_begin(dmr_sim* s, int cls) {
     s->evs.push_back(e);
   }
   s->evs[s->ev_used].cls = cls;
-  s->evs[s->ev_used].n = 1;
+  s->evs[s->ev_used].n = steps;
   (void)hipEventRecord(s->evs[s->ev_used].a, s->st);
   s->ev_open = true;
 }
@@ -950,6 +954,115 @@ int run_copies(dmr_sim* s, const CopyJobs& J) {
   return e == hipSuccess ? DMR_OK : hipfail(s, e, "tape copy");
 }
 
+// What follows a base step: the window and continuity cadence and the growth
+// test (or, in the adjoint's replay, the recorded growth).
+int step_close(dmr_sim* s, StepCtx* cx) {
+  const dmr_params& p = s->p;
+  const bool st = cx && cx->store;
+  hipError_t e = hipSuccess;
+  if (p.continuity_on && s->step % s->L0.spb == 0) {
+    const int slot = (int)(s->blocks % kRing);
+    s->blocks++;
+    const int update = s->blocks >= kRing;
+    if (cx) {
+      cx->meta.sync = 1;
+      cx->meta.update = update;
+      cx->meta.slot = slot;
+    }
+    ContArgs K;
+    make_base_cont(s, s->ncur, &K);
+    K.slot = slot; K.update = update;
+    // a small rectangular r = 2 patch on a small (latency-bound) grid: both
+    // levels in one launch (its boundary lines take one block of their own;
+    // measured: 5.7 instead of 9.3 us on 512 x 256, even on 1024 x 512,
+    // slower on 4096 x 2048, where the coarse level streams better in the
+    // plain launch)
+    const long perim = s->has_patch ? 2L * p.r * ((s->ext[2] - s->ext[0]) + (s->ext[3] - s->ext[1])) : 0;
+    const bool merge = s->has_patch && !s->uni && (p.r == 2 || p.r == 4) && perim <= 2048 &&
+                       s->ext[2] > s->ext[0] && s->ext[3] > s->ext[1] &&
+                       (s->cont_merge >= 0 ? s->cont_merge == 1 : (long)p.nx * p.ny <= (1L << 19));
+    if (merge) {
+      ContArgs G;
+      make_fine_cont(s, s->ncur, &G);
+      G.slot = slot; G.update = update;
+      K.pL = s->ext[0]; K.pB = s->ext[1]; K.pR = s->ext[2]; K.pT = s->ext[3];
+      ev_begin(s, 2);
+      e = launch_cont2(K, G, s->st);
+      ev_end(s);
+      if (e != hipSuccess) return hipfail(s, e, "continuity launch");
+    } else {
+      ev_begin(s, 2);
+      e = launch_cont(K, false, s->st);
+      ev_end(s);
+      if (e != hipSuccess) return hipfail(s, e, "continuity launch");
+    }
+    if (s->has_patch && !merge) {
+      ContArgs G;
+      make_fine_cont(s, s->ncur, &G);
+      G.slot = slot; G.update = update;
+      ev_begin(s, 2);
+      if (s->uni) e = launch_cont_union(G, s->d_tiles, s->ntiles, s->tyu, s->st);
+      else e = launch_cont(G, true, s->st);
+      ev_end(s);
+      if (e != hipSuccess) return hipfail(s, e, "fine continuity launch");
+    }
+    if (st && update) {  // the E_rms^2 each continuity step used
+      const Level& C = s->L0;
+      e = launch_ring_e2(C.ring, C.plane, C.pitch, 0, 0, p.nx, p.ny, cx->ss.ce2, s->st);
+      if (e == hipSuccess && s->has_patch) {
+        const Level& F = s->L1;
+        const int r = p.r;
+        e = launch_ring_e2(F.ring, F.plane, F.pitch, r * s->ext[0], r * s->ext[1],
+                           r * s->ext[2], r * s->ext[3], cx->ss.fe2, s->st);
+      }
+      if (e != hipSuccess) return hipfail(s, e, "window sum launch");
+    }
+    if (update) s->ncur = 1 - s->ncur;
+  }
+  if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every == 0) {
+    if (cx && cx->forced) {
+      if (!cx->force_grow) return DMR_OK;
+      if (int rc = prolong(s, cx->force_ext, false)) return rc;
+    } else {
+      const bool had = s->has_patch;
+      int before[4];
+      for (int q = 0; q < 4; q++) before[q] = s->ext[q];
+      if (int rc = regrid(s, false)) return rc;
+      bool grew = s->has_patch != had;
+      for (int q = 0; q < 4; q++) grew = grew || s->ext[q] != before[q];
+      if (!grew || !cx) return DMR_OK;
+    }
+    cx->meta.grow = 1;
+    for (int q = 0; q < 4; q++) cx->meta.gnew[q] = s->ext[q];
+  }
+  return DMR_OK;
+}
+
+// Waves per block of a t-step launch on an nx x ny grid (4 rows a wave).  Tall
+// blocks recompute less (they own 4 W - 2 t of 4 W rows) but overlap their
+// loads with another block's steps less: a compute unit holds one block of 16
+// waves (its vector units were busy 62% of the time on 4096x2048), two of 12
+// (86%) or of 8 (95%).  Small grids: the busiest of the 256 compute units
+// sets the time, in waves per SIMD (1024x512: 2.86 ms per 1024 steps with 16
+// waves, 3.28 with 12 and 3.30 with 8; 8192x4096: 5.08, 4.00 and 4.86 ms per
+// 32 steps).
+int multi_waves(int nx, int ny, int t) {
+  const int ws[] = {8, 12, 16, 6};
+  const double busy[] = {0.95, 0.86, 0.62, 0.95};
+  const int held[] = {2, 2, 1, 3};
+  int best = 8;
+  double least = 1e30;
+  for (int k = 0; k < 4; k++) {
+    const int w = ws[k], h = 4 * w - 2 * t;
+    if (h < 2) continue;
+    const long n = (long)((nx + 1 + 63 - 2 * t) / (64 - 2 * t)) * ((ny + 1 + h - 1) / h);
+    const double simd = (double)(((n + 255) / 256 * w + 3) / 4);
+    const double cost = n <= 256 * held[k] ? simd : n * w / (1024.0 * busy[k]);
+    if (cost < least) { least = cost; best = w; }
+  }
+  return best;
+}
+
 // One base step with subcycling (Sec. III.C), the window/continuity cadence
 // and the regrid cadence.  With cx, the step also reports what it did and,
 // for the adjoint's replay, stores its forward values and applies a
@@ -1127,82 +1240,30 @@ int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
   }
   s->ccur = 1 - c;
   s->step++;
-  if (p.continuity_on && s->step % s->L0.spb == 0) {
-    const int slot = (int)(s->blocks % kRing);
-    s->blocks++;
-    const int update = s->blocks >= kRing;
-    if (cx) {
-      cx->meta.sync = 1;
-      cx->meta.update = update;
-      cx->meta.slot = slot;
-    }
-    ContArgs K;
-    make_base_cont(s, s->ncur, &K);
-    K.slot = slot; K.update = update;
-    // a small rectangular r = 2 patch on a small (latency-bound) grid: both
-    // levels in one launch (its boundary lines take one block of their own;
-    // measured: 5.7 instead of 9.3 us on 512 x 256, even on 1024 x 512,
-    // slower on 4096 x 2048, where the coarse level streams better in the
-    // plain launch)
-    const long perim = s->has_patch ? 2L * p.r * ((s->ext[2] - s->ext[0]) + (s->ext[3] - s->ext[1])) : 0;
-    const bool merge = s->has_patch && !s->uni && (p.r == 2 || p.r == 4) && perim <= 2048 &&
-                       s->ext[2] > s->ext[0] && s->ext[3] > s->ext[1] &&
-                       (s->cont_merge >= 0 ? s->cont_merge == 1 : (long)p.nx * p.ny <= (1L << 19));
-    if (merge) {
-      ContArgs G;
-      make_fine_cont(s, s->ncur, &G);
-      G.slot = slot; G.update = update;
-      K.pL = s->ext[0]; K.pB = s->ext[1]; K.pR = s->ext[2]; K.pT = s->ext[3];
-      ev_begin(s, 2);
-      e = launch_cont2(K, G, s->st);
-      ev_end(s);
-      if (e != hipSuccess) return hipfail(s, e, "continuity launch");
-    } else {
-      ev_begin(s, 2);
-      e = launch_cont(K, false, s->st);
-      ev_end(s);
-      if (e != hipSuccess) return hipfail(s, e, "continuity launch");
-    }
-    if (s->has_patch && !merge) {
-      ContArgs G;
-      make_fine_cont(s, s->ncur, &G);
-      G.slot = slot; G.update = update;
-      ev_begin(s, 2);
-      if (s->uni) e = launch_cont_union(G, s->d_tiles, s->ntiles, s->tyu, s->st);
-      else e = launch_cont(G, true, s->st);
-      ev_end(s);
-      if (e != hipSuccess) return hipfail(s, e, "fine continuity launch");
-    }
-    if (st && update) {  // the E_rms^2 each continuity step used
-      const Level& C = s->L0;
-      e = launch_ring_e2(C.ring, C.plane, C.pitch, 0, 0, p.nx, p.ny, cx->ss.ce2, s->st);
-      if (e == hipSuccess && s->has_patch) {
-        const Level& F = s->L1;
-        const int r = p.r;
-        e = launch_ring_e2(F.ring, F.plane, F.pitch, r * s->ext[0], r * s->ext[1],
-                           r * s->ext[2], r * s->ext[3], cx->ss.fe2, s->st);
-      }
-      if (e != hipSuccess) return hipfail(s, e, "window sum launch");
-    }
-    if (update) s->ncur = 1 - s->ncur;
-  }
-  if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every == 0) {
-    if (cx && cx->forced) {
-      if (!cx->force_grow) return DMR_OK;
-      if (int rc = prolong(s, cx->force_ext, false)) return rc;
-    } else {
-      const bool had = s->has_patch;
-      int before[4];
-      for (int q = 0; q < 4; q++) before[q] = s->ext[q];
-      if (int rc = regrid(s, false)) return rc;
-      bool grew = s->has_patch != had;
-      for (int q = 0; q < 4; q++) grew = grew || s->ext[q] != before[q];
-      if (!grew || !cx) return DMR_OK;
-    }
-    cx->meta.grow = 1;
-    for (int q = 0; q < 4; q++) cx->meta.gnew[q] = s->ext[q];
-  }
-  return DMR_OK;
+  return step_close(s, cx);
+}
+
+// Several base steps in one launch where no patch takes part in them; the
+// steps end at or before the next window block's.  last: Hz of the half
+// level before is kept too (growth and saved states use it).
+int multi_steps(dmr_sim* s, int t, bool last) {
+  const int c = s->ccur;
+  Level& C = s->L0;
+  MultiArgs M{};
+  make_base_em(s, c, s->ncur, &M.em);
+  M.acc1 = C.acc;
+  M.hzp = last ? s->hzp : nullptr;
+  M.t = t;
+  for (int k = 0; k < t; k++) incident_values(s, s->step + k, &M.src[k].x, &M.src[k].y);
+  const int waves = s->multi_w ? s->multi_w : multi_waves(s->p.nx, s->p.ny, t);
+  ev_begin(s, 0, t);
+  const hipError_t e = launch_em_multi(M, waves, s->st);
+  ev_end(s);
+  if (e != hipSuccess) return hipfail(s, e, "base EM launch");
+  if (last) std::swap(C.hz[c], s->hzp);
+  s->ccur = 1 - c;
+  s->step += t;
+  return step_close(s, nullptr);
 }
 
 struct View {
@@ -1333,6 +1394,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   s->d_desc = (int*)(s->ws + lay.off_desc);
   s->d_err = (int*)(s->ws + lay.off_err);
   s->stage = (float*)(s->ws + lay.off_stage);
+  s->hzp = (float*)(s->ws + lay.off_hzp);
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
     s->uni = true;
     const size_t nb = (size_t)lay.NB;
@@ -1359,6 +1421,13 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   if (const char* f = getenv("DMR_FNT")) s->nt1 = atoi(f) >= 1024 ? 1024 : 256;
   if (const char* f = getenv("DMR_TW")) { const int v = atoi(f); s->tw1 = (v == 16 || v == 32 || v == 64) ? v : 0; }
   if (const char* f = getenv("DMR_FINE_STREAM")) s->stream_force = atoi(f) != 0 ? 1 : 0;
+  // DMR_MULTI=steps[,waves]: most base steps of a launch (1: one launch a
+  // step) and its waves per block
+  if (const char* f = getenv("DMR_MULTI")) {
+    (void)sscanf(f, "%d,%d", &s->multi_t, &s->multi_w);
+    s->multi_t = std::min(std::max(s->multi_t, 1), kMultiSteps);
+    s->multi_w = s->multi_w < 5 ? 0 : std::min(s->multi_w, 16);
+  }
   if (const char* f = getenv("DMR_CONT_MERGE")) s->cont_merge = atoi(f) != 0 ? 1 : 0;
   if (const char* f = getenv("DMR_FINE_SEG")) s->fseg = atoi(f) >= 2 ? atoi(f) : 0;
   if (const char* f = getenv("DMR_FINE_DEPTH")) s->fdepth = atoi(f) >= 4 ? 4 : 2;
@@ -1448,9 +1517,20 @@ void dmr_destroy(dmr_sim* s) {
 
 int dmr_step(dmr_sim* s, int64_t n) {
   if (!s || n < 0) return fail(s, DMR_EINVAL, "bad step count");
-  for (int64_t k = 0; k < n; k++) {
-    const int rc = base_step(s);
+  while (n > 0) {
+    // up to the next window block, in launches of equal length
+    const int blk = s->L0.spb - (int)(s->step % s->L0.spb);
+    const int64_t left = std::min<int64_t>(n, blk);
+    const int most = s->multi_t;
+    int t = 1;
+    if (!s->has_patch && left > 1 && most > 1) {
+      const int64_t parts = (left + most - 1) / most;
+      t = (int)((left + parts - 1) / parts);
+    }
+    const bool last = t == n || (s->p.mode == DMR_DYNAMIC && (s->step + t) % s->p.regrid_every == 0);
+    const int rc = t > 1 ? multi_steps(s, t, last) : base_step(s);
     if (rc) { ev_close(s); return rc; }
+    n -= t;
   }
   ev_close(s);  // a timing group does not span calls (the caller may queue other work)
   const hipError_t e = hipGetLastError();

@@ -84,6 +84,17 @@ struct EMArgs {
   const int2* utiles;  // batched union levels: the instance's tile list
 };
 
+// several base-level steps in one launch (dmr_multi.hip)
+constexpr int kMultiSteps = 8;   // most steps of a launch
+struct MultiArgs {
+  EMArgs em;     // reads buffer 0, writes buffer 1; the window is read at em.acc
+  float* acc1;   // window accumulator after the steps (em.acc: in place)
+  float* hzp;    // Hz entering the last step (the half level before), nullable
+  int t;         // steps
+  int ntx, nty;  // blocks along x and y (set by the launcher)
+  float2 src[kMultiSteps];  // incident Ey, eta0 Hz of each step
+};
+
 struct ContArgs {
   const float* n0;
   float* n1;
@@ -186,6 +197,8 @@ hipError_t launch_fine_stream(const EMArgs& A, int seg, int depth, hipStream_t s
 hipError_t launch_line_flags(const float* n, int pitch, int I0, int J0, int I1, int J1,
                              float thr, int* flags, hipStream_t st);
 int stream_segments(int NY, int seg);
+// M.t base-level steps in one launch, blocks of 64 columns x 4 waves rows
+hipError_t launch_em_multi(MultiArgs& M, int waves, hipStream_t st);
 // batched forms: blk[b] = (instance, block index within the instance)
 hipError_t launch_em_stream_batch(const EMArgs* args, const int2* blk, int nblk,
                                   const float2* src, int k, int depth, hipStream_t st);

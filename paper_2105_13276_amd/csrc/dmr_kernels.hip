@@ -17,23 +17,10 @@
 // E, J, Hz are ping-ponged (read buffer 0, write buffer 1) so a tile can
 // recompute its halo without racing its neighbours; the window accumulator
 // is updated in place by the tile owning the node.
+#include "dmr_device.h"
 #include "dmr_kernels.h"
 
 namespace dmr {
-
-// Base-level per-entity arithmetic, shared by the streaming kernel and the
-// patch tiles of the combined step (which recompute coarse E on the patch
-// boundary lines), so both round identically.
-__device__ inline float base_kap(float kn, float n0, float n1) { return kn * (0.5f * (n0 + n1)); }
-__device__ inline float base_hz(float hz, float S, float ey1, float ey, float exu, float ex) {
-  return hz - S * ((ey1 - ey) - (exu - ex));
-}
-__device__ inline float base_ex(float e, float kap, float S, float h, float hp, float c1, float j) {
-  return ((1.f - kap) * e + S * (h - hp) - c1 * j) * __builtin_amdgcn_rcpf(1.f + kap);
-}
-__device__ inline float base_ey(float e, float kap, float curl, float c1, float j) {
-  return ((1.f - kap) * e + curl - c1 * j) * __builtin_amdgcn_rcpf(1.f + kap);
-}
 
 // ---------------------------------------------------------------------------
 // Per-entity arithmetic of the patch substep, shared by the one-substep and
@@ -2365,6 +2352,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
   const bool wave_has_right = c0 - 2 <= NX && NX <= c0 + 61;
   const bool exv = i >= 0 && i < NX;
   const bool eyc = i >= 0 && i <= NX;
+  const float fxe = i > 0 && i < NX ? 1.f : 2.f;  // x-edges of a window node: 2 or 1
   const float S = A.S, c1 = A.c1, a = A.a, kn = A.kn, cm = A.cmur;
   // combined step: the coarse entities strictly inside the patch are written
   // by the patch tiles' fine -> coarse transfer in the same launch
@@ -2458,28 +2446,16 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
         }
       }
       const float exl0 = __shfl_up(ex0, 1, 64);
-      if (own && eyc) {
-        float sx = 0.f, e2;
-        int cx = 0;
-        if (i > 0) { sx += exl0 * exl0; cx++; }
-        if (i < NX) { sx += ex0 * ex0; cx++; }
-        e2 = (cx == 2 ? 0.5f * sx : sx) + eyn_p * eyn_p;
-        str<O32>(A.acc, row_addr(A, i, 0), acc0 + e2);
-      }
+      if (own && eyc)
+        str<O32>(A.acc, row_addr(A, i, 0),
+                 base_win(acc0, i > 0 ? exl0 : 0.f, i < NX ? ex0 : 0.f, 0.f, eyn_p, fxe, 2.f));
     }
     // window at node (i, j)
     const float exl = __shfl_up(exn, 1, 64);
     if (j > 0) {
-      if (store && own) {
-        float sx = 0.f, sy = 0.f;
-        int cx = 0, cy = 0;
-        if (i > 0) { sx += exl * exl; cx++; }
-        if (i < NX) { sx += exn * exn; cx++; }
-        sy += eyn_p * eyn_p; cy++;
-        if (j < NY) { sy += eyn * eyn; cy++; }
-        const float e2 = (cx == 2 ? 0.5f * sx : sx) + (cy == 2 ? 0.5f * sy : sy);
-        str<O32>(A.acc, o, cur.acc + e2);
-      }
+      if (store && own)
+        str<O32>(A.acc, o, base_win(cur.acc, i > 0 ? exl : 0.f, i < NX ? exn : 0.f, eyn_p,
+                                    j < NY ? eyn : 0.f, fxe, j < NY ? 1.f : 2.f));
     } else {
       acc0 = cur.acc;
     }
@@ -2520,17 +2496,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       str<O32>(A.jy1, o, a * cur.jy + 2.f * kapy * (cur.ey + eyn));
     }
     const float exl = __shfl_up(exn, 1, 64);
-    if (store && own) {
-      float sx = 0.f, sy = 0.f;
-      sx += exl * exl;
-      sx += exn * exn;
-      sy += eyn_p * eyn_p;
-      sy += eyn * eyn;
-      const float hx = 0.5f * sx;
-      const float hy = 0.5f * sy;
-      const float e2 = hx + hy;
-      str<O32>(A.acc, o, cur.acc + e2);
-    }
+    if (store && own) str<O32>(A.acc, o, base_win(cur.acc, exl, exn, eyn_p, eyn));
     hzn_p = hzn;
     eyn_p = eyn;
   };
@@ -2555,15 +2521,6 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
   } else {
     run(row);
   }
-}
-
-// Workgroups are dispatched to the 8 XCDs round-robin by linear id, and each
-// XCD has its own L2.  Hand XCD x a contiguous band of the row-major
-// (column block, segment) grid so that neighbouring blocks, which read the
-// same cache lines at their common columns and rows, share an L2.
-__device__ inline int xcd_band(int L, int N) {
-  const int x = L & 7, k = L >> 3, q = N >> 3, r = N & 7;
-  return x * q + min(x, r) + k;
 }
 
 template <int DEPTH, bool ST = false>

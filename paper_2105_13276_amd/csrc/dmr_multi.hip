@@ -1,0 +1,257 @@
+// dmr_multi.hip -- several base-level EM steps (Eqs. (1)-(3), Mur/PEC, TF/SF,
+// E^2 window) in one launch, where nothing outside the level enters between
+// them (no patch, or far enough from it).
+//
+// One step per launch moves 52 bytes per cell-update: every plane of the
+// state is read and written once a step, and on small grids every step pays a
+// launch and a memory round trip.  Here a block holds a region of 64 columns
+// x NW R rows in registers (a lane one column, a wave R rows) and takes t
+// steps of it; the region it can trust shrinks by one cell on each side per
+// step, so it owns the 64 - 2t columns and NW R - 2t rows in the middle and
+// recomputes the rest, which its neighbours own.  x-neighbours come from the
+// next lane (DPP, no LDS), y-neighbours from the next register; only the rows
+// at the border of two waves go through LDS, once a step (the wave below its
+// first row recomputes that Hz row itself, so one barrier a step suffices).
+// Every entity is computed by the operations of k_em_stream, so the results
+// are identical to t launches of it.
+#include "dmr_device.h"
+#include "dmr_kernels.h"
+
+namespace dmr {
+
+namespace {
+
+// value of the lane one column to the right / left (0 beyond the wave)
+__device__ __forceinline__ float lane_right(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+      0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));  // wave_shl:1
+}
+__device__ __forceinline__ float lane_left(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+      0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));  // wave_shr:1
+}
+
+// The region is stepped by the interior update everywhere, also where it
+// reaches beyond the grid: E that does not exist (or is zero, PEC) takes the
+// factor 0 for 1 / (1 + kap), which also drops it from the window of the
+// boundary nodes.  XE: the region holds column 0 or NX or a source column;
+// YE: the wave holds row 0 or NY.
+template <int R, bool XE, bool YE>
+__device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, int own_x,
+                                           int own_lo, int own_hi, float (*sE)[3][64]) {
+  const EMArgs& A = M.em;
+  const int NX = A.R, NY = A.T, t = M.t;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nw = (int)(blockDim.x >> 6);
+  const int i = x0 + lane, jt = y0 + w * R;  // column, first row of the wave
+  const float S = A.S, c1 = A.c1, a = A.a, kn = A.kn, cm = A.cmur;
+
+  // rows jt .. jt + R - 1 of every plane, row jt - 1 of Hz, row jt + R of n,
+  // all requested before any is used
+  float ex[R], ey[R], hz[R], jx[R], jy[R], ac[R], n[R + 1], hm;
+  {
+    const unsigned o = (unsigned)(XE ? min(max(i, 0), NX) : i) << 2;
+    auto row = [&](const float* p, int j) {
+      return *(const float*)((const char*)(p + (size_t)min(max(j, 0), NY) * A.pitch) + o);
+    };
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      n[r] = row(A.n, jt + r);
+      ey[r] = row(A.ey0, jt + r);
+      ex[r] = row(A.ex0, jt + r);
+      hz[r] = row(A.hz0, jt + r);
+      jx[r] = row(A.jx0, jt + r);
+      jy[r] = row(A.jy0, jt + r);
+      ac[r] = row(A.acc, jt + r);
+    }
+    n[R] = row(A.n, jt + R);
+    hm = row(A.hz0, jt - 1);
+  }
+  const int rb = -jt, rt = NY - jt;  // rows 0 and NY of the grid in the wave
+  const bool mur_x = A.bc_x == kBcMur, mur_y = A.bc_y == kBcMur;
+  const bool c0 = i == 0, cN = i == NX;
+  const bool mur0 = mur_x && x0 <= 0, murN = mur_x && x0 + 63 >= NX;
+  const bool src = A.is > 0 && A.is >= x0 && A.is - 1 <= x0 + 63;
+  const float fx = XE && (c0 || cN) ? 2.f : 1.f;
+
+  // (conditions without branches: short-circuit forms of them were compiled
+  // to code that lost the factor 0)
+  const bool colx = !XE | ((i >= 0) & (i < NX));
+  const bool coly = !XE | ((i >= 0) & (i <= NX) & (mur_x | !(c0 | cN)));
+  float kx[R], ky[R], rx[R], ry[R];
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    kx[r] = base_kap(kn, n[r], lane_right(n[r]));
+    ky[r] = base_kap(kn, n[r], n[r + 1]);
+    const int j = jt + r;
+    const bool rowx = (j >= 0) & (j <= NY) & (mur_y | ((j != 0) & (j != NY)));
+    const bool rowy = (j >= 0) & (j < NY);
+    rx[r] = (rowx & colx) ? base_rcp(kx[r]) : 0.f;
+    ry[r] = (rowy & coly) ? base_rcp(ky[r]) : 0.f;
+  }
+
+  // window of the wave's node row r, Ey of the row below it
+  auto window = [&](int r, float yd) {
+    const float fy = YE && (r == rb || r == rt) ? 2.f : 1.f;
+    return base_win(ac[r], lane_left(ex[r]), ex[r], yd, ey[r], fx, fy);
+  };
+  // the wave's border rows to its neighbours
+  auto publish = [&](int b) {
+    float (*e)[64] = sE[b * nw + w];
+    e[0][lane] = ex[0];
+    e[1][lane] = ex[R - 1];
+    e[2][lane] = ey[R - 1];
+  };
+
+  for (int s = 0; s < t; s++) {
+    const int b = (s & 1) * nw;
+    publish(s & 1);
+    __syncthreads();
+    if (s == t - 1 && M.hzp) {  // Hz entering the last step
+#pragma unroll
+      for (int r = 0; r < R; r++) {
+        const int j = jt + r;
+        if (j >= own_lo && j < own_hi && j < NY && i >= own_x && lane < 64 - t && i < NX)
+          M.hzp[(size_t)j * A.pitch + i] = hz[r];
+      }
+    }
+    const float exu = sE[b + (w + 1 < nw ? w + 1 : w)][0][lane];  // Ex of row jt + R
+    const int wb = b + (w > 0 ? w - 1 : 0);
+    const float exm = sE[wb][1][lane], eym = sE[wb][2][lane];  // row jt - 1
+    // the window of the wave's first node row waits for Ey of the row below
+    // (before the first step the accumulator stays)
+    const float a0 = window(0, YE && rb == 0 ? 0.f : eym);
+    ac[0] = s > 0 ? a0 : ac[0];
+
+    // Faraday, Eq. (2)
+    hm = base_hz(hm, S, lane_right(eym), eym, ex[0], exm);
+#pragma unroll
+    for (int r = 0; r < R; r++)
+      hz[r] = base_hz(hz[r], S, lane_right(ey[r]), ey[r], r + 1 < R ? ex[r + 1 < R ? r + 1 : r] : exu,
+                      ex[r]);
+    // source terms; -0 (which changes no value) off the source columns
+    float add_e = -0.f;
+    if (XE && src) {
+      const float add_h = i == A.is - 1 ? S * M.src[s].x : -0.f;
+      add_e = i == A.is ? S * M.src[s].y : -0.f;
+      hm += add_h;
+#pragma unroll
+      for (int r = 0; r < R; r++) hz[r] += add_h;
+    }
+
+    // Ampere + Drude, Eqs. (1), (3)
+    float en[R];
+#pragma unroll
+    for (int r = 0; r < R; r++)
+      en[r] = base_ex(ex[r], kx[r], S, hz[r], r > 0 ? hz[r > 0 ? r - 1 : 0] : hm, c1, jx[r], rx[r]);
+    if (YE && mur_y) {
+#pragma unroll
+      for (int r = 0; r + 1 < R; r++) {
+        const float eb = ex[r + 1] + cm * (en[r + 1] - ex[r]);
+        const float et = ex[r] + cm * (en[r] - ex[r + 1]);
+        if (r == rb) en[r] = colx ? eb : 0.f;
+        if (r + 1 == rt) en[r + 1] = colx ? et : 0.f;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      jx[r] = a * jx[r] + 2.f * kx[r] * (ex[r] + en[r]);
+      ex[r] = en[r];
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      float curl = -S * (hz[r] - lane_left(hz[r]));
+      if (XE && src) curl += add_e;
+      const float eyo = ey[r];
+      en[r] = base_ey(eyo, ky[r], curl, c1, jy[r], ry[r]);
+      if (XE && mur0) {
+        const float m = lane_right(eyo) + cm * (lane_right(en[r]) - eyo);
+        en[r] = c0 ? m : en[r];
+      }
+      if (XE && murN) {
+        const float m = lane_left(eyo) + cm * (lane_left(en[r]) - eyo);
+        en[r] = cN ? m : en[r];
+      }
+      if (XE && YE && (jt + r < 0 || jt + r >= NY)) en[r] = 0.f;
+      jy[r] = a * jy[r] + 2.f * ky[r] * (eyo + en[r]);
+      ey[r] = en[r];
+    }
+#pragma unroll
+    for (int r = 1; r < R; r++) ac[r] = window(r, ey[r - 1]);
+  }
+  publish(t & 1);
+  __syncthreads();
+  {
+    const float eym = sE[(t & 1) * nw + (w > 0 ? w - 1 : 0)][2][lane];
+    ac[0] = window(0, YE && rb == 0 ? 0.f : eym);
+  }
+
+  if (!(i >= own_x && lane < 64 - t) || i > NX) return;
+  const unsigned o = (unsigned)i << 2;
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    const int j = jt + r;
+    if (j < own_lo || j >= own_hi) continue;
+    const size_t ro = (size_t)j * A.pitch;
+    auto put = [&](float* p, float v) { *(float*)((char*)(p + ro) + o) = v; };
+    if (!XE || i < NX) {
+      if (j < NY) put(A.hz1, hz[r]);
+      put(A.ex1, ex[r]);
+      put(A.jx1, jx[r]);
+    }
+    if (j < NY) {
+      put(A.ey1, ey[r]);
+      put(A.jy1, jy[r]);
+    }
+    put(M.acc1, ac[r]);
+  }
+}
+
+// R rows a wave, at most NW waves a block, EU waves per SIMD
+template <int R, int NW, int EU>
+__global__ __launch_bounds__(64 * NW, EU) void k_em_multi(MultiArgs M) {
+  __shared__ float sE[2 * NW][3][64];
+  const EMArgs& A = M.em;
+  const int b = xcd_band(blockIdx.x, M.ntx * M.nty);
+  const int bx = b % M.ntx, by = b / M.ntx;
+  const int t = M.t, rows = (int)(blockDim.x >> 6) * R;
+  const int NX = A.R, NY = A.T;
+  const int own_x = bx * (64 - 2 * t);
+  const int own_lo = by * (rows - 2 * t);
+  const int own_hi = min(own_lo + rows - 2 * t, NY + 1);
+  // Mur entities depend on the new value one cell further in: a region that
+  // owns none but the last column (row) takes one more beside it
+  const int x0 = own_x - t - (own_x == NX ? 1 : 0);
+  // Ex(i, 0) is formed with Ex(i, 1) and Ex(i, NY) with Ex(i, NY-1), which
+  // have to be rows of one wave: shift the region by a row where they are not
+  // (towards the inside of the grid, where the boundary leaves rows to spare)
+  int y0 = own_lo - t - (own_lo == NY ? 1 : 0);
+  if (y0 <= 0 && NY - y0 < rows) y0 = NY % R == 0 ? -1 : 0;
+  else if (y0 <= 0 && -y0 % R == R - 1) y0++;
+  else if (y0 > 0 && NY - y0 < rows && (NY - y0) % R == 0) y0--;
+  const bool xe = x0 < 1 || x0 + 63 > NX - 1 || (A.is > 0 && A.is >= x0 && A.is - 1 <= x0 + 63);
+  // (chosen per wave; every form passes the same barriers)
+  const int jt = y0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * R;
+  const bool ye = jt < 1 || jt + R > NY;
+  if (xe && ye) multi_tile<R, true, true>(M, x0, y0, own_x, own_lo, own_hi, sE);
+  else if (xe) multi_tile<R, true, false>(M, x0, y0, own_x, own_lo, own_hi, sE);
+  else if (ye) multi_tile<R, false, true>(M, x0, y0, own_x, own_lo, own_hi, sE);
+  else multi_tile<R, false, false>(M, x0, y0, own_x, own_lo, own_hi, sE);
+}
+
+}  // namespace
+
+hipError_t launch_em_multi(MultiArgs& M, int waves, hipStream_t st) {
+  const int t = M.t, h = 4 * waves - 2 * t;
+  if (t < 1 || t > kMultiSteps || waves < 1 || waves > 16 || h < 2) return hipErrorInvalidValue;
+  M.ntx = (M.em.R + 1 + 63 - 2 * t) / (64 - 2 * t);
+  M.nty = (M.em.T + 1 + h - 1) / h;
+  const dim3 g(M.ntx * M.nty), bl(64 * waves);
+  if (waves <= 8) hipLaunchKernelGGL((k_em_multi<4, 8, 5>), g, bl, 0, st, M);
+  else if (waves <= 12) hipLaunchKernelGGL((k_em_multi<4, 12, 6>), g, bl, 0, st, M);
+  else hipLaunchKernelGGL((k_em_multi<4, 16, 4>), g, bl, 0, st, M);
+  return hipGetLastError();
+}
+
+}  // namespace dmr
