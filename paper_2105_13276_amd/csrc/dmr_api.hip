@@ -89,17 +89,25 @@ struct Layout {
   size_t plane0 = 0, plane1 = 0;
   int pitch0 = 0, pitch1 = 0;
   size_t off_l1 = 0, off_flag = 0, off_scan = 0, off_list = 0, off_desc = 0,
-         off_err = 0, off_stage = 0, off_hzp = 0, total = 0;
+         off_err = 0, off_stage = 0, off_hzp = 0, off_far = 0, total = 0;
   int NB = 0;
   // union-of-blocks fine level: two block maps, two tile lists (64 x 4 tiles
   // at most over the fine domain)
   size_t off_act = 0, off_tiles = 0, off_cfb = 0;
   size_t max_tiles = 0;
+  // and of its base level around them: block map, streaming blocks
+  size_t off_near = 0, off_nblk = 0, max_nblk = 0;
 };
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 bool refined(const dmr_params* p) { return p->mode != DMR_UNIFORM; }
+
+// rows per segment of the base-level launches around the fine level of a
+// split group (short chains: the region is small)
+constexpr int kNearSeg = 2;
+
+int stream_blocks_x(int NX) { return ((NX + 1 + 61) / 62 + kThreads / 64 - 1) / (kThreads / 64); }
 
 Layout layout_of(const dmr_params* p) {
   Layout L;
@@ -121,11 +129,16 @@ Layout layout_of(const dmr_params* p) {
   L.off_err = off;   off += 256;
   L.off_stage = off; off += align256(stage * sizeof(float));
   L.off_hzp = off;   off += align256(L.plane0 * sizeof(float));
+  L.off_far = off;
+  if (refined(p)) off += align256(6 * L.plane0 * sizeof(float));
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
     L.max_tiles = (size_t)((p->r * p->nx + 1 + kTX - 1) / kTX) * ((p->r * p->ny + 1 + 3) / 4);
     L.off_act = off;   off += 2 * align256(nb);
     L.off_tiles = off; off += 2 * align256(L.max_tiles * sizeof(int2));
     L.off_cfb = off;   off += align256(L.max_tiles * kCfbStride * sizeof(float));
+    L.max_nblk = (size_t)stream_blocks_x(p->nx) * stream_segments(p->ny, kNearSeg);
+    L.off_near = off;  off += align256(nb);
+    L.off_nblk = off;  off += align256(L.max_nblk * sizeof(int2));
   }
   L.total = off;
   return L;
@@ -275,6 +288,19 @@ struct dmr_sim {
   float* stage = nullptr;
   float* hzp = nullptr;  // base level: third Hz plane (the half level before, multi_steps)
   int multi_t = kMultiSteps, multi_w = 0;  // DMR_MULTI (waves 0: by size)
+  // refined runs: a third set of the base level's planes (Hz, Ex, Ey, Jx, Jy,
+  // window) for the split groups, and the grids they are used on
+  float* far[6] = {};
+  long split_min = -1;  // DMR_SPLIT_MIN (cells; -1: by kind)
+  // union-of-blocks level: the blocks around it (host, device) and the
+  // base-level streaming blocks that cover them
+  std::vector<uint8_t> h_near;
+  std::vector<int2> h_nblk;
+  uint8_t* d_near = nullptr;
+  int2* d_nblk = nullptr;
+  double near_share = 1.0;  // of the base-level cells
+  int64_t near_gen = -1;    // growth (ugen) they were made for
+  bool near_combine = true; // base step around the patch and substeps in one launch
   int h_desc[16] = {};
   // patch built at t = 0, and whether its density came from a fine seed
   bool had0 = false, keep_n0 = false;
@@ -667,6 +693,7 @@ void union_extents(dmr_sim* s) {
 // make h_act the level as it stands (restart): map and tile list to the
 // device, extents; no prolongation (the state carries the fine data)
 int union_install(dmr_sim* s) {
+  s->near_gen = -1;
   pick_union_rows(s, s->h_act);
   union_tiles(s, s->tyu, [&](int b) { return s->h_act[b] != 0; }, &s->h_tiles);
   HIPCHK(s, hipMemcpyAsync(s->d_act[s->acur], s->h_act.data(), s->h_act.size(),
@@ -810,12 +837,10 @@ void em_args_level(EMArgs* A, const Level& L, int src, int dst, const float* n,
   A->jx0 = L.jx[src]; A->jy0 = L.jy[src];
   A->hz1 = L.hz[dst]; A->ex1 = L.ex[dst]; A->ey1 = L.ey[dst];
   A->jx1 = L.jx[dst]; A->jy1 = L.jy[dst];
-  A->n = n; A->acc = acc;
+  A->n = n; A->acc = acc; A->acc1 = acc;
   A->pitch = L.pitch;
   A->S = L.S; A->c1 = L.c1; A->a = L.a; A->kn = L.kn; A->cmur = L.cmur;
 }
-
-int stream_blocks_x(int NX) { return ((NX + 1 + 61) / 62 + kThreads / 64 - 1) / (kThreads / 64); }
 
 // argument blocks of the four per-step launches, for buffer parities c
 // (E/H/J) and nc (density); shared by the plain and the batched schedules
@@ -1067,7 +1092,23 @@ int multi_waves(int nx, int ny, int t) {
 // and the regrid cadence.  With cx, the step also reports what it did and,
 // for the adjoint's replay, stores its forward values and applies a
 // recorded growth instead of running the growth test.
+struct NearWin;
+int em_part(dmr_sim* s, StepCtx* cx, const NearWin* win);
+
 int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
+  if (int rc = em_part(s, cx, nullptr)) return rc;
+  return step_close(s, cx);
+}
+
+// The base-level waves of a step of a split group: only those around the fine
+// level, and the window accumulator they write
+struct NearWin {
+  StreamWin stream;  // rectangle
+  float* acc1;
+};
+
+// EM step of both levels.  win: the base level around the fine level only.
+int em_part(dmr_sim* s, StepCtx* cx, const NearWin* win) {
   const dmr_params& p = s->p;
   const int c = s->ccur;
   const bool st = cx && cx->store;
@@ -1103,6 +1144,9 @@ int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
   EMArgs A;
   make_base_em(s, c, s->ncur, &A);
   incident_values(s, s->step, &A.ey_src, &A.hz_src);
+  const int seg = win ? kNearSeg : s->seg0, depth = win ? 2 : s->depth0;
+  const StreamWin sw = win ? win->stream : StreamWin();
+  if (win) A.acc1 = win->acc1;
   hipError_t e = hipSuccess;
   if (kst) {
     A.stix = cx->ss.cexi; A.stiy = cx->ss.ceyi;
@@ -1121,7 +1165,7 @@ int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
   // (1, 2); (3, 4) and the fine -> coarse transfer follow in a launch of
   // their own, so the base waves store every coarse entity
   const bool r4 = p.r == 4;
-  const bool combined = fuse && s->combine && (!r4 || (s->ty1 == 4 && !kst));
+  const bool combined = fuse && (s->combine || (win && s->near_combine)) && (!r4 || (s->ty1 == 4 && !kst));
   // what patch tiles need to form the coarse E after the base step on their
   // boundary lines themselves: the coarse state entering the step
   auto coarse_state = [&](EMArgs* G) {
@@ -1146,7 +1190,7 @@ int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
     coarse_state(&G);
     fine_stores(&G);
     ev_begin(s, 0);
-    e = launch_dmr_step(A, G, s->seg0, s->depth0, s->ty1, s->tw1, s->st, r4);
+    e = launch_dmr_step(A, G, seg, depth, s->ty1, s->tw1, s->st, r4, sw);
     ev_end(s);
     if (e != hipSuccess) return hipfail(s, e, "combined step launch");
     if (!r4) {  // r = 4: the second pair writes buffer 0 again
@@ -1158,7 +1202,8 @@ int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
     }
   } else {
     ev_begin(s, 0);
-    e = launch_em_stream(A, s->seg0, s->depth0, s->st);
+    if (win && s->uni) e = launch_em_stream_list(A, s->d_nblk, (int)s->h_nblk.size(), seg, s->st);
+    else e = launch_em_stream(A, seg, depth, s->st, sw);
     ev_end(s);
     if (e != hipSuccess) return hipfail(s, e, "base EM launch");
   }
@@ -1240,7 +1285,147 @@ int base_step(dmr_sim* s, StepCtx* cx = nullptr) {
   }
   s->ccur = 1 - c;
   s->step++;
-  return step_close(s, cx);
+  return DMR_OK;
+}
+
+// cells around the patch that the far launch of a t-step group leaves to the
+// step-by-step launches: within t + 1 of it ({i0, j0, i1, j1}); the fine level
+// reaches no further in t steps
+void near_rect(const dmr_sim* s, int t, int r[4]) {
+  r[0] = s->ext[0] - t - 1; r[1] = s->ext[1] - t - 1;
+  r[2] = s->ext[2] + t + 2; r[3] = s->ext[3] + t + 2;
+}
+
+// the streaming waves that cover that region and the t cells around it from
+// which its values follow
+StreamWin near_window(const dmr_sim* s, int t) {
+  int r[4];
+  near_rect(s, t, r);
+  const int x0 = std::max(r[0] - t, 0), y0 = std::max(r[1] - t, 0);
+  const int x1 = std::min(r[2] + t, s->p.nx + 1), y1 = std::min(r[3] + t, s->p.ny + 1);
+  const int nseg = stream_segments(s->p.ny, kNearSeg);
+  StreamWin w;
+  w.cw0 = x0 / 62;
+  w.ncw = (x1 - 1) / 62 + 1 - w.cw0;
+  w.k0 = std::min(y0 / kNearSeg, nseg - 1);
+  w.nk = std::min((y1 - 1) / kNearSeg + 1, nseg) - w.k0;
+  return w;
+}
+
+// union of blocks: the blocks within two blocks' reach of t + 1 cells of an
+// active one, and the streaming blocks that cover those and the t cells
+// around them
+int near_blocks(dmr_sim* s) {
+  const dmr_params& p = s->p;
+  const int Bk = p.block, NBx = p.nx / Bk, NBy = p.ny / Bk;
+  const int d = (kMultiSteps + 1 + Bk - 1) / Bk;
+  auto dilate = [&](const std::vector<uint8_t>& a, std::vector<uint8_t>* o) {
+    o->assign((size_t)NBx * NBy, 0);
+    for (int by = 0; by < NBy; by++)
+      for (int bx = 0; bx < NBx; bx++)
+        if (a[(size_t)by * NBx + bx])
+          for (int y = std::max(by - d, 0); y <= std::min(by + d, NBy - 1); y++)
+            for (int x = std::max(bx - d, 0); x <= std::min(bx + d, NBx - 1); x++)
+              (*o)[(size_t)y * NBx + x] = 1;
+  };
+  dilate(s->h_act, &s->h_near);
+  std::vector<uint8_t> cover;
+  dilate(s->h_near, &cover);
+  const int nbx = stream_blocks_x(p.nx), nseg = stream_segments(p.ny, kNearSeg);
+  const int cols = 62 * (kThreads / 64);
+  s->h_nblk.clear();
+  for (int k = 0; k < nseg; k++) {
+    const int j1 = k == nseg - 1 ? p.ny : (k + 1) * kNearSeg - 1;
+    const int yb0 = std::min(k * kNearSeg / Bk, NBy - 1), yb1 = std::min(j1 / Bk, NBy - 1);
+    for (int b = 0; b < nbx; b++) {
+      const int xb0 = std::min(b * cols / Bk, NBx - 1);
+      const int xb1 = std::min((b * cols + cols - 1) / Bk, NBx - 1);
+      bool hit = false;
+      for (int y = yb0; y <= yb1 && !hit; y++)
+        for (int x = xb0; x <= xb1 && !hit; x++) hit = cover[(size_t)y * NBx + x] != 0;
+      if (hit) s->h_nblk.push_back(make_int2(b, k));
+    }
+  }
+  s->near_share = (double)s->h_nblk.size() / ((double)nbx * nseg);
+  HIPCHK(s, hipMemcpyAsync(s->d_near, s->h_near.data(), s->h_near.size(), hipMemcpyHostToDevice,
+                           s->st));
+  if (!s->h_nblk.empty())
+    HIPCHK(s, hipMemcpyAsync(s->d_nblk, s->h_nblk.data(), s->h_nblk.size() * sizeof(int2),
+                             hipMemcpyHostToDevice, s->st));
+  HIPCHK(s, hipStreamSynchronize(s->st));
+  s->near_gen = s->ugen;
+  return DMR_OK;
+}
+
+// whether t steps of a run with a fine level are split (split_steps)
+bool can_split(dmr_sim* s, int t) {
+  const dmr_params& p = s->p;
+  // Where the base level is what a step waits for; on smaller grids the patch's
+  // chain is, and the far launch only adds to it.  Per step, one launch a step
+  // against split: patch r = 2: 512x256 7.6 / 8.6 us, 704x352 9.8 / 9.5,
+  // 1024x512 11.0 / 10.2, 4096x2048 123 / 47; union of blocks: 704x352 22.6 /
+  // 23.3, 1024x512 24.4 / 24.0, 4096x2048 137 / 67; r = 4: 1024x512 18.8 /
+  // 19.3, 1440x720 23.6 / 21.3.
+  const long least = s->split_min >= 0 ? s->split_min
+                     : p.r == 4       ? 1L << 20
+                     : s->uni         ? 1L << 19
+                                      : 1L << 18;
+  if (t < 2 || !s->has_patch || (long)p.nx * p.ny < least) return false;
+  if (s->uni) {
+    if (log2i(p.block) > 30 || (p.block & (p.block - 1))) return false;
+    return s->near_gen == s->ugen && s->near_share <= 0.5;
+  }
+  const StreamWin w = near_window(s, t);
+  return (double)w.ncw * 62 * w.nk * kNearSeg <= 0.5 * (p.nx + 1.0) * (p.ny + 1.0);
+}
+
+// t base steps of a run with a fine level.  Within t steps the fine level
+// reaches t cells into the base level: the cells around it are stepped with it
+// one step at a time, on scratch planes, and the rest takes the t steps in
+// one launch (dmr_multi.hip) from the same state.  Three sets of base-level
+// planes: the state entering, and two that the steps around the fine level
+// alternate between, such that the last lands where the far launch writes.
+// The far launch comes last: it puts right what the step-by-step launches
+// leave in the outer cells of their region, whose neighbours they do not step.
+int split_steps(dmr_sim* s, int t, bool last) {
+  const int c = s->ccur;
+  Level& C = s->L0;
+  MultiArgs M{};
+  make_base_em(s, c, s->ncur, &M.em);
+  M.t = t;
+  for (int k = 0; k < t; k++) incident_values(s, s->step + k, &M.src[k].x, &M.src[k].y);
+  NearWin win{};
+  if (!s->uni) win.stream = near_window(s, t);
+  win.acc1 = s->far[5];
+  for (int k = 0; k < t; k++) {
+    if (int rc = em_part(s, nullptr, &win)) return rc;
+    if (k) continue;
+    // the state entering leaves the two planes that alternate
+    std::swap(C.hz[c], s->far[0]); std::swap(C.ex[c], s->far[1]); std::swap(C.ey[c], s->far[2]);
+    std::swap(C.jx[c], s->far[3]); std::swap(C.jy[c], s->far[4]);
+    std::swap(C.acc, s->far[5]);
+    win.acc1 = C.acc;
+  }
+  const int g = s->ccur;
+  M.em.hz1 = C.hz[g]; M.em.ex1 = C.ex[g]; M.em.ey1 = C.ey[g];
+  M.em.jx1 = C.jx[g]; M.em.jy1 = C.jy[g];
+  M.em.acc1 = C.acc;
+  M.hzp = last ? C.hz[1 - g] : nullptr;
+  if (s->uni) {
+    M.near = s->d_near;
+    M.nbs = log2i(s->p.block);
+    M.nnx = s->p.nx / s->p.block;
+  } else {
+    int r[4];
+    near_rect(s, t, r);
+    M.sL = r[0]; M.sB = r[1]; M.sR = r[2]; M.sT = r[3];
+  }
+  const int waves = s->multi_w ? s->multi_w : multi_waves(s->p.nx, s->p.ny, t);
+  ev_begin(s, 0, 0);  // its steps are counted with the launches around the fine level
+  const hipError_t e = launch_em_multi(M, waves, s->st);
+  ev_end(s);
+  if (e != hipSuccess) return hipfail(s, e, "base EM launch");
+  return step_close(s, nullptr);
 }
 
 // Several base steps in one launch where no patch takes part in them; the
@@ -1251,7 +1436,6 @@ int multi_steps(dmr_sim* s, int t, bool last) {
   Level& C = s->L0;
   MultiArgs M{};
   make_base_em(s, c, s->ncur, &M.em);
-  M.acc1 = C.acc;
   M.hzp = last ? s->hzp : nullptr;
   M.t = t;
   for (int k = 0; k < t; k++) incident_values(s, s->step + k, &M.src[k].x, &M.src[k].y);
@@ -1395,6 +1579,8 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   s->d_err = (int*)(s->ws + lay.off_err);
   s->stage = (float*)(s->ws + lay.off_stage);
   s->hzp = (float*)(s->ws + lay.off_hzp);
+  if (refined(p))
+    for (int q = 0; q < 6; q++) s->far[q] = (float*)(s->ws + lay.off_far) + q * lay.plane0;
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
     s->uni = true;
     const size_t nb = (size_t)lay.NB;
@@ -1403,6 +1589,8 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     s->d_tiles = (int2*)(s->ws + lay.off_tiles);
     s->d_ptiles = s->d_tiles + align256(lay.max_tiles * sizeof(int2)) / sizeof(int2);
     s->d_cfb = (float*)(s->ws + lay.off_cfb);
+    s->d_near = (uint8_t*)(s->ws + lay.off_near);
+    s->d_nblk = (int2*)(s->ws + lay.off_nblk);
     s->h_act.assign(nb, 0);
     if (const char* f = getenv("DMR_UTY")) {
       const int v = atoi(f);
@@ -1414,7 +1602,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   // one launch per coarse step pays off where launch latency dominates; on
   // bandwidth-bound grids the base kernel's own launch shape is faster
   s->combine = (long)p->nx * p->ny <= (1L << 21);
-  if (const char* f = getenv("DMR_COMBINE")) s->combine = atoi(f) != 0;
+  if (const char* f = getenv("DMR_COMBINE")) s->combine = s->near_combine = atoi(f) != 0;
   // r = 2: the base step and both substeps in one launch; r = 4: the base
   // step and the first pair of substeps (4-row tiles), then the second pair
   if (const char* f = getenv("DMR_FUSE_MAX")) s->fuse_max = atol(f);
@@ -1428,6 +1616,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     s->multi_t = std::min(std::max(s->multi_t, 1), kMultiSteps);
     s->multi_w = s->multi_w < 5 ? 0 : std::min(s->multi_w, 16);
   }
+  if (const char* f = getenv("DMR_SPLIT_MIN")) s->split_min = atol(f);
   if (const char* f = getenv("DMR_CONT_MERGE")) s->cont_merge = atoi(f) != 0 ? 1 : 0;
   if (const char* f = getenv("DMR_FINE_SEG")) s->fseg = atoi(f) >= 2 ? atoi(f) : 0;
   if (const char* f = getenv("DMR_FINE_DEPTH")) s->fdepth = atoi(f) >= 4 ? 4 : 2;
@@ -1523,12 +1712,16 @@ int dmr_step(dmr_sim* s, int64_t n) {
     const int64_t left = std::min<int64_t>(n, blk);
     const int most = s->multi_t;
     int t = 1;
-    if (!s->has_patch && left > 1 && most > 1) {
+    if (left > 1 && most > 1) {
       const int64_t parts = (left + most - 1) / most;
       t = (int)((left + parts - 1) / parts);
     }
+    if (s->has_patch && s->uni && s->near_gen != s->ugen)
+      if (int rc = near_blocks(s)) return rc;
+    const bool split = can_split(s, t);
+    if (s->has_patch && !split) t = 1;
     const bool last = t == n || (s->p.mode == DMR_DYNAMIC && (s->step + t) % s->p.regrid_every == 0);
-    const int rc = t > 1 ? multi_steps(s, t, last) : base_step(s);
+    const int rc = split ? split_steps(s, t, last) : t > 1 ? multi_steps(s, t, last) : base_step(s);
     if (rc) { ev_close(s); return rc; }
     n -= t;
   }

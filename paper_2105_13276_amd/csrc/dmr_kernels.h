@@ -29,6 +29,7 @@ struct EMArgs {
   float *hz1, *ex1, *ey1, *jx1, *jy1;        // state at step n+1 (written)
   const float* n;                            // density at the nodes
   float* acc;                                // window accumulator (in place)
+  float* acc1;                               // base level: where it is written
   int pitch;
   int L, B, R, T;  // active cells [L,R) x [B,T); nodes [L,R] x [B,T]
   float S;         // c dt / dx
@@ -87,11 +88,16 @@ struct EMArgs {
 // several base-level steps in one launch (dmr_multi.hip)
 constexpr int kMultiSteps = 8;   // most steps of a launch
 struct MultiArgs {
-  EMArgs em;     // reads buffer 0, writes buffer 1; the window is read at em.acc
-  float* acc1;   // window accumulator after the steps (em.acc: in place)
+  EMArgs em;     // reads buffer 0 and em.acc, writes buffer 1 and em.acc1
   float* hzp;    // Hz entering the last step (the half level before), nullable
   int t;         // steps
   int ntx, nty;  // blocks along x and y (set by the launcher)
+  // cells that another launch steps (around the patch) and this one does not
+  // write: the rectangle [sL, sR) x [sB, sT) (empty: none), or, with near, the
+  // blocks of 2^nbs cells with near != 0 of a map [.][nnx]
+  int sL, sB, sR, sT;
+  const uint8_t* near;
+  int nbs, nnx;
   float2 src[kMultiSteps];  // incident Ey, eta0 Hz of each step
 };
 
@@ -161,6 +167,12 @@ struct ProlongArgs {
   const float* seed;  // union with keep_n: the fine density of new nodes (pitched)
 };
 
+// the waves of a base-level streaming launch: 62-column waves [cw0, cw0 + ncw)
+// of the row segments [k0, k0 + nk); ncw 0: all of the grid
+struct StreamWin {
+  int cw0 = 0, ncw = 0, k0 = 0, nk = 0;
+};
+
 // patch substep kernel, 64 x ty tiles of nt threads (256 or 1024)
 hipError_t launch_em(const EMArgs& A, bool fine, int ty, int nt, hipStream_t st);
 // the same substep on the union of blocks: the 64 x ty tiles (tile column,
@@ -186,9 +198,14 @@ hipError_t launch_fine2_fast(const EMArgs& A, int tw, hipStream_t st);
 // base-level step (C, with the patch's coarse entities skipped) and both patch
 // substeps (F, coarse boundary E computed in the tiles) in one launch
 hipError_t launch_dmr_step(const EMArgs& C, const EMArgs& F, int seg, int depth, int ty,
-                           int tw, hipStream_t st, bool r4 = false);
+                           int tw, hipStream_t st, bool r4 = false, StreamWin win = StreamWin());
 // base level, column-streaming kernel; seg = rows per segment (>= 2)
-hipError_t launch_em_stream(const EMArgs& A, int seg, int depth, hipStream_t st);
+hipError_t launch_em_stream(const EMArgs& A, int seg, int depth, hipStream_t st,
+                            StreamWin win = StreamWin());
+// the same over a list of (group of four 62-column waves, segment); 2 rows of
+// loads in flight
+hipError_t launch_em_stream_list(const EMArgs& A, const int2* blk, int nblk, int seg,
+                                 hipStream_t st);
 // one patch substep (rectangle, r = 2) in column-streaming form, for large
 // patches; seg = rows per segment (even), depth = rows of loads in flight
 hipError_t launch_fine_stream(const EMArgs& A, int seg, int depth, hipStream_t st);

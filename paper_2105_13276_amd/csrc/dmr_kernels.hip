@@ -2447,14 +2447,14 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       }
       const float exl0 = __shfl_up(ex0, 1, 64);
       if (own && eyc)
-        str<O32>(A.acc, row_addr(A, i, 0),
+        str<O32>(A.acc1, row_addr(A, i, 0),
                  base_win(acc0, i > 0 ? exl0 : 0.f, i < NX ? ex0 : 0.f, 0.f, eyn_p, fxe, 2.f));
     }
     // window at node (i, j)
     const float exl = __shfl_up(exn, 1, 64);
     if (j > 0) {
       if (store && own)
-        str<O32>(A.acc, o, base_win(cur.acc, i > 0 ? exl : 0.f, i < NX ? exn : 0.f, eyn_p,
+        str<O32>(A.acc1, o, base_win(cur.acc, i > 0 ? exl : 0.f, i < NX ? exn : 0.f, eyn_p,
                                     j < NY ? eyn : 0.f, fxe, j < NY ? 1.f : 2.f));
     } else {
       acc0 = cur.acc;
@@ -2496,7 +2496,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       str<O32>(A.jy1, o, a * cur.jy + 2.f * kapy * (cur.ey + eyn));
     }
     const float exl = __shfl_up(exn, 1, 64);
-    if (store && own) str<O32>(A.acc, o, base_win(cur.acc, exl, exn, eyn_p, eyn));
+    if (store && own) str<O32>(A.acc1, o, base_win(cur.acc, exl, exn, eyn_p, eyn));
     hzn_p = hzn;
     eyn_p = eyn;
   };
@@ -2524,10 +2524,20 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
 }
 
 template <int DEPTH, bool ST = false>
-__global__ __launch_bounds__(kThreads) void k_em_stream(EMArgs A, int seg, int nseg, int nbx) {
-  const int b = xcd_band(blockIdx.x, nbx * nseg);
-  em_stream_body<DEPTH, ST>(A, (b % nbx) * (kThreads / 64) + (threadIdx.x >> 6), b / nbx, seg, nseg,
-                        A.ey_src, A.hz_src);
+__global__ __launch_bounds__(kThreads) void k_em_stream(EMArgs A, int seg, int nseg, int nbx,
+                                                        int nk, int cw0, int k0) {
+  const int b = xcd_band(blockIdx.x, nbx * nk);
+  em_stream_body<DEPTH, ST>(A, cw0 + (b % nbx) * (kThreads / 64) + (threadIdx.x >> 6), k0 + b / nbx,
+                            seg, nseg, A.ey_src, A.hz_src);
+}
+
+// over a list of (group of four 62-column waves, segment)
+template <int DEPTH>
+__global__ __launch_bounds__(kThreads) void k_em_stream_list(EMArgs A, const int2* __restrict__ blk,
+                                                             int seg, int nseg) {
+  const int2 b = blk[blockIdx.x];
+  em_stream_body<DEPTH>(A, b.x * (kThreads / 64) + (threadIdx.x >> 6), b.y, seg, nseg, A.ey_src,
+                        A.hz_src);
 }
 
 // batched form; the incident values of step k of the current interval come
@@ -2813,7 +2823,8 @@ __global__ __launch_bounds__(kThreads) void k_fine_stream(EMArgs A, int seg, int
 template <int DEPTH, int TY, bool ST = false, int TW = kTX, bool R4 = false>
 __global__ __launch_bounds__(step_threads(ST, TY)) void k_dmr_step(EMArgs C, EMArgs F, int seg,
                                                                        int nseg, int waves_x,
-                                                                       int ncb, int nbx_f) {
+                                                                       int ncb, int nbx_f,
+                                                                       int nk, int cw0, int k0) {
   constexpr int NTC = step_threads(ST, TY);
   // the patch tiles are the longer chain: they take the first blocks, which
   // the dispatcher starts first
@@ -2822,7 +2833,8 @@ __global__ __launch_bounds__(step_threads(ST, TY)) void k_dmr_step(EMArgs C, EMA
   if (b >= ntl) {
     const int w = xcd_band(b - ntl, ncb) * (NTC / 64) + (threadIdx.x >> 6);
     const int k = w / waves_x;
-    if (k < nseg) em_stream_body<DEPTH, ST>(C, w % waves_x, k, seg, nseg, C.ey_src, C.hz_src);
+    if (k < nk)
+      em_stream_body<DEPTH, ST>(C, cw0 + w % waves_x, k0 + k, seg, nseg, C.ey_src, C.hz_src);
     return;
   }
   if constexpr (!ST && TY == 4)
@@ -3024,21 +3036,22 @@ hipError_t launch_fine2(const EMArgs& A, int ty, int nt, hipStream_t st) {
 }
 
 hipError_t launch_dmr_step(const EMArgs& C, const EMArgs& F, int seg, int depth, int ty,
-                           int tw, hipStream_t st, bool r4) {
+                           int tw, hipStream_t st, bool r4, StreamWin win) {
   if (r4 && (ty != 4 || C.stix)) return hipErrorInvalidValue;  // 4-row tiles, no replay
-  const int waves_x = (C.R + 1 + 61) / 62;
   const int nseg = stream_segments(C.T, seg);
+  if (win.ncw <= 0) win = StreamWin{0, (C.R + 1 + 61) / 62, 0, nseg};
+  const int waves_x = win.ncw;
   const int nt = step_threads(C.stix != nullptr, ty);
   const int wpb = nt / 64;
-  const int ncb = (waves_x * nseg + wpb - 1) / wpb;
+  const int ncb = (waves_x * win.nk + wpb - 1) / wpb;
   if (ty != 4) tw = kTX;  // narrow tiles: 4-row tiles only
   else if (tw <= 0) tw = patch_tile_width(F, ncb);
   const int nbx_f = (F.R - F.L + 1 + tw - 1) / tw;
   const int nby_f = (F.T - F.B + 1 + ty - 1) / ty;
   const dim3 g(ncb + nbx_f * nby_f), blk(nt);
-#define DMR_STEP(D, T_, W_) hipLaunchKernelGGL((k_dmr_step<D, T_, false, W_>), g, blk, 0, st, C, F, seg, nseg, waves_x, ncb, nbx_f)
-#define DMR_STEP_ST(D, T_, W_) hipLaunchKernelGGL((k_dmr_step<D, T_, true, W_>), g, blk, 0, st, C, F, seg, nseg, waves_x, ncb, nbx_f)
-#define DMR_STEP_R4(D, W_) hipLaunchKernelGGL((k_dmr_step<D, 4, false, W_, true>), g, blk, 0, st, C, F, seg, nseg, waves_x, ncb, nbx_f)
+#define DMR_STEP(D, T_, W_) hipLaunchKernelGGL((k_dmr_step<D, T_, false, W_>), g, blk, 0, st, C, F, seg, nseg, waves_x, ncb, nbx_f, win.nk, win.cw0, win.k0)
+#define DMR_STEP_ST(D, T_, W_) hipLaunchKernelGGL((k_dmr_step<D, T_, true, W_>), g, blk, 0, st, C, F, seg, nseg, waves_x, ncb, nbx_f, win.nk, win.cw0, win.k0)
+#define DMR_STEP_R4(D, W_) hipLaunchKernelGGL((k_dmr_step<D, 4, false, W_, true>), g, blk, 0, st, C, F, seg, nseg, waves_x, ncb, nbx_f, win.nk, win.cw0, win.k0)
   if (r4) {
     if (depth >= 4) { if (tw == 16) DMR_STEP_R4(4, 16); else if (tw == 32) DMR_STEP_R4(4, 32); else DMR_STEP_R4(4, kTX); }
     else { if (tw == 16) DMR_STEP_R4(2, 16); else if (tw == 32) DMR_STEP_R4(2, 32); else DMR_STEP_R4(2, kTX); }
@@ -3129,18 +3142,27 @@ int stream_segments(int NY, int seg) {
   return nseg;
 }
 
-hipError_t launch_em_stream(const EMArgs& A, int seg, int depth, hipStream_t st) {
-  const int waves = (A.R + 1 + 61) / 62;
+hipError_t launch_em_stream_list(const EMArgs& A, const int2* blk, int nblk, int seg,
+                                 hipStream_t st) {
+  if (nblk <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_em_stream_list<2>, dim3(nblk), dim3(kThreads), 0, st, A, blk, seg,
+                     stream_segments(A.T, seg));
+  return hipGetLastError();
+}
+
+hipError_t launch_em_stream(const EMArgs& A, int seg, int depth, hipStream_t st, StreamWin win) {
   const int nseg = stream_segments(A.T, seg);
-  const int nbx = (waves + kThreads / 64 - 1) / (kThreads / 64);
-  dim3 g(nbx * nseg);
+  if (win.ncw <= 0) win = StreamWin{0, (A.R + 1 + 61) / 62, 0, nseg};
+  const int nbx = (win.ncw + kThreads / 64 - 1) / (kThreads / 64);
+  const int nk = win.nk, cw0 = win.cw0, k0 = win.k0;
+  dim3 g(nbx * nk);
   if (A.stix) {  // replay: stores for the adjoint
-    if (depth >= 4) hipLaunchKernelGGL((k_em_stream<4, true>), g, dim3(kThreads), 0, st, A, seg, nseg, nbx);
-    else hipLaunchKernelGGL((k_em_stream<2, true>), g, dim3(kThreads), 0, st, A, seg, nseg, nbx);
+    if (depth >= 4) hipLaunchKernelGGL((k_em_stream<4, true>), g, dim3(kThreads), 0, st, A, seg, nseg, nbx, nk, cw0, k0);
+    else hipLaunchKernelGGL((k_em_stream<2, true>), g, dim3(kThreads), 0, st, A, seg, nseg, nbx, nk, cw0, k0);
   } else if (depth >= 4) {
-    hipLaunchKernelGGL(k_em_stream<4>, g, dim3(kThreads), 0, st, A, seg, nseg, nbx);
+    hipLaunchKernelGGL(k_em_stream<4>, g, dim3(kThreads), 0, st, A, seg, nseg, nbx, nk, cw0, k0);
   } else {
-    hipLaunchKernelGGL(k_em_stream<2>, g, dim3(kThreads), 0, st, A, seg, nseg, nbx);
+    hipLaunchKernelGGL(k_em_stream<2>, g, dim3(kThreads), 0, st, A, seg, nseg, nbx, nk, cw0, k0);
   }
   return hipGetLastError();
 }

@@ -104,6 +104,14 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
     e[2][lane] = ey[R - 1];
   };
 
+  // whether this launch writes the entities at (i, j)
+  const bool in_sx = i >= M.sL && i < M.sR;
+  auto mine = [&](int j) {
+    if (M.near)
+      return M.near[(size_t)(min(j, NY - 1) >> M.nbs) * M.nnx + (min(i, NX - 1) >> M.nbs)] == 0;
+    return !(in_sx && j >= M.sB && j < M.sT);
+  };
+
   for (int s = 0; s < t; s++) {
     const int b = (s & 1) * nw;
     publish(s & 1);
@@ -112,7 +120,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
 #pragma unroll
       for (int r = 0; r < R; r++) {
         const int j = jt + r;
-        if (j >= own_lo && j < own_hi && j < NY && i >= own_x && lane < 64 - t && i < NX)
+        if (j >= own_lo && j < own_hi && j < NY && i >= own_x && lane < 64 - t && i < NX && mine(j))
           M.hzp[(size_t)j * A.pitch + i] = hz[r];
       }
     }
@@ -192,7 +200,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
 #pragma unroll
   for (int r = 0; r < R; r++) {
     const int j = jt + r;
-    if (j < own_lo || j >= own_hi) continue;
+    if (j < own_lo || j >= own_hi || !mine(j)) continue;
     const size_t ro = (size_t)j * A.pitch;
     auto put = [&](float* p, float v) { *(float*)((char*)(p + ro) + o) = v; };
     if (!XE || i < NX) {
@@ -204,7 +212,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
       put(A.ey1, ey[r]);
       put(A.jy1, jy[r]);
     }
-    put(M.acc1, ac[r]);
+    put(A.acc1, ac[r]);
   }
 }
 
@@ -230,6 +238,9 @@ __global__ __launch_bounds__(64 * NW, EU) void k_em_multi(MultiArgs M) {
   if (y0 <= 0 && NY - y0 < rows) y0 = NY % R == 0 ? -1 : 0;
   else if (y0 <= 0 && -y0 % R == R - 1) y0++;
   else if (y0 > 0 && NY - y0 < rows && (NY - y0) % R == 0) y0--;
+  // nothing of it is this launch's to write
+  if (own_x >= M.sL && min(own_x + 64 - 2 * t, NX + 1) <= M.sR && own_lo >= M.sB && own_hi <= M.sT)
+    return;
   const bool xe = x0 < 1 || x0 + 63 > NX - 1 || (A.is > 0 && A.is >= x0 && A.is - 1 <= x0 + 63);
   // (chosen per wave; every form passes the same barriers)
   const int jt = y0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * R;

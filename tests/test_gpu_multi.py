@@ -65,3 +65,52 @@ def test_several_steps_in_one_launch(nx, ny, cpl, bc_x, bc_y, src, multi):
     # the header's unused bytes apart; as numbers (a PEC zero may be -0)
     assert np.array_equal(sa[:72], sb[:72])
     assert np.array_equal(sa[256:].view(np.float32), sb[256:].view(np.float32))
+
+
+def _refined(kind):
+    lam = W.C0 / 110e9
+    if kind == "r4":
+        cfg = W.make(160, 112, 16, "dynamic", 1, r=4, block=8, erms_over_ebd=3.0)
+    else:
+        cfg = W.make(256, 160, 32, "dynamic", 1, erms_over_ebd=3.0,
+                     regrid_rule="union" if kind == "union" else "blocks")
+    if kind == "static":  # a patch off the block lines, two cells from the wall margin
+        cfg.update(mode="static", static_ext=(101, 17, 140, 41))
+    if kind == "wide":    # too large a share of the grid: one launch a step
+        cfg.update(mode="static", static_ext=(30, 20, 240, 140))
+    cfg["regrid_every"] = 4 * (cfg["steps_per_period"] // 8)
+    dx = lam / cfg["cells_per_lambda"]
+    at = [(0.55, 0.4)] if kind != "union" else [(0.4, 0.3), (0.75, 0.7)]
+    centres = [(x * cfg["nx"] * dx, y * cfg["ny"] * dx) for x, y in at]
+    return cfg, W.seeds(cfg, centres, [1e17] * len(at))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["rect", "r4", "union", "static", "wide"])
+def test_steps_split_around_the_fine_level(kind, monkeypatch):
+    """Groups of steps split into the cells around the fine level (one launch a
+    step) and the rest (one launch a group) against one launch per step, over
+    growths, with stretches that end inside a window block: the same bits on
+    both levels, also after a restart."""
+    cfg, (sb, sf) = _refined(kind)
+    runs = []
+    for env in ({"DMR_MULTI": "1"}, {"DMR_SPLIT_MIN": "0"}, {"DMR_SPLIT_MIN": "0", "DMR_MULTI": "3"}):
+        for k in ("DMR_MULTI", "DMR_SPLIT_MIN"):
+            monkeypatch.delenv(k, raising=False)
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        s = B.Sim(cfg, sb, sf)
+        got = []
+        for n in (5, 100, 61):
+            s.step(n)
+            got.append({(f, lv): s.get(f, lv) for lv in (0, 1) for f in FIELDS})
+            got[-1]["patch"] = np.array(s.patch())
+        s.load(s.save())
+        s.step(30)
+        got.append({(f, lv): s.get(f, lv) for lv in (0, 1) for f in FIELDS})
+        s.sync()
+        runs.append(got)
+    for other in runs[1:]:
+        for x, y in zip(runs[0], other):
+            for f in x:
+                assert np.array_equal(x[f], y[f]), f
