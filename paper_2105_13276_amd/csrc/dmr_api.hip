@@ -2782,8 +2782,25 @@ struct dmr_batch {
   std::vector<EMArgs> h_fem2, h_cem, h_floc;
   std::vector<int2> h_blk_comb;
   bool use_graph = true, tuned = false, forced = false;
+  // Groups of tg steps split around the fine levels, as split_steps (0: none).
+  // The base-level planes of the state change places with the third set after
+  // each group (gp: odd number of groups since the tables were built); every
+  // table is built for both.  Steps of a group: phase 0 the first, 1 the odd
+  // ones, 2 the others (which planes they read and write).
+  int tg = 0, gp = 0, far_waves = 12;
+  EMArgs* d_nem = nullptr;    // [2 gp][2 density][3 phases][count] base level, near
+  EMArgs* d_nfem = nullptr;   // [2][2][3][rf][count] patch, one launch a substep
+  EMArgs* d_nfem2 = nullptr;  // [2][2][3][2][count] patch, two substeps a launch
+  MultiArgs* d_multi = nullptr;  // [2][2][count]
+  int2 *d_blk_near = nullptr, *d_blk_far = nullptr;
+  int nblk_near = 0, nblk_far = 0;
+  size_t cap_far = 0;
+  std::vector<EMArgs> h_nem, h_nfem, h_nfem2;
+  std::vector<MultiArgs> h_multi;
+  std::vector<int2> h_blk_near, h_blk_far;
   hipGraphExec_t gexec = nullptr;
   bool graph_ok = false;
+  int graph_gp = 0;  // gp it was captured at
   // host copies of the tables (kept alive until their upload completes)
   std::vector<EMArgs> h_em, h_fem;
   std::vector<ContArgs> h_cont, h_fcont;
@@ -2802,6 +2819,8 @@ struct BatchLayout {
   size_t off_em = 0, off_fem = 0, off_cont = 0, off_fcont = 0, off_blk_base = 0,
          off_blk_fine = 0, off_blk_cont = 0, off_blk_fcont = 0, off_src = 0, total = 0;
   size_t off_fem2 = 0, off_cem = 0, off_floc = 0, off_blk_comb = 0;
+  size_t off_nem = 0, off_nfem = 0, off_nfem2 = 0, off_multi = 0, off_blk_near = 0,
+         off_blk_far = 0, cap_far = 0;
   size_t cap_base = 0, cap_fine = 0, cap_cont = 0, cap_fcont = 0, cap_comb = 0;
 };
 
@@ -2846,11 +2865,14 @@ int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* wh
       L->cap_fine += t;
       L->cap_fcont += t;
     }
+    // the far launches' blocks: at least 48 x 16 cells each
+    L->cap_far += (size_t)((nx + 1 + 47) / 48) * ((ny + 1 + 15) / 16);
   }
-  L->off_em = off;    off += align256(sizeof(EMArgs) * 4 * count);
-  L->off_fem = off;   off += align256(sizeof(EMArgs) * 4 * L->rf * count);
-  L->off_cont = off;  off += align256(sizeof(ContArgs) * 2 * count);
-  L->off_fcont = off; off += align256(sizeof(ContArgs) * 2 * count);
+  // (two of each argument table: see dmr_batch::gp)
+  L->off_em = off;    off += align256(sizeof(EMArgs) * 2 * 4 * count);
+  L->off_fem = off;   off += align256(sizeof(EMArgs) * 2 * 4 * L->rf * count);
+  L->off_cont = off;  off += align256(sizeof(ContArgs) * 2 * 2 * count);
+  L->off_fcont = off; off += align256(sizeof(ContArgs) * 2 * 2 * count);
   L->off_blk_base = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_base, 1));
   L->off_blk_fine = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_fine, 1));
   L->off_blk_cont = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_cont, 1));
@@ -2858,9 +2880,16 @@ int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* wh
   L->off_src = off;       off += align256(sizeof(float2) * kSrcSteps * count);
   // the two-substep and combined schedules: their argument tables, and the
   // combined table (groups of 16 base waves <= 4-wave blocks, plus the tiles)
-  L->off_fem2 = off;      off += align256(sizeof(EMArgs) * 4 * 2 * count);
-  L->off_cem = off;       off += align256(sizeof(EMArgs) * 4 * count);
-  L->off_floc = off;      off += align256(sizeof(EMArgs) * 4 * count);
+  L->off_fem2 = off;      off += align256(sizeof(EMArgs) * 2 * 4 * 2 * count);
+  L->off_cem = off;       off += align256(sizeof(EMArgs) * 2 * 4 * count);
+  L->off_floc = off;      off += align256(sizeof(EMArgs) * 2 * 4 * count);
+  // split groups
+  L->off_nem = off;       off += align256(sizeof(EMArgs) * 2 * 2 * 3 * count);
+  L->off_nfem = off;      off += align256(sizeof(EMArgs) * 2 * 2 * 3 * L->rf * count);
+  L->off_nfem2 = off;     off += align256(sizeof(EMArgs) * 2 * 2 * 3 * 2 * count);
+  L->off_multi = off;     off += align256(sizeof(MultiArgs) * 2 * 2 * count);
+  L->off_blk_near = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_base, 1));
+  L->off_blk_far = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_far, 1));
   L->cap_comb = L->cap_base + L->cap_fine;
   L->off_blk_comb = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_comb, 1));
   L->total = off;
@@ -2872,19 +2901,169 @@ int bfail(dmr_batch* b, int code, const char* what) {
   return code;
 }
 
+// Steps of a split group (0: the batch steps one launch a step).  A forced
+// launch configuration is taken as it is.  Even, so that a group ends in the
+// planes (and patch buffers) it started from but for the exchanged sets, and
+// the interval holds whole window blocks with an even number of groups, which
+// lets a captured interval be replayed.
+int batch_group(const dmr_batch* b) {
+  const dmr_sim* s0 = b->sims[0];
+  const int spb = s0->L0.spb;
+  if (b->forced || !refined(&s0->p) || s0->multi_t < 2) return 0;
+  const int t = std::min(s0->multi_t, spb) & ~1;
+  if (t < 2 || spb % 2 || kSrcSteps % spb || (kSrcSteps / spb) * (spb / t) % 2) return 0;
+  if (4 * b->far_waves - 2 * t < 16) return 0;  // (the table's capacity)
+  // worth it where the fine levels' surroundings are a small part of the cells
+  double near = 0, all = 0;
+  for (const dmr_sim* s : b->sims) {
+    const double cells = (s->p.nx + 1.0) * (s->p.ny + 1.0);
+    all += cells;
+    if (!s->has_patch) continue;
+    if (s->uni && (s->p.block & (s->p.block - 1))) return 0;
+    if (s->uni) {
+      double act = 0;
+      for (uint8_t v : s->h_act) act += v;
+      near += std::min(cells, act * s->p.block * s->p.block * 25.0);
+      continue;
+    }
+    const StreamWin w = near_window(s, t);
+    near += std::min(cells, (w.ncw + 3) / 4 * 248.0 * w.nk * kNearSeg);
+  }
+  return near <= 0.5 * all ? t : 0;
+}
+
+// exchange an instance's base-level state planes with its third set (what a
+// split group of an even number of steps does, from coarse parity 0)
+void swap_far(dmr_sim* s) {
+  Level& C = s->L0;
+  const int c = 0;
+  std::swap(C.hz[c], s->far[0]); std::swap(C.ex[c], s->far[1]); std::swap(C.ey[c], s->far[2]);
+  std::swap(C.jx[c], s->far[3]); std::swap(C.jy[c], s->far[4]);
+  std::swap(C.acc, s->far[5]);
+}
+
+// argument tables of instance k with its planes as they are now, as set g
+void batch_args(dmr_batch* b, int k, int g) {
+  const int n = b->count;
+  dmr_sim* s = b->sims[k];
+  EMArgs* em = &b->h_em[(size_t)g * 4 * n];
+  EMArgs* fem = &b->h_fem[(size_t)g * 4 * b->rf * n];
+  EMArgs* fem2 = &b->h_fem2[(size_t)g * 8 * n];
+  EMArgs* cem = &b->h_cem[(size_t)g * 4 * n];
+  EMArgs* floc = &b->h_floc[(size_t)g * 4 * n];
+  // a pair of substeps in one launch: r = 2 both, from buffer `from` to the
+  // other; r = 4 (1, 2) and (3, 4), buffer 0 -> 1 -> 0
+  auto pair_args = [&](int h, int c, int nc, int from, EMArgs* G) {
+    const Level& F = s->L1;
+    if (b->rf == 4) {
+      make_fine_em(s, 2 * h + 2, c, nc, b->ty, G);
+      em_args_level(G, F, h, 1 - h, F.n[nc], F.acc);
+      G->frac = (float)(2 * h + 1) / 4.f;
+      G->hz_save = nullptr;
+      G->hz_lo = nullptr;
+    } else {
+      make_fine_em(s, 2, c, nc, b->ty, G);  // restriction targets
+      em_args_level(G, F, from, 1 - from, F.n[nc], F.acc);
+      G->frac = 0.5f;  // time fraction of substep 1
+    }
+  };
+  for (int v = 0; v < 4; v++) {
+    const int c = v & 1, nc = v >> 1;
+    make_base_em(s, c, nc, &em[v * n + k]);
+    if (s->has_patch)
+      for (int m = 1; m <= b->rf; m++)
+        make_fine_em(s, m, c, nc, b->ty, &fem[((m - 1) * 4 + v) * n + k]);
+    cem[v * n + k] = em[v * n + k];
+    if (!s->has_patch || s->uni) continue;
+    // two-substep / combined launches read the patch state from one buffer
+    // and write the other; the buffers swap every step (batch_advance), so
+    // at coarse parity c the state is in buffer c ^ ccur of this build
+    const Level& C = s->L0;
+    for (int h = 0; h < (b->rf == 4 ? 2 : 1); h++)
+      pair_args(h, c, nc, c ^ s->ccur, &fem2[(h * 4 + v) * n + k]);
+    if (b->rf == 4) continue;
+    EMArgs& A = cem[v * n + k];
+    A.skip_on = 1;
+    A.sL = s->ext[0]; A.sB = s->ext[1]; A.sR = s->ext[2]; A.sT = s->ext[3];
+    EMArgs& H = floc[v * n + k];
+    H = fem2[v * n + k];
+    H.chz0 = C.hz[c]; H.cjx0 = C.jx[c]; H.cjy0 = C.jy[c]; H.cn0 = C.n[nc];
+    H.cS = C.S; H.cc1 = C.c1; H.ckn = C.kn; H.cis = s->p.tfsf_i;
+    H.cnx = s->p.nx; H.cny = s->p.ny;
+  }
+  for (int nc = 0; nc < 2; nc++) {
+    make_base_cont(s, nc, &b->h_cont[(size_t)(g * 2 + nc) * n + k]);
+    if (s->has_patch) make_fine_cont(s, nc, &b->h_fcont[(size_t)(g * 2 + nc) * n + k]);
+  }
+  if (!b->tg) return;
+  // split groups (they start at coarse parity 0)
+  const Level keep = s->L0;
+  auto set = [](Level* L, int b, float* const* q) {
+    L->hz[b] = q[0]; L->ex[b] = q[1]; L->ey[b] = q[2]; L->jx[b] = q[3]; L->jy[b] = q[4];
+  };
+  float* const st[3][5] = {{keep.hz[0], keep.ex[0], keep.ey[0], keep.jx[0], keep.jy[0]},
+                           {keep.hz[1], keep.ex[1], keep.ey[1], keep.jx[1], keep.jy[1]},
+                           {s->far[0], s->far[1], s->far[2], s->far[3], s->far[4]}};
+  const int from[3] = {0, 1, 2}, to[3] = {1, 2, 1};
+  for (int nc = 0; nc < 2; nc++) {
+    const size_t gv = (size_t)g * 2 + nc;
+    for (int ph = 0; ph < 3; ph++) {
+      set(&s->L0, 0, st[from[ph]]);
+      set(&s->L0, 1, st[to[ph]]);
+      if (ph) s->L0.acc = s->far[5];
+      EMArgs& A = b->h_nem[(gv * 3 + ph) * n + k];
+      make_base_em(s, 0, nc, &A);
+      A.acc1 = s->far[5];
+      A.seg = kNearSeg;
+      A.nseg = stream_segments(s->p.ny, kNearSeg);
+      if (s->has_patch) {
+        for (int m = 1; m <= b->rf; m++)
+          make_fine_em(s, m, 0, nc, b->ty, &b->h_nfem[((gv * 3 + ph) * b->rf + m - 1) * n + k]);
+        if (!s->uni)
+          for (int h = 0; h < (b->rf == 4 ? 2 : 1); h++)
+            pair_args(h, 0, nc, s->ccur ^ (ph & 1), &b->h_nfem2[((gv * 3 + ph) * 2 + h) * n + k]);
+      }
+      s->L0 = keep;
+    }
+    MultiArgs& M = b->h_multi[gv * n + k];
+    set(&s->L0, 1, st[2]);
+    make_base_em(s, 0, nc, &M.em);
+    s->L0 = keep;
+    M.em.acc1 = s->far[5];
+    M.hzp = keep.hz[1];
+    M.t = b->tg;
+    if (s->has_patch && s->uni) {
+      M.near = s->d_near;
+      M.nbs = log2i(s->p.block);
+      M.nnx = s->p.nx / s->p.block;
+    } else if (s->has_patch) {
+      int r[4];
+      near_rect(s, b->tg, r);
+      M.sL = r[0]; M.sB = r[1]; M.sR = r[2]; M.sT = r[3];
+    }
+    (void)multi_grid(&M, b->far_waves);
+  }
+}
+
 // rebuild block tables and argument arrays for the current configuration,
 // parities and patches; uploads on the batch stream and waits
 int batch_tables(dmr_batch* b) {
   const int n = b->count;
-  b->h_em.assign(4 * n, EMArgs{});
-  b->h_fem.assign(4 * b->rf * n, EMArgs{});
-  b->h_cont.assign(2 * n, ContArgs{});
-  b->h_fcont.assign(2 * n, ContArgs{});
-  b->h_fem2.assign(4 * 2 * n, EMArgs{});
-  b->h_cem.assign(4 * n, EMArgs{});
-  b->h_floc.assign(4 * n, EMArgs{});
+  b->gp = 0;
+  b->h_em.assign(2 * 4 * n, EMArgs{});
+  b->h_fem.assign(2 * 4 * b->rf * n, EMArgs{});
+  b->h_cont.assign(2 * 2 * n, ContArgs{});
+  b->h_fcont.assign(2 * 2 * n, ContArgs{});
+  b->h_fem2.assign(2 * 4 * 2 * n, EMArgs{});
+  b->h_cem.assign(2 * 4 * n, EMArgs{});
+  b->h_floc.assign(2 * 4 * n, EMArgs{});
+  b->h_nem.assign(2 * 2 * 3 * n, EMArgs{});
+  b->h_nfem.assign(2 * 2 * 3 * b->rf * n, EMArgs{});
+  b->h_nfem2.assign(2 * 2 * 3 * 2 * n, EMArgs{});
+  b->h_multi.assign(2 * 2 * n, MultiArgs{});
   b->h_blk_base.clear(); b->h_blk_fine.clear();
   b->h_blk_cont.clear(); b->h_blk_fcont.clear(); b->h_blk_comb.clear();
+  b->h_blk_near.clear(); b->h_blk_far.clear();
   // the two-substep and combined schedules need rectangular patches
   bool any_patch = false, any_union = false;
   for (const dmr_sim* s : b->sims) {
@@ -2895,6 +3074,7 @@ int batch_tables(dmr_batch* b) {
   b->can_combine = b->can_fuse && b->rf == 2;
   if ((b->sched == kSchedFused && !b->can_fuse) || (b->sched == kSchedCombined && !b->can_combine))
     b->sched = kSchedSeparate;
+  b->tg = batch_group(b);
   for (int k = 0; k < n; k++) {
     dmr_sim* s = b->sims[k];
     s->seg0 = b->seg;
@@ -2905,46 +3085,11 @@ int batch_tables(dmr_batch* b) {
       s->tyu_env = true;
       if (int rc = union_install(s)) return bfail(b, rc, s->err.c_str());
     }
-    for (int v = 0; v < 4; v++) {
-      const int c = v & 1, nc = v >> 1;
-      make_base_em(s, c, nc, &b->h_em[v * n + k]);
-      if (s->has_patch)
-        for (int m = 1; m <= b->rf; m++)
-          make_fine_em(s, m, c, nc, b->ty, &b->h_fem[((m - 1) * 4 + v) * n + k]);
-      b->h_cem[v * n + k] = b->h_em[v * n + k];
-      if (!s->has_patch || s->uni) continue;
-      // two-substep / combined launches read the patch state from one buffer
-      // and write the other; the buffers swap every step (batch_advance), so
-      // at coarse parity c the state is in buffer c ^ ccur of this build
-      const Level &C = s->L0, &F = s->L1;
-      const int rel = c ^ s->ccur;
-      if (b->rf == 4) {  // substeps (1, 2) then (3, 4): buffer 0 -> 1 -> 0
-        for (int h = 0; h < 2; h++) {
-          EMArgs& G = b->h_fem2[(h * 4 + v) * n + k];
-          make_fine_em(s, 2 * h + 2, c, nc, b->ty, &G);
-          em_args_level(&G, F, h, 1 - h, F.n[nc], F.acc);
-          G.frac = (float)(2 * h + 1) / 4.f;
-          G.hz_save = nullptr;
-          G.hz_lo = nullptr;
-        }
-      } else {
-        EMArgs& G = b->h_fem2[v * n + k];
-        make_fine_em(s, 2, c, nc, b->ty, &G);  // restriction targets
-        em_args_level(&G, F, rel, 1 - rel, F.n[nc], F.acc);
-        G.frac = 0.5f;  // time fraction of substep 1
-        EMArgs& A = b->h_cem[v * n + k];
-        A.skip_on = 1;
-        A.sL = s->ext[0]; A.sB = s->ext[1]; A.sR = s->ext[2]; A.sT = s->ext[3];
-        EMArgs& H = b->h_floc[v * n + k];
-        H = G;
-        H.chz0 = C.hz[c]; H.cjx0 = C.jx[c]; H.cjy0 = C.jy[c]; H.cn0 = C.n[nc];
-        H.cS = C.S; H.cc1 = C.c1; H.ckn = C.kn; H.cis = s->p.tfsf_i;
-        H.cnx = s->p.nx; H.cny = s->p.ny;
-      }
-    }
-    for (int nc = 0; nc < 2; nc++) {
-      make_base_cont(s, nc, &b->h_cont[nc * n + k]);
-      if (s->has_patch) make_fine_cont(s, nc, &b->h_fcont[nc * n + k]);
+    if (b->tg && s->uni && s->has_patch && s->near_gen != s->ugen)
+      if (int rc = near_blocks(s)) return bfail(b, rc, s->err.c_str());
+    for (int g = 0; g < 2; g++) {
+      batch_args(b, k, g);
+      if (refined(&s->p)) swap_far(s);  // (twice: back as it was)
     }
     const EMArgs& A = b->h_em[k];
     for (int t = 0; t < A.nbx * A.nseg; t++) b->h_blk_base.push_back(make_int2(k, t));
@@ -2964,6 +3109,18 @@ int batch_tables(dmr_batch* b) {
       const int hny = (H.T - H.B + 1 + 3) / 4;
       for (int t = 0; t < H.nbx * hny; t++) b->h_blk_fcont.push_back(make_int2(k, t));
     }
+    if (!b->tg) continue;
+    const MultiArgs& M = b->h_multi[k];
+    for (int t = 0; t < M.ntx * M.nty; t++) b->h_blk_far.push_back(make_int2(k, t));
+    const EMArgs& N = b->h_nem[k];
+    if (s->has_patch && s->uni) {
+      for (const int2& q : s->h_nblk) b->h_blk_near.push_back(make_int2(k, q.y * N.nbx + q.x));
+    } else if (s->has_patch) {
+      const StreamWin w = near_window(s, b->tg);
+      for (int q = w.k0; q < w.k0 + w.nk; q++)
+        for (int x = w.cw0 / 4; x <= (w.cw0 + w.ncw - 1) / 4; x++)
+          b->h_blk_near.push_back(make_int2(k, q * N.nbx + x));
+    }
   }
   // combined table: every instance's groups of 16 base waves, then the
   // patch tiles (the same 64 x ty tiles as h_blk_fine, coded -1 - t)
@@ -2976,28 +3133,28 @@ int batch_tables(dmr_batch* b) {
     for (const int2& t : b->h_blk_fine) b->h_blk_comb.push_back(make_int2(t.x, -1 - t.y));
   if (b->h_blk_base.size() > b->cap_base || b->h_blk_fine.size() > b->cap_fine ||
       b->h_blk_cont.size() > b->cap_cont || b->h_blk_fcont.size() > b->cap_fcont ||
-      b->h_blk_comb.size() > b->cap_comb)
+      b->h_blk_comb.size() > b->cap_comb || b->h_blk_near.size() > b->cap_base ||
+      b->h_blk_far.size() > b->cap_far)
     return bfail(b, DMR_EINVAL, "batch block table exceeds its workspace capacity");
   b->nblk_comb = (int)b->h_blk_comb.size();
   b->nblk_base = (int)b->h_blk_base.size();
   b->nblk_fine = (int)b->h_blk_fine.size();
   b->nblk_cont = (int)b->h_blk_cont.size();
   b->nblk_fcont = (int)b->h_blk_fcont.size();
-  auto up = [&](void* dst, const void* src, size_t bytes) {
-    return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, b->st) : hipSuccess;
+  b->nblk_near = (int)b->h_blk_near.size();
+  b->nblk_far = (int)b->h_blk_far.size();
+  auto up = [&](void* dst, const auto& v) {
+    const size_t bytes = v.size() * sizeof(v[0]);
+    return bytes ? hipMemcpyAsync(dst, v.data(), bytes, hipMemcpyHostToDevice, b->st) : hipSuccess;
   };
-  if (up(b->d_em, b->h_em.data(), b->h_em.size() * sizeof(EMArgs)) ||
-      up(b->d_fem, b->h_fem.data(), b->h_fem.size() * sizeof(EMArgs)) ||
-      up(b->d_cont, b->h_cont.data(), b->h_cont.size() * sizeof(ContArgs)) ||
-      up(b->d_fcont, b->h_fcont.data(), b->h_fcont.size() * sizeof(ContArgs)) ||
-      up(b->d_blk_base, b->h_blk_base.data(), b->h_blk_base.size() * sizeof(int2)) ||
-      up(b->d_blk_fine, b->h_blk_fine.data(), b->h_blk_fine.size() * sizeof(int2)) ||
-      up(b->d_blk_cont, b->h_blk_cont.data(), b->h_blk_cont.size() * sizeof(int2)) ||
-      up(b->d_blk_fcont, b->h_blk_fcont.data(), b->h_blk_fcont.size() * sizeof(int2)) ||
-      up(b->d_fem2, b->h_fem2.data(), b->h_fem2.size() * sizeof(EMArgs)) ||
-      up(b->d_cem, b->h_cem.data(), b->h_cem.size() * sizeof(EMArgs)) ||
-      up(b->d_floc, b->h_floc.data(), b->h_floc.size() * sizeof(EMArgs)) ||
-      up(b->d_blk_comb, b->h_blk_comb.data(), b->h_blk_comb.size() * sizeof(int2)) ||
+  if (up(b->d_em, b->h_em) || up(b->d_fem, b->h_fem) || up(b->d_cont, b->h_cont) ||
+      up(b->d_fcont, b->h_fcont) || up(b->d_blk_base, b->h_blk_base) ||
+      up(b->d_blk_fine, b->h_blk_fine) || up(b->d_blk_cont, b->h_blk_cont) ||
+      up(b->d_blk_fcont, b->h_blk_fcont) || up(b->d_fem2, b->h_fem2) || up(b->d_cem, b->h_cem) ||
+      up(b->d_floc, b->h_floc) || up(b->d_blk_comb, b->h_blk_comb) ||
+      (b->tg && (up(b->d_nem, b->h_nem) || up(b->d_nfem, b->h_nfem) || up(b->d_nfem2, b->h_nfem2) ||
+                 up(b->d_multi, b->h_multi) || up(b->d_blk_near, b->h_blk_near) ||
+                 up(b->d_blk_far, b->h_blk_far))) ||
       hipStreamSynchronize(b->st))
     return bfail(b, DMR_EHIP, "batch table upload failed");
   b->graph_ok = false;
@@ -3046,38 +3203,81 @@ void batch_advance(dmr_batch* b, int* slot, int* update) {
   }
 }
 
+// the same for a split group: the planes change places; an even number of
+// steps leaves the parities as they are
+void batch_advance_group(dmr_batch* b, int* slot, int* update) {
+  *slot = -1;
+  *update = 0;
+  for (dmr_sim* s : b->sims) {
+    swap_far(s);
+    s->step += b->tg;
+    if (s->p.continuity_on && s->step % s->L0.spb == 0) {
+      *slot = (int)(s->blocks % kRing);
+      s->blocks++;
+      *update = s->blocks >= kRing;
+      if (*update) s->ncur = 1 - s->ncur;
+    }
+  }
+  b->gp ^= 1;
+}
+
+// whether the next steps, `left` of which are to be done, are a split group
+bool batch_at_group(const dmr_batch* b, int64_t left) {
+  const dmr_sim* s = b->sims[0];
+  return b->tg && s->ccur == 0 && left >= b->tg && s->step % s->L0.spb % b->tg == 0 &&
+         s->step % s->L0.spb + b->tg <= s->L0.spb;
+}
+
+// window block / continuity of both levels, density buffers nc + 2 gp
+int batch_cont(dmr_batch* b, int nc, int slot, int update) {
+  if (slot < 0) return DMR_OK;
+  const int n = b->count;
+  hipError_t e = launch_cont_batch(b->d_cont + nc * n, b->d_blk_cont, b->nblk_cont, false, slot,
+                                   update, b->st);
+  if (e == hipSuccess && b->sims[0]->uni)
+    e = launch_cont_union_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, b->ty, slot,
+                                update, b->st);
+  else if (e == hipSuccess)
+    e = launch_cont_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, true, slot, update,
+                          b->st);
+  return e == hipSuccess ? DMR_OK : bfail(b, DMR_EHIP, "batched continuity launch");
+}
+
 // queue one base step of every instance (no growth test)
 int batch_launch_step(dmr_batch* b, hipEvent_t* tb, hipEvent_t* tf) {
   const int n = b->count;
   dmr_sim* s0 = b->sims[0];
   const int v = s0->ccur + 2 * s0->ncur;
-  const int nc = s0->ncur;
+  const int nc = s0->ncur + 2 * b->gp;
   const int k = (int)(s0->step - b->src_base);
   const bool uni = s0->uni;
+  const EMArgs *d_em = b->d_em + b->gp * 4 * n, *d_cem = b->d_cem + b->gp * 4 * n,
+               *d_floc = b->d_floc + b->gp * 4 * n, *d_fem2 = b->d_fem2 + b->gp * 8 * n,
+               *d_fem = b->d_fem + b->gp * 4 * b->rf * n;
   if (tb) (void)hipEventRecord(tb[0], b->st);
   hipError_t e = hipSuccess;
   if (b->sched == kSchedCombined) {
-    e = launch_dmr_step_batch(b->d_cem + v * n, b->d_floc + v * n, b->d_blk_comb, b->nblk_comb,
+    e = launch_dmr_step_batch(d_cem + v * n, d_floc + v * n, b->d_blk_comb, b->nblk_comb,
                               b->d_src, k, b->depth, b->ty, b->st);
     if (tb) (void)hipEventRecord(tb[1], b->st);
     if (tf) (void)hipEventRecord(tf[0], b->st);
     if (tf) (void)hipEventRecord(tf[1], b->st);
     if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched combined step launch");
   } else {
-    e = launch_em_stream_batch(b->d_em + v * n, b->d_blk_base, b->nblk_base, b->d_src, k,
+    e = launch_em_stream_batch(d_em + v * n, b->d_blk_base, b->nblk_base, b->d_src, k,
                                b->depth, b->st);
     if (tb) (void)hipEventRecord(tb[1], b->st);
     if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched base EM launch");
     if (tf) (void)hipEventRecord(tf[0], b->st);
     if (b->sched == kSchedFused) {
       for (int h = 0; h < (b->rf == 4 ? 2 : 1) && b->nblk_fine; h++) {
-        e = launch_fine2_batch(b->d_fem2 + (h * 4 + v) * n, b->d_blk_fine, b->nblk_fine, b->ty,
+        e = launch_fine2_batch(d_fem2 + (h * 4 + v) * n, b->d_blk_fine, b->nblk_fine, b->ty,
                                b->rf == 4, b->st);
         if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched two-substep launch");
       }
     } else {
       for (int m = 1; m <= b->rf && b->nblk_fine; m++) {
-        const EMArgs* fa = b->d_fem + ((m - 1) * 4 + v) * n;
+        const EMArgs* fa = d_fem + ((m - 1) * 4 + v) * n;
         e = uni ? launch_em_union_batch(fa, b->d_blk_fine, b->nblk_fine, b->ty, b->st)
                 : launch_em_batch(fa, b->d_blk_fine, b->nblk_fine, b->ty, b->st);
         if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched fine EM launch");
@@ -3087,18 +3287,41 @@ int batch_launch_step(dmr_batch* b, hipEvent_t* tb, hipEvent_t* tf) {
   }
   int slot, update;
   batch_advance(b, &slot, &update);
-  if (slot >= 0) {
-    e = launch_cont_batch(b->d_cont + nc * n, b->d_blk_cont, b->nblk_cont, false, slot,
-                          update, b->st);
-    if (e == hipSuccess && uni)
-      e = launch_cont_union_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, b->ty,
-                                  slot, update, b->st);
-    else if (e == hipSuccess)
-      e = launch_cont_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, true, slot,
-                            update, b->st);
-    if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched continuity launch");
+  return batch_cont(b, nc, slot, update);
+}
+
+// queue a split group of tg base steps of every instance; last: the growth
+// test follows
+int batch_launch_group(dmr_batch* b, bool last) {
+  const int n = b->count, nc = b->sims[0]->ncur;
+  const int k0 = (int)(b->sims[0]->step - b->src_base);
+  const bool uni = b->sims[0]->uni;
+  const size_t gv = (size_t)b->gp * 2 + nc;
+  hipError_t e = hipSuccess;
+  for (int k = 0; k < b->tg; k++) {
+    const size_t q = gv * 3 + (k == 0 ? 0 : (k & 1) ? 1 : 2);
+    e = launch_em_stream_batch(b->d_nem + q * n, b->d_blk_near, b->nblk_near, b->d_src, k0 + k, 2,
+                               b->st);
+    if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched base EM launch");
+    if (b->sched != kSchedSeparate) {
+      for (int h = 0; h < (b->rf == 4 ? 2 : 1) && b->nblk_fine && e == hipSuccess; h++)
+        e = launch_fine2_batch(b->d_nfem2 + (q * 2 + h) * n, b->d_blk_fine, b->nblk_fine, b->ty,
+                               b->rf == 4, b->st);
+    } else {
+      for (int m = 1; m <= b->rf && b->nblk_fine && e == hipSuccess; m++) {
+        const EMArgs* fa = b->d_nfem + (q * b->rf + m - 1) * n;
+        e = uni ? launch_em_union_batch(fa, b->d_blk_fine, b->nblk_fine, b->ty, b->st)
+                : launch_em_batch(fa, b->d_blk_fine, b->nblk_fine, b->ty, b->st);
+      }
+    }
+    if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched fine EM launch");
   }
-  return DMR_OK;
+  e = launch_em_multi_batch(b->d_multi + gv * n, b->d_blk_far, b->nblk_far, b->d_src, k0, b->tg,
+                            last, b->far_waves, b->st);
+  if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched base EM launch");
+  int slot, update;
+  batch_advance_group(b, &slot, &update);
+  return batch_cont(b, nc + 2 * b->gp, slot, update);
 }
 
 int batch_regrid(dmr_batch* b) {
@@ -3195,7 +3418,32 @@ int batch_tune(dmr_batch* b, int64_t* used) {
     return r;
   };
   float best = 1e30f;
-  if (!rc && (b->can_fuse || b->can_combine)) {
+  if (!rc && b->tg) {
+    // split groups: the patch launches of a group (separate or two substeps a
+    // launch) and their tile height, by timing a group of each
+    for (int sched = kSchedSeparate; sched <= kSchedFused && !rc; sched++) {
+      if (sched == kSchedFused && !b->can_fuse) continue;
+      for (int c = 0; c < nty && !rc; c++) {
+        b->sched = sched;
+        b->ty = kTyCand[c];
+        rc = batch_tables(b);
+        // to the next group (the candidates above stop anywhere)
+        while (!rc && !batch_at_group(b, b->tg)) {
+          if (b->sims[0]->step - b->src_base >= kSrcSteps) rc = batch_sources(b, b->sims[0]->step);
+          if (!rc) rc = batch_launch_step(b, nullptr, nullptr);
+          if (!rc) (*used)++;
+        }
+        (void)hipEventRecord(tb[0], b->st);
+        if (!rc) rc = batch_launch_group(b, true);
+        if (!rc) *used += b->tg;
+        (void)hipEventRecord(tf[1], b->st);
+        if (!rc && hipStreamSynchronize(b->st) != hipSuccess) rc = DMR_EHIP;
+        float t = 0.f;
+        (void)hipEventElapsedTime(&t, tb[0], tf[1]);
+        if (!rc && t < best) { best = t; bsched = sched; bty = kTyCand[c]; }
+      }
+    }
+  } else if (!rc && (b->can_fuse || b->can_combine)) {
     float t = 0.f;
     rc = step_ms(kSchedSeparate, bty, &t);
     best = t;
@@ -3217,6 +3465,21 @@ int batch_tune(dmr_batch* b, int64_t* used) {
   b->tuned = true;
   tune_cache().push_back({key, {bseg, bdep, bty, bsched}});
   return batch_tables(b);
+}
+
+// queue `steps` base steps (no growth test between them)
+int batch_run(dmr_batch* b, int64_t steps) {
+  int rc = DMR_OK;
+  while (steps > 0 && !rc) {
+    if (batch_at_group(b, steps)) {
+      rc = batch_launch_group(b, steps == b->tg);
+      steps -= b->tg;
+    } else {
+      rc = batch_launch_step(b, nullptr, nullptr);
+      steps--;
+    }
+  }
+  return rc;
 }
 
 int batch_step(dmr_batch* b, int64_t n) {
@@ -3243,13 +3506,14 @@ int batch_step(dmr_batch* b, int64_t n) {
     const bool whole = step % kSrcSteps == 0 && chunk == kSrcSteps &&
                        (!dyn || p.regrid_every % kSrcSteps == 0);
     if (b->use_graph && whole && steady) {
-      if (!b->graph_ok) {
+      if (!b->graph_ok || b->graph_gp != b->gp) {
+        b->graph_gp = b->gp;
         if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
         b->gexec = nullptr;
         hipGraph_t g = nullptr;
         if (hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal) != hipSuccess)
           return bfail(b, DMR_EHIP, "graph capture begin");
-        for (int q = 0; q < kSrcSteps && !rc; q++) rc = batch_launch_step(b, nullptr, nullptr);
+        rc = batch_run(b, kSrcSteps);
         hipError_t e = hipStreamEndCapture(b->st, &g);
         if (rc) return rc;
         if (e != hipSuccess || hipGraphInstantiate(&b->gexec, g, nullptr, nullptr, 0) != hipSuccess)
@@ -3260,10 +3524,18 @@ int batch_step(dmr_batch* b, int64_t n) {
       } else {
         if (hipGraphLaunch(b->gexec, b->st) != hipSuccess) return bfail(b, DMR_EHIP, "graph launch");
         int slot, update;
-        for (int q = 0; q < kSrcSteps; q++) batch_advance(b, &slot, &update);
+        for (int q = 0; q < kSrcSteps;) {
+          if (batch_at_group(b, kSrcSteps - q)) {
+            batch_advance_group(b, &slot, &update);
+            q += b->tg;
+          } else {
+            batch_advance(b, &slot, &update);
+            q++;
+          }
+        }
       }
     } else {
-      for (int64_t q = 0; q < chunk && !rc; q++) rc = batch_launch_step(b, nullptr, nullptr);
+      rc = batch_run(b, chunk);
       if (rc) return rc;
     }
     n -= chunk;
@@ -3346,6 +3618,13 @@ int dmr_batch_create(const dmr_params* p, int count, const double* const* seed_b
   b->d_floc = (EMArgs*)(b->ws + L.off_floc);
   b->d_blk_comb = (int2*)(b->ws + L.off_blk_comb);
   b->cap_comb = std::max<size_t>(L.cap_comb, 1);
+  b->d_nem = (EMArgs*)(b->ws + L.off_nem);
+  b->d_nfem = (EMArgs*)(b->ws + L.off_nfem);
+  b->d_nfem2 = (EMArgs*)(b->ws + L.off_nfem2);
+  b->d_multi = (MultiArgs*)(b->ws + L.off_multi);
+  b->d_blk_near = (int2*)(b->ws + L.off_blk_near);
+  b->d_blk_far = (int2*)(b->ws + L.off_blk_far);
+  b->cap_far = std::max<size_t>(L.cap_far, 1);
   rc = batch_tables(b);
   if (rc) {
     fprintf(stderr, "dmr_batch_create: %s\n", b->err.c_str());

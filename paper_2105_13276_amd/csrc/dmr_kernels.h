@@ -216,6 +216,13 @@ hipError_t launch_line_flags(const float* n, int pitch, int I0, int J0, int I1, 
 int stream_segments(int NY, int seg);
 // M.t base-level steps in one launch, blocks of 64 columns x 4 waves rows
 hipError_t launch_em_multi(MultiArgs& M, int waves, hipStream_t st);
+// its blocks along x and y for M->t steps (false: no such launch)
+bool multi_grid(MultiArgs* M, int waves);
+// batched: steps k .. k + t - 1 of the interval; last: Hz of the half level
+// before is stored (at most 12 waves)
+hipError_t launch_em_multi_batch(const MultiArgs* args, const int2* blk, int nblk,
+                                 const float2* src, int k, int t, int last, int waves,
+                                 hipStream_t st);
 // batched forms: blk[b] = (instance, block index within the instance)
 hipError_t launch_em_stream_batch(const EMArgs* args, const int2* blk, int nblk,
                                   const float2* src, int k, int depth, hipStream_t st);

@@ -37,10 +37,11 @@ __device__ __forceinline__ float lane_left(float v) {
 // boundary nodes.  XE: the region holds column 0 or NX or a source column;
 // YE: the wave holds row 0 or NY.
 template <int R, bool XE, bool YE>
-__device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, int own_x,
-                                           int own_lo, int own_hi, float (*sE)[3][64]) {
+__device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const float2* in, float* hzp,
+                                           int x0, int y0, int own_x, int own_lo, int own_hi,
+                                           float (*sE)[3][64]) {
   const EMArgs& A = M.em;
-  const int NX = A.R, NY = A.T, t = M.t;
+  const int NX = A.R, NY = A.T;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int nw = (int)(blockDim.x >> 6);
@@ -116,12 +117,12 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
     const int b = (s & 1) * nw;
     publish(s & 1);
     __syncthreads();
-    if (s == t - 1 && M.hzp) {  // Hz entering the last step
+    if (s == t - 1 && hzp) {  // Hz entering the last step
 #pragma unroll
       for (int r = 0; r < R; r++) {
         const int j = jt + r;
         if (j >= own_lo && j < own_hi && j < NY && i >= own_x && lane < 64 - t && i < NX && mine(j))
-          M.hzp[(size_t)j * A.pitch + i] = hz[r];
+          hzp[(size_t)j * A.pitch + i] = hz[r];
       }
     }
     const float exu = sE[b + (w + 1 < nw ? w + 1 : w)][0][lane];  // Ex of row jt + R
@@ -141,8 +142,8 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
     // source terms; -0 (which changes no value) off the source columns
     float add_e = -0.f;
     if (XE && src) {
-      const float add_h = i == A.is - 1 ? S * M.src[s].x : -0.f;
-      add_e = i == A.is ? S * M.src[s].y : -0.f;
+      const float add_h = i == A.is - 1 ? S * in[s].x : -0.f;
+      add_e = i == A.is ? S * in[s].y : -0.f;
       hm += add_h;
 #pragma unroll
       for (int r = 0; r < R; r++) hz[r] += add_h;
@@ -216,14 +217,13 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int x0, int y0, i
   }
 }
 
-// R rows a wave, at most NW waves a block, EU waves per SIMD
-template <int R, int NW, int EU>
-__global__ __launch_bounds__(64 * NW, EU) void k_em_multi(MultiArgs M) {
-  __shared__ float sE[2 * NW][3][64];
+// Block (bx, by) of the t-step launch; in: the incident values of the steps,
+// hzp: where Hz entering the last one goes (nullable)
+template <int R>
+__device__ __forceinline__ void multi_block(const MultiArgs& M, int t, const float2* in, float* hzp,
+                                            int bx, int by, float (*sE)[3][64]) {
   const EMArgs& A = M.em;
-  const int b = xcd_band(blockIdx.x, M.ntx * M.nty);
-  const int bx = b % M.ntx, by = b / M.ntx;
-  const int t = M.t, rows = (int)(blockDim.x >> 6) * R;
+  const int rows = (int)(blockDim.x >> 6) * R;
   const int NX = A.R, NY = A.T;
   const int own_x = bx * (64 - 2 * t);
   const int own_lo = by * (rows - 2 * t);
@@ -245,19 +245,57 @@ __global__ __launch_bounds__(64 * NW, EU) void k_em_multi(MultiArgs M) {
   // (chosen per wave; every form passes the same barriers)
   const int jt = y0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * R;
   const bool ye = jt < 1 || jt + R > NY;
-  if (xe && ye) multi_tile<R, true, true>(M, x0, y0, own_x, own_lo, own_hi, sE);
-  else if (xe) multi_tile<R, true, false>(M, x0, y0, own_x, own_lo, own_hi, sE);
-  else if (ye) multi_tile<R, false, true>(M, x0, y0, own_x, own_lo, own_hi, sE);
-  else multi_tile<R, false, false>(M, x0, y0, own_x, own_lo, own_hi, sE);
+  if (xe && ye) multi_tile<R, true, true>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
+  else if (xe) multi_tile<R, true, false>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
+  else if (ye) multi_tile<R, false, true>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
+  else multi_tile<R, false, false>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
+}
+
+// R rows a wave, at most NW waves a block, EU waves per SIMD
+template <int R, int NW, int EU>
+__global__ __launch_bounds__(64 * NW, EU) void k_em_multi(MultiArgs M) {
+  __shared__ float sE[2 * NW][3][64];
+  const int b = xcd_band(blockIdx.x, M.ntx * M.nty);
+  multi_block<R>(M, M.t, M.src, M.hzp, b % M.ntx, b / M.ntx, sE);
+}
+
+// over the blocks of many instances, blk[b] = (instance, block within it);
+// step k of the interval is the first, its incident values src[instance *
+// kSrcSteps + k]
+template <int R, int NW, int EU>
+__global__ __launch_bounds__(64 * NW, EU) void k_em_multi_batch(const MultiArgs* __restrict__ args,
+                                                                const int2* __restrict__ blk,
+                                                                const float2* __restrict__ src,
+                                                                int k, int t, int last) {
+  __shared__ float sE[2 * NW][3][64];
+  const int2 bi = blk[blockIdx.x];
+  const MultiArgs& M = args[bi.x];
+  multi_block<R>(M, t, src + (size_t)bi.x * kSrcSteps + k, last ? M.hzp : nullptr, bi.y % M.ntx,
+                 bi.y / M.ntx, sE);
 }
 
 }  // namespace
 
+bool multi_grid(MultiArgs* M, int waves) {
+  const int t = M->t, h = 4 * waves - 2 * t;
+  if (t < 1 || t > kMultiSteps || waves < 1 || waves > 16 || h < 2) return false;
+  M->ntx = (M->em.R + 1 + 63 - 2 * t) / (64 - 2 * t);
+  M->nty = (M->em.T + 1 + h - 1) / h;
+  return true;
+}
+
+hipError_t launch_em_multi_batch(const MultiArgs* args, const int2* blk, int nblk,
+                                 const float2* src, int k, int t, int last, int waves,
+                                 hipStream_t st) {
+  if (nblk <= 0) return hipSuccess;
+  if (waves > 12) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_em_multi_batch<4, 12, 6>), dim3(nblk), dim3(64 * waves), 0, st, args, blk,
+                     src, k, t, last);
+  return hipGetLastError();
+}
+
 hipError_t launch_em_multi(MultiArgs& M, int waves, hipStream_t st) {
-  const int t = M.t, h = 4 * waves - 2 * t;
-  if (t < 1 || t > kMultiSteps || waves < 1 || waves > 16 || h < 2) return hipErrorInvalidValue;
-  M.ntx = (M.em.R + 1 + 63 - 2 * t) / (64 - 2 * t);
-  M.nty = (M.em.T + 1 + h - 1) / h;
+  if (!multi_grid(&M, waves)) return hipErrorInvalidValue;
   const dim3 g(M.ntx * M.nty), bl(64 * waves);
   if (waves <= 8) hipLaunchKernelGGL((k_em_multi<4, 8, 5>), g, bl, 0, st, M);
   else if (waves <= 12) hipLaunchKernelGGL((k_em_multi<4, 12, 6>), g, bl, 0, st, M);

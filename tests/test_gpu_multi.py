@@ -114,3 +114,38 @@ def test_steps_split_around_the_fine_level(kind, monkeypatch):
         for x, y in zip(runs[0], other):
             for f in x:
                 assert np.array_equal(x[f], y[f]), f
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["rect", "r4", "union"])
+def test_batch_steps_split_around_the_fine_levels(kind, monkeypatch):
+    """A batch whose steps are split (tuned configuration, a captured interval,
+    stretches that leave an odd number of groups) against plain runs of one
+    launch per step: the same bits and saved states."""
+    lam = W.C0 / 110e9
+    cfgs, seeds = [], []
+    for nx, ny in ((384, 224), (320, 256), (256, 288)):
+        if kind == "r4":
+            cfg = W.make(nx, ny, 32, "dynamic", 1, r=4, block=16, erms_over_ebd=2.0)
+        else:
+            cfg = W.make(nx, ny, 32, "dynamic", 1, erms_over_ebd=2.0,
+                         regrid_rule="union" if kind == "union" else "blocks")
+        dx = lam / 32
+        cfgs.append(cfg)
+        seeds.append(W.seeds(cfg, [(0.5 * nx * dx, 0.45 * ny * dx)], [1e17]))
+    b = B.Batch(cfgs, seeds)
+    monkeypatch.setenv("DMR_MULTI", "1")
+    plain = [B.Sim(c, *s) for c, s in zip(cfgs, seeds)]
+    monkeypatch.delenv("DMR_MULTI")
+    for n in (256, 264, 504, 3):
+        b.step(n)
+        for h, s in zip(b.instances, plain):
+            s.step(n)
+            assert h.patch() == s.patch()
+            for lv in (0, 1):
+                for f in FIELDS:
+                    assert np.array_equal(h.get(f, lv), s.get(f, lv)), (n, f, lv)
+            a, c = (x.save(np.zeros(x.state_bytes(), np.uint8)) for x in (h, s))
+            assert np.array_equal(a[256:].view(np.float32), c[256:].view(np.float32))
+    b.sync()
+    b.close()
