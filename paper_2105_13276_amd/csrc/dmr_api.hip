@@ -136,7 +136,8 @@ Layout layout_of(const dmr_params* p) {
     L.off_act = off;   off += 2 * align256(nb);
     L.off_tiles = off; off += 2 * align256(L.max_tiles * sizeof(int2));
     L.off_cfb = off;   off += align256(L.max_tiles * kCfbStride * sizeof(float));
-    L.max_nblk = (size_t)stream_blocks_x(p->nx) * stream_segments(p->ny, kNearSeg);
+    L.max_nblk = (size_t)((p->nx + 1 + 61) / 62) *
+                 ((stream_segments(p->ny, kNearSeg) + kThreads / 64 - 1) / (kThreads / 64));
     L.off_near = off;  off += align256(nb);
     L.off_nblk = off;  off += align256(L.max_nblk * sizeof(int2));
   }
@@ -277,6 +278,12 @@ struct dmr_sim {
   int stream_force = -1;
   int fseg = 0, fdepth = 0;  // its rows per segment and load depth (0: by size)
   int nt1 = 1024;  // threads per patch tile
+  // both r = 2 substeps in the register tiles from reg_min fine cells on.  On
+  // 2048x1024 with a square patch, us per coarse step, the LDS tiles (in the
+  // base step's launch, or two launches from 2^20 on) against these: 65 K
+  // cells 20.1 / 22.6, 147 K 25.6 / 23.3, 590 K 54.9 / 27.4, 1 M 83.9 / 41.1
+  long reg_min = 1L << 17;
+  int reg_waves = 0;  // DMR_FINE_REG=cells[,waves] (waves 0: by size)
   // continuity of both levels in one launch (small rectangular r = 2 patch);
   // DMR_CONT_MERGE=0/1 forces either form
   int cont_merge = -1;
@@ -1165,7 +1172,9 @@ int em_part(dmr_sim* s, StepCtx* cx, const NearWin* win) {
   // (1, 2); (3, 4) and the fine -> coarse transfer follow in a launch of
   // their own, so the base waves store every coarse entity
   const bool r4 = p.r == 4;
-  const bool combined = fuse && (s->combine || (win && s->near_combine)) && (!r4 || (s->ty1 == 4 && !kst));
+  const bool reg = s->has_patch && s->fuse_fine && !s->uni && p.r == 2 && !st &&
+                   fine_cells >= s->reg_min;
+  const bool combined = fuse && !reg && (s->combine || (win && s->near_combine)) && (!r4 || (s->ty1 == 4 && !kst));
   // what patch tiles need to form the coarse E after the base step on their
   // boundary lines themselves: the coarse state entering the step
   auto coarse_state = [&](EMArgs* G) {
@@ -1215,6 +1224,21 @@ int em_part(dmr_sim* s, StepCtx* cx, const NearWin* win) {
   }
   if (combined && !r4) {
     // done above
+  } else if (reg) {  // both substeps, register tiles
+    Level& F = s->L1;
+    EMArgs G;
+    make_fine_em(s, 2, c, s->ncur, s->ty1, &G);  // restriction targets
+    em_args_level(&G, F, 0, 1, F.n[s->ncur], F.acc);
+    G.frac = 0.5f;  // time fraction of substep 1
+    ev_begin(s, 1);
+    e = launch_fine_reg(G, s->reg_waves, s->st);
+    ev_end(s);
+    if (e != hipSuccess) return hipfail(s, e, "fine EM launch");
+    std::swap(F.hz[0], F.hz[1]);
+    std::swap(F.ex[0], F.ex[1]);
+    std::swap(F.ey[0], F.ey[1]);
+    std::swap(F.jx[0], F.jx[1]);
+    std::swap(F.jy[0], F.jy[1]);
   } else if (fuse && p.r == 4) {  // substeps (1, 2) then (3, 4), one launch each
     Level& F = s->L1;
     for (int h = combined ? 1 : 0; h < 2; h++) {
@@ -1298,17 +1322,17 @@ void near_rect(const dmr_sim* s, int t, int r[4]) {
 
 // the streaming waves that cover that region and the t cells around it from
 // which its values follow
-StreamWin near_window(const dmr_sim* s, int t) {
+StreamWin near_window(const dmr_sim* s, int t, int seg = kNearSeg) {
   int r[4];
   near_rect(s, t, r);
   const int x0 = std::max(r[0] - t, 0), y0 = std::max(r[1] - t, 0);
   const int x1 = std::min(r[2] + t, s->p.nx + 1), y1 = std::min(r[3] + t, s->p.ny + 1);
-  const int nseg = stream_segments(s->p.ny, kNearSeg);
+  const int nseg = stream_segments(s->p.ny, seg);
   StreamWin w;
   w.cw0 = x0 / 62;
   w.ncw = (x1 - 1) / 62 + 1 - w.cw0;
-  w.k0 = std::min(y0 / kNearSeg, nseg - 1);
-  w.nk = std::min((y1 - 1) / kNearSeg + 1, nseg) - w.k0;
+  w.k0 = std::min(y0 / seg, nseg - 1);
+  w.nk = std::min((y1 - 1) / seg + 1, nseg) - w.k0;
   return w;
 }
 
@@ -1331,22 +1355,22 @@ int near_blocks(dmr_sim* s) {
   dilate(s->h_act, &s->h_near);
   std::vector<uint8_t> cover;
   dilate(s->h_near, &cover);
-  const int nbx = stream_blocks_x(p.nx), nseg = stream_segments(p.ny, kNearSeg);
-  const int cols = 62 * (kThreads / 64);
+  const int nbx = (p.nx + 1 + 61) / 62, nseg = stream_segments(p.ny, kNearSeg);
+  const int rows = kNearSeg * (kThreads / 64), nrow = (nseg + kThreads / 64 - 1) / (kThreads / 64);
   s->h_nblk.clear();
-  for (int k = 0; k < nseg; k++) {
-    const int j1 = k == nseg - 1 ? p.ny : (k + 1) * kNearSeg - 1;
-    const int yb0 = std::min(k * kNearSeg / Bk, NBy - 1), yb1 = std::min(j1 / Bk, NBy - 1);
+  for (int k = 0; k < nrow; k++) {
+    const int j1 = k == nrow - 1 ? p.ny : (k + 1) * rows - 1;
+    const int yb0 = std::min(k * rows / Bk, NBy - 1), yb1 = std::min(j1 / Bk, NBy - 1);
     for (int b = 0; b < nbx; b++) {
-      const int xb0 = std::min(b * cols / Bk, NBx - 1);
-      const int xb1 = std::min((b * cols + cols - 1) / Bk, NBx - 1);
+      const int xb0 = std::min(b * 62 / Bk, NBx - 1);
+      const int xb1 = std::min((b * 62 + 61) / Bk, NBx - 1);
       bool hit = false;
       for (int y = yb0; y <= yb1 && !hit; y++)
         for (int x = xb0; x <= xb1 && !hit; x++) hit = cover[(size_t)y * NBx + x] != 0;
       if (hit) s->h_nblk.push_back(make_int2(b, k));
     }
   }
-  s->near_share = (double)s->h_nblk.size() / ((double)nbx * nseg);
+  s->near_share = (double)s->h_nblk.size() / ((double)nbx * nrow);
   HIPCHK(s, hipMemcpyAsync(s->d_near, s->h_near.data(), s->h_near.size(), hipMemcpyHostToDevice,
                            s->st));
   if (!s->h_nblk.empty())
@@ -1618,6 +1642,8 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   }
   if (const char* f = getenv("DMR_SPLIT_MIN")) s->split_min = atol(f);
   if (const char* f = getenv("DMR_CONT_MERGE")) s->cont_merge = atoi(f) != 0 ? 1 : 0;
+  if (const char* f = getenv("DMR_FINE_REG"))
+    (void)sscanf(f, "%ld,%d", &s->reg_min, &s->reg_waves);
   if (const char* f = getenv("DMR_FINE_SEG")) s->fseg = atoi(f) >= 2 ? atoi(f) : 0;
   if (const char* f = getenv("DMR_FINE_DEPTH")) s->fdepth = atoi(f) >= 4 ? 4 : 2;
   s->depth0 = stream_depth(s->seg0);
@@ -2793,7 +2819,11 @@ struct dmr_batch {
   EMArgs* d_nfem2 = nullptr;  // [2][2][3][2][count] patch, two substeps a launch
   MultiArgs* d_multi = nullptr;  // [2][2][count]
   int2 *d_blk_near = nullptr, *d_blk_far = nullptr;
-  int nblk_near = 0, nblk_far = 0;
+  int nblk_near = 0, nblk_far = 0, near_seg = kNearSeg;
+  // register patch tiles of the groups (fused, r = 2, 16 tile rows)
+  int2* d_blk_reg = nullptr;
+  int nblk_reg = 0, reg_waves = 16;
+  std::vector<int2> h_blk_reg;
   size_t cap_far = 0;
   std::vector<EMArgs> h_nem, h_nfem, h_nfem2;
   std::vector<MultiArgs> h_multi;
@@ -2820,7 +2850,7 @@ struct BatchLayout {
          off_blk_fine = 0, off_blk_cont = 0, off_blk_fcont = 0, off_src = 0, total = 0;
   size_t off_fem2 = 0, off_cem = 0, off_floc = 0, off_blk_comb = 0;
   size_t off_nem = 0, off_nfem = 0, off_nfem2 = 0, off_multi = 0, off_blk_near = 0,
-         off_blk_far = 0, cap_far = 0;
+         off_blk_far = 0, off_blk_reg = 0, cap_far = 0;
   size_t cap_base = 0, cap_fine = 0, cap_cont = 0, cap_fcont = 0, cap_comb = 0;
 };
 
@@ -2890,6 +2920,7 @@ int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* wh
   L->off_multi = off;     off += align256(sizeof(MultiArgs) * 2 * 2 * count);
   L->off_blk_near = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_base, 1));
   L->off_blk_far = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_far, 1));
+  L->off_blk_reg = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_fine, 1));
   L->cap_comb = L->cap_base + L->cap_fine;
   L->off_blk_comb = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_comb, 1));
   L->total = off;
@@ -2927,9 +2958,26 @@ int batch_group(const dmr_batch* b) {
       continue;
     }
     const StreamWin w = near_window(s, t);
-    near += std::min(cells, (w.ncw + 3) / 4 * 248.0 * w.nk * kNearSeg);
+    near += std::min(cells, w.ncw * 62.0 * w.nk * kNearSeg);
   }
   return near <= 0.5 * all ? t : 0;
+}
+
+// Rows per segment of the near launches of rectangles: the longest that leave
+// the chip two waves per SIMD (a segment reads one row more than it steps; 64
+// instances with 64x64-cell patches: 26 us a launch with 2 rows)
+int batch_near_seg(const dmr_batch* b) {
+  if (!b->tg) return kNearSeg;
+  for (int seg = 8; seg > kNearSeg; seg >>= 1) {
+    long waves = 0;
+    for (const dmr_sim* s : b->sims) {
+      if (!s->has_patch || s->uni) continue;
+      const StreamWin w = near_window(s, b->tg, seg);
+      waves += (long)w.ncw * w.nk;
+    }
+    if (waves >= 2048) return seg;
+  }
+  return kNearSeg;
 }
 
 // exchange an instance's base-level state planes with its third set (what a
@@ -3014,8 +3062,15 @@ void batch_args(dmr_batch* b, int k, int g) {
       EMArgs& A = b->h_nem[(gv * 3 + ph) * n + k];
       make_base_em(s, 0, nc, &A);
       A.acc1 = s->far[5];
-      A.seg = kNearSeg;
-      A.nseg = stream_segments(s->p.ny, kNearSeg);
+      const int seg = s->uni ? kNearSeg : b->near_seg;
+      A.seg = seg;
+      A.nseg = stream_segments(s->p.ny, seg);
+      A.nbx = (s->p.nx + 1 + 61) / 62;
+      A.sT = A.nseg;
+      if (s->has_patch && !s->uni) {
+        const StreamWin w = near_window(s, b->tg, seg);
+        A.nbx = w.ncw; A.sL = w.cw0; A.sB = w.k0; A.sT = w.k0 + w.nk;
+      }
       if (s->has_patch) {
         for (int m = 1; m <= b->rf; m++)
           make_fine_em(s, m, 0, nc, b->ty, &b->h_nfem[((gv * 3 + ph) * b->rf + m - 1) * n + k]);
@@ -3075,6 +3130,9 @@ int batch_tables(dmr_batch* b) {
   if ((b->sched == kSchedFused && !b->can_fuse) || (b->sched == kSchedCombined && !b->can_combine))
     b->sched = kSchedSeparate;
   b->tg = batch_group(b);
+  std::vector<int> pw, ph, pk;  // patches: cells, instance
+  b->h_blk_reg.clear();
+  b->near_seg = batch_near_seg(b);
   for (int k = 0; k < n; k++) {
     dmr_sim* s = b->sims[k];
     s->seg0 = b->seg;
@@ -3116,11 +3174,18 @@ int batch_tables(dmr_batch* b) {
     if (s->has_patch && s->uni) {
       for (const int2& q : s->h_nblk) b->h_blk_near.push_back(make_int2(k, q.y * N.nbx + q.x));
     } else if (s->has_patch) {
-      const StreamWin w = near_window(s, b->tg);
-      for (int q = w.k0; q < w.k0 + w.nk; q++)
-        for (int x = w.cw0 / 4; x <= (w.cw0 + w.ncw - 1) / 4; x++)
-          b->h_blk_near.push_back(make_int2(k, q * N.nbx + x));
+      const int nrow = (N.sT - N.sB + kThreads / 64 - 1) / (kThreads / 64);
+      for (int q = 0; q < nrow * N.nbx; q++) b->h_blk_near.push_back(make_int2(k, q));
+      const int w = s->p.r * (s->ext[2] - s->ext[0]), h = s->p.r * (s->ext[3] - s->ext[1]);
+      pw.push_back(w); ph.push_back(h); pk.push_back(k);
     }
+  }
+  // register patch tiles (schedule fused, 16 tile rows, r = 2)
+  if (b->rf == 2 && !pw.empty()) {
+    b->reg_waves = fine_reg_waves(pw.data(), ph.data(), (int)pw.size());
+    for (size_t q = 0; q < pw.size(); q++)
+      for (int t = 0; t < fine_reg_blocks(pw[q], ph[q], b->reg_waves); t++)
+        b->h_blk_reg.push_back(make_int2(pk[q], t));
   }
   // combined table: every instance's groups of 16 base waves, then the
   // patch tiles (the same 64 x ty tiles as h_blk_fine, coded -1 - t)
@@ -3134,7 +3199,7 @@ int batch_tables(dmr_batch* b) {
   if (b->h_blk_base.size() > b->cap_base || b->h_blk_fine.size() > b->cap_fine ||
       b->h_blk_cont.size() > b->cap_cont || b->h_blk_fcont.size() > b->cap_fcont ||
       b->h_blk_comb.size() > b->cap_comb || b->h_blk_near.size() > b->cap_base ||
-      b->h_blk_far.size() > b->cap_far)
+      b->h_blk_far.size() > b->cap_far || b->h_blk_reg.size() > b->cap_fine)
     return bfail(b, DMR_EINVAL, "batch block table exceeds its workspace capacity");
   b->nblk_comb = (int)b->h_blk_comb.size();
   b->nblk_base = (int)b->h_blk_base.size();
@@ -3143,6 +3208,7 @@ int batch_tables(dmr_batch* b) {
   b->nblk_fcont = (int)b->h_blk_fcont.size();
   b->nblk_near = (int)b->h_blk_near.size();
   b->nblk_far = (int)b->h_blk_far.size();
+  b->nblk_reg = (int)b->h_blk_reg.size();
   auto up = [&](void* dst, const auto& v) {
     const size_t bytes = v.size() * sizeof(v[0]);
     return bytes ? hipMemcpyAsync(dst, v.data(), bytes, hipMemcpyHostToDevice, b->st) : hipSuccess;
@@ -3154,7 +3220,7 @@ int batch_tables(dmr_batch* b) {
       up(b->d_floc, b->h_floc) || up(b->d_blk_comb, b->h_blk_comb) ||
       (b->tg && (up(b->d_nem, b->h_nem) || up(b->d_nfem, b->h_nfem) || up(b->d_nfem2, b->h_nfem2) ||
                  up(b->d_multi, b->h_multi) || up(b->d_blk_near, b->h_blk_near) ||
-                 up(b->d_blk_far, b->h_blk_far))) ||
+                 up(b->d_blk_far, b->h_blk_far) || up(b->d_blk_reg, b->h_blk_reg))) ||
       hipStreamSynchronize(b->st))
     return bfail(b, DMR_EHIP, "batch table upload failed");
   b->graph_ok = false;
@@ -3300,10 +3366,11 @@ int batch_launch_group(dmr_batch* b, bool last) {
   hipError_t e = hipSuccess;
   for (int k = 0; k < b->tg; k++) {
     const size_t q = gv * 3 + (k == 0 ? 0 : (k & 1) ? 1 : 2);
-    e = launch_em_stream_batch(b->d_nem + q * n, b->d_blk_near, b->nblk_near, b->d_src, k0 + k, 2,
-                               b->st);
+    e = launch_em_near_batch(b->d_nem + q * n, b->d_blk_near, b->nblk_near, b->d_src, k0 + k, b->st);
     if (e != hipSuccess) return bfail(b, DMR_EHIP, "batched base EM launch");
-    if (b->sched != kSchedSeparate) {
+    if (b->sched != kSchedSeparate && b->ty == 16 && b->rf == 2) {
+      e = launch_fine_reg_batch(b->d_nfem2 + q * 2 * n, b->d_blk_reg, b->nblk_reg, b->reg_waves, b->st);
+    } else if (b->sched != kSchedSeparate) {
       for (int h = 0; h < (b->rf == 4 ? 2 : 1) && b->nblk_fine && e == hipSuccess; h++)
         e = launch_fine2_batch(b->d_nfem2 + (q * 2 + h) * n, b->d_blk_fine, b->nblk_fine, b->ty,
                                b->rf == 4, b->st);
@@ -3427,20 +3494,25 @@ int batch_tune(dmr_batch* b, int64_t* used) {
         b->sched = sched;
         b->ty = kTyCand[c];
         rc = batch_tables(b);
-        // to the next group (the candidates above stop anywhere)
-        while (!rc && !batch_at_group(b, b->tg)) {
-          if (b->sims[0]->step - b->src_base >= kSrcSteps) rc = batch_sources(b, b->sims[0]->step);
-          if (!rc) rc = batch_launch_step(b, nullptr, nullptr);
-          if (!rc) (*used)++;
+        // to the next group (the candidates above stop anywhere); the faster
+        // of two, since a kernel's first launch may wait for its set-up
+        for (int rep = 0; rep < 2 && !rc; rep++) {
+          while (!rc && !batch_at_group(b, b->tg)) {
+            if (b->sims[0]->step - b->src_base >= kSrcSteps) rc = batch_sources(b, b->sims[0]->step);
+            if (!rc) rc = batch_launch_step(b, nullptr, nullptr);
+            if (!rc) (*used)++;
+          }
+          if (!rc && b->sims[0]->step - b->src_base >= kSrcSteps)
+            rc = batch_sources(b, b->sims[0]->step);
+          (void)hipEventRecord(tb[0], b->st);
+          if (!rc) rc = batch_launch_group(b, true);
+          if (!rc) *used += b->tg;
+          (void)hipEventRecord(tf[1], b->st);
+          if (!rc && hipStreamSynchronize(b->st) != hipSuccess) rc = DMR_EHIP;
+          float t = 0.f;
+          (void)hipEventElapsedTime(&t, tb[0], tf[1]);
+          if (!rc && t < best) { best = t; bsched = sched; bty = kTyCand[c]; }
         }
-        (void)hipEventRecord(tb[0], b->st);
-        if (!rc) rc = batch_launch_group(b, true);
-        if (!rc) *used += b->tg;
-        (void)hipEventRecord(tf[1], b->st);
-        if (!rc && hipStreamSynchronize(b->st) != hipSuccess) rc = DMR_EHIP;
-        float t = 0.f;
-        (void)hipEventElapsedTime(&t, tb[0], tf[1]);
-        if (!rc && t < best) { best = t; bsched = sched; bty = kTyCand[c]; }
       }
     }
   } else if (!rc && (b->can_fuse || b->can_combine)) {
@@ -3625,6 +3697,7 @@ int dmr_batch_create(const dmr_params* p, int count, const double* const* seed_b
   b->d_blk_near = (int2*)(b->ws + L.off_blk_near);
   b->d_blk_far = (int2*)(b->ws + L.off_blk_far);
   b->cap_far = std::max<size_t>(L.cap_far, 1);
+  b->d_blk_reg = (int2*)(b->ws + L.off_blk_reg);
   rc = batch_tables(b);
   if (rc) {
     fprintf(stderr, "dmr_batch_create: %s\n", b->err.c_str());

@@ -40,6 +40,52 @@ __device__ __forceinline__ float base_win(float acc, float xl, float xr, float y
   return acc + 0.5f * e2;
 }
 
+// ---------------------------------------------------------------------------
+// Per-entity arithmetic of the patch substep, shared by the one-substep and
+// the two-substep kernels so that all round identically.
+// ---------------------------------------------------------------------------
+// 5-point Laplacian; neighbours outside the patch already replaced by c
+__device__ __forceinline__ float lap5(float c, float l, float r, float d, float u) {
+  return l + r + d + u - 4.f * c;
+}
+// E filter of the patch interior: E - gamma L(L(E))
+__device__ __forceinline__ float filter_e(float e, float gamma, float l2) { return e - gamma * l2; }
+// Faraday, Eq. (2), scaled: H~ - S [(Ey_{i+1}-Ey_i) - (Ex_{j+1}-Ex_j)]
+__device__ __forceinline__ float faraday(float ho, float S, float dey, float dex) {
+  return ho - S * (dey - dex);
+}
+// Ampere + Drude, Eqs. (1), (3): new E from the old E, the curl term and J~
+// (times the hardware reciprocal of 1 + kap, as the base level: two
+// instructions where a correctly rounded division takes eleven)
+__device__ __forceinline__ float ampere(float e, float kap, float curl, float c1, float jo) {
+  return ((1.f - kap) * e + curl - c1 * jo) * __builtin_amdgcn_rcpf(1.f + kap);
+}
+// new J~ = a J~ + 2k (E + E+)
+__device__ __forceinline__ float drude(float a, float jo, float kap, float e, float en) {
+  return a * jo + 2.f * kap * (e + en);
+}
+// Eq. (5b): space weights w0, w1 on two coarse edges, time fraction frac
+__device__ __forceinline__ float cfb(float w0, float w1, float o0, float o1, float n0, float n1,
+                            float frac) {
+  const float vo = w0 * o0 + w1 * o1;
+  const float vn = w0 * n0 + w1 * n1;
+  return (1.f - frac) * vo + frac * vn;
+}
+// window increment of a node from its existing edges (mean per axis)
+__device__ __forceinline__ float win_e2(float sx, int cx, float sy, int cy) {
+  return (cx == 2 ? 0.5f * sx : sx) + (cy == 2 ? 0.5f * sy : sy);
+}
+
+// value of the lane one column to the right / left (0 beyond the wave)
+__device__ __forceinline__ float lane_right(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+      0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));  // wave_shl:1
+}
+__device__ __forceinline__ float lane_left(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+      0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));  // wave_shr:1
+}
+
 // Workgroups are dispatched to the 8 XCDs round-robin by linear id, and each
 // XCD has its own L2.  Hand XCD x a contiguous band of the row-major
 // (column block, segment) grid so that neighbouring blocks, which read the

@@ -195,6 +195,14 @@ hipError_t launch_prolong_union(const ProlongArgs& A, const int2* tiles, int nti
 // writes buffer 1 (hz1..), A.frac = time fraction of substep 1, restriction on
 hipError_t launch_fine2(const EMArgs& A, int ty, int nt, hipStream_t st);
 hipError_t launch_fine2_fast(const EMArgs& A, int tw, hipStream_t st);
+// the same in registers (dmr_fine.hip; r = 2 rectangle); waves per block 16, 12
+// or 8 (0: by size); blocks of a w x h-cell patch, and the waves for several
+hipError_t launch_fine_reg(const EMArgs& A, int waves, hipStream_t st);
+int fine_reg_blocks(int w, int h, int waves);
+int fine_reg_waves(const int* w, const int* h, int count);
+// batched: blk[b] = (instance, block within its patch)
+hipError_t launch_fine_reg_batch(const EMArgs* args, const int2* blk, int nblk, int waves,
+                                 hipStream_t st);
 // base-level step (C, with the patch's coarse entities skipped) and both patch
 // substeps (F, coarse boundary E computed in the tiles) in one launch
 hipError_t launch_dmr_step(const EMArgs& C, const EMArgs& F, int seg, int depth, int ty,
@@ -240,6 +248,12 @@ hipError_t launch_dmr_step_batch(const EMArgs* cargs, const EMArgs* fargs, const
                                  hipStream_t st);
 hipError_t launch_cont_batch(const ContArgs* args, const int2* blk, int nblk, bool fine,
                              int slot, int update, hipStream_t st);
+// the near launches of a batch's split groups: blk[b] = (instance, entry), the
+// block's four waves take four segments of one column wave; of args, the
+// column waves [sL, ..) by segments [sB, sT), entry = row of blocks * nbx +
+// column wave from sL
+hipError_t launch_em_near_batch(const EMArgs* args, const int2* blk, int nblk,
+                                const float2* src, int k, hipStream_t st);
 hipError_t launch_cont(const ContArgs& A, bool fine, hipStream_t st);
 hipError_t launch_cont2(const ContArgs& C, const ContArgs& F, hipStream_t st);
 hipError_t launch_regrid_test(const FlagArgs& F, const ScanArgs& S, hipStream_t st);

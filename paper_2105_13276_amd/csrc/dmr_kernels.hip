@@ -23,42 +23,6 @@
 namespace dmr {
 
 // ---------------------------------------------------------------------------
-// Per-entity arithmetic of the patch substep, shared by the one-substep and
-// the two-substep kernels so that both round identically.
-// ---------------------------------------------------------------------------
-// 5-point Laplacian; neighbours outside the patch already replaced by c
-__device__ inline float lap5(float c, float l, float r, float d, float u) {
-  return l + r + d + u - 4.f * c;
-}
-// E filter of the patch interior: E - gamma L(L(E))
-__device__ inline float filter_e(float e, float gamma, float l2) { return e - gamma * l2; }
-// Faraday, Eq. (2), scaled: H~ - S [(Ey_{i+1}-Ey_i) - (Ex_{j+1}-Ex_j)]
-__device__ inline float faraday(float ho, float S, float dey, float dex) {
-  return ho - S * (dey - dex);
-}
-// Ampere + Drude, Eqs. (1), (3): new E from the old E, the curl term and J~
-// (times the hardware reciprocal of 1 + kap, as the base level: two
-// instructions where a correctly rounded division takes eleven)
-__device__ inline float ampere(float e, float kap, float curl, float c1, float jo) {
-  return ((1.f - kap) * e + curl - c1 * jo) * __builtin_amdgcn_rcpf(1.f + kap);
-}
-// new J~ = a J~ + 2k (E + E+)
-__device__ inline float drude(float a, float jo, float kap, float e, float en) {
-  return a * jo + 2.f * kap * (e + en);
-}
-// Eq. (5b): space weights w0, w1 on two coarse edges, time fraction frac
-__device__ inline float cfb(float w0, float w1, float o0, float o1, float n0, float n1,
-                            float frac) {
-  const float vo = w0 * o0 + w1 * o1;
-  const float vn = w0 * n0 + w1 * n1;
-  return (1.f - frac) * vo + frac * vn;
-}
-// window increment of a node from its existing edges (mean per axis)
-__device__ inline float win_e2(float sx, int cx, float sy, int cy) {
-  return (cx == 2 ? 0.5f * sx : sx) + (cy == 2 ? 0.5f * sy : sy);
-}
-
-// ---------------------------------------------------------------------------
 // EM substep of the fine patch (Eqs. (1)-(3)), one TX x TY tile of nodes per
 // block.  The tile owns Hz(i,j), Ex(i,j), Ey(i,j) and node (i,j) for (i,j)
 // in the tile.  It needs old E over [i0-2, i0+TX] x [j0-2, j0+TY] (after the
@@ -2531,13 +2495,25 @@ __global__ __launch_bounds__(kThreads) void k_em_stream(EMArgs A, int seg, int n
                             seg, nseg, A.ey_src, A.hz_src);
 }
 
-// over a list of (group of four 62-column waves, segment)
+// over a list of (62-column wave, group of four segments)
 template <int DEPTH>
 __global__ __launch_bounds__(kThreads) void k_em_stream_list(EMArgs A, const int2* __restrict__ blk,
                                                              int seg, int nseg) {
   const int2 b = blk[blockIdx.x];
-  em_stream_body<DEPTH>(A, b.x * (kThreads / 64) + (threadIdx.x >> 6), b.y, seg, nseg, A.ey_src,
-                        A.hz_src);
+  const int k = b.y * (kThreads / 64) + (threadIdx.x >> 6);
+  if (k < nseg) em_stream_body<DEPTH>(A, b.x, k, seg, nseg, A.ey_src, A.hz_src);
+}
+
+template <int DEPTH>
+__global__ __launch_bounds__(kThreads) void k_em_near_batch(const EMArgs* __restrict__ args,
+                                                            const int2* __restrict__ blk,
+                                                            const float2* __restrict__ src, int q) {
+  const int2 bi = blk[blockIdx.x];
+  const EMArgs& A = args[bi.x];
+  const float2 sv = src[(size_t)bi.x * kSrcSteps + q];
+  const int k = A.sB + bi.y / A.nbx * (kThreads / 64) + (threadIdx.x >> 6);
+  if (k < A.sT)
+    em_stream_body<DEPTH>(A, A.sL + bi.y % A.nbx, k, A.seg, A.nseg, sv.x, sv.y);
 }
 
 // batched form; the incident values of step k of the current interval come
@@ -3114,6 +3090,13 @@ hipError_t launch_em_stream_batch(const EMArgs* args, const int2* blk, int nblk,
     hipLaunchKernelGGL(k_em_stream_batch<4>, dim3(nblk), dim3(kThreads), 0, st, args, blk, src, k);
   else
     hipLaunchKernelGGL(k_em_stream_batch<2>, dim3(nblk), dim3(kThreads), 0, st, args, blk, src, k);
+  return hipGetLastError();
+}
+
+hipError_t launch_em_near_batch(const EMArgs* args, const int2* blk, int nblk,
+                                const float2* src, int k, hipStream_t st) {
+  if (nblk <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_em_near_batch<2>, dim3(nblk), dim3(kThreads), 0, st, args, blk, src, k);
   return hipGetLastError();
 }
 

@@ -21,16 +21,6 @@ namespace dmr {
 
 namespace {
 
-// value of the lane one column to the right / left (0 beyond the wave)
-__device__ __forceinline__ float lane_right(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-      0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));  // wave_shl:1
-}
-__device__ __forceinline__ float lane_left(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-      0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));  // wave_shr:1
-}
-
 // The region is stepped by the interior update everywhere, also where it
 // reaches beyond the grid: E that does not exist (or is zero, PEC) takes the
 // factor 0 for 1 / (1 + kap), which also drops it from the window of the

@@ -149,3 +149,44 @@ def test_batch_steps_split_around_the_fine_levels(kind, monkeypatch):
             assert np.array_equal(a[256:].view(np.float32), c[256:].view(np.float32))
     b.sync()
     b.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("w,h,x,y,waves,gamma", [
+    (1, 1, 40, 30, 8, 1e-3),       # smaller than a halo
+    (3, 25, 41, 31, 16, 1e-3),     # 50 own columns or rows: one more node than whole blocks
+    (25, 2, 33, 20, 12, 1e-3),
+    (24, 8, 60, 41, 12, 0.0),      # whole blocks less one node; no filter
+    (60, 57, 30, 20, 0, 1.0 / 64),
+    (101, 33, 30, 20, 8, 1e-3),
+])
+def test_register_patch_tiles(w, h, x, y, waves, gamma, monkeypatch):
+    """Both r = 2 substeps in the register tiles against one launch a substep,
+    over patches of sizes around the tiles' own 50 columns and 18 to 50 rows:
+    the same bits on both levels."""
+    cfg = W.make(160, 96, 32, "static", 1, static_ext=(x, y, x + w, y + h), fine_filter=gamma,
+                 erms_over_ebd=3.0)
+    g = np.random.Generator(np.random.PCG64(w * 100 + h))
+    base = 10.0 ** g.uniform(17, 20, (97, 161))
+    E = 4e6
+    runs = []
+    for env in ({"DMR_FINE_REG": "0,%d" % waves}, {"DMR_FUSE": "0", "DMR_MULTI": "1"}):
+        for k in ("DMR_FINE_REG", "DMR_FUSE", "DMR_MULTI"):
+            monkeypatch.delenv(k, raising=False)
+        for k, v in env.items():
+            monkeypatch.setenv(k, v)
+        s = B.Sim(cfg, base, None)
+        q = np.random.Generator(np.random.PCG64(7))
+        for lv in (0, 1):
+            for f in ("hz", "ex", "ey"):
+                a = E * q.uniform(-1, 1, s.dims(f, lv))
+                s.set(f, lv, a / 377 if f == "hz" else a)
+        got = []
+        for n in (1, 3, 70):
+            s.step(n)
+            got.append({(f, lv): s.get(f, lv) for lv in (0, 1) for f in FIELDS})
+        s.sync()
+        runs.append(got)
+    for a, b in zip(*runs):
+        for f in a:
+            assert np.array_equal(a[f], b[f]), (f, int((a[f] != b[f]).sum()))
