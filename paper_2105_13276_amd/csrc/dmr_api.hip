@@ -3152,7 +3152,7 @@ int batch_tables(dmr_batch* b) {
     const EMArgs& A = b->h_em[k];
     for (int t = 0; t < A.nbx * A.nseg; t++) b->h_blk_base.push_back(make_int2(k, t));
     const ContArgs& K = b->h_cont[k];
-    const int cny = (K.T - K.B + 1 + 3) / 4;
+    const int cny = (K.T - K.B + 1 + 15) / 16;
     for (int t = 0; t < K.nbx * cny; t++) b->h_blk_cont.push_back(make_int2(k, t));
     if (s->has_patch && s->uni) {  // the instance's tile list
       for (int t = 0; t < s->ntiles; t++) {

@@ -1676,18 +1676,12 @@ __device__ inline float d_eff(const ContArgs &A, float n) {
   return (al * A.Da + A.De) / (1.f + al);
 }
 
-// the new density of one updated node from its old value, the neighbours
-// that exist (zero-flux faces elsewhere) and E_rms^2
-__device__ __forceinline__ float cont_update(const ContArgs& A, size_t o, float e2, bool l,
-                                             bool r, bool d, bool u) {
-  const int pitch = A.pitch;
-  const float ni = A.n0[o];
-  const float di = d_eff(A, ni);
-  float flux = 0.f;
-  if (l) { const float v = A.n0[o - 1]; flux += 0.5f * (di + d_eff(A, v)) * (v - ni); }
-  if (r) { const float v = A.n0[o + 1]; flux += 0.5f * (di + d_eff(A, v)) * (v - ni); }
-  if (d) { const float v = A.n0[o - pitch]; flux += 0.5f * (di + d_eff(A, v)) * (v - ni); }
-  if (u) { const float v = A.n0[o + pitch]; flux += 0.5f * (di + d_eff(A, v)) * (v - ni); }
+// flux of a node (density ni, diffusion di) through the face to a neighbour
+__device__ __forceinline__ float face_flux(float ni, float di, float v, float dv) {
+  return 0.5f * (di + dv) * (v - ni);
+}
+// the new density of a node from its old value, the flux sum and E_rms^2
+__device__ __forceinline__ float cont_source(const ContArgs& A, float ni, float flux, float e2) {
   float nn;
   if (!A.town && A.rei == 0.f) {
     const float nu = A.nuA * (powf(e2 * A.eeff_p2, A.half_beta) - A.att);
@@ -1703,6 +1697,90 @@ __device__ __forceinline__ float cont_update(const ContArgs& A, size_t o, float 
     nn = ni + A.dtn * (flux * A.inv_dx2 + (nu - A.rei * ni) * ni);
   }
   return nn > 0.f ? nn : 0.f;
+}
+
+// the new density of one updated node from its old value, the neighbours
+// that exist (zero-flux faces elsewhere) and E_rms^2
+__device__ __forceinline__ float cont_update(const ContArgs& A, size_t o, float e2, bool l,
+                                             bool r, bool d, bool u) {
+  const int pitch = A.pitch;
+  const float ni = A.n0[o];
+  const float di = d_eff(A, ni);
+  float flux = 0.f;
+  if (l) { const float v = A.n0[o - 1]; flux += face_flux(ni, di, v, d_eff(A, v)); }
+  if (r) { const float v = A.n0[o + 1]; flux += face_flux(ni, di, v, d_eff(A, v)); }
+  if (d) { const float v = A.n0[o - pitch]; flux += face_flux(ni, di, v, d_eff(A, v)); }
+  if (u) { const float v = A.n0[o + pitch]; flux += face_flux(ni, di, v, d_eff(A, v)); }
+  return cont_source(A, ni, flux, e2);
+}
+
+// Base level, RPT rows a thread (64 columns x 4 RPT rows per block of 256
+// threads): every load of a thread comes before its stores, and the diffusion
+// of a row serves the rows beside it.
+constexpr int kContRows = 4;
+__device__ __forceinline__ void cont_rows(const ContArgs& A, int bx, int by, int slot, int update) {
+  constexpr int R = kContRows;
+  const int i = A.L + bx * kTX + (int)(threadIdx.x % kTX);
+  const int j0 = A.B + (by * (kThreads / kTX) + (int)(threadIdx.x / kTX)) * R;
+  if (i > A.R || j0 > A.T) return;
+  const int pitch = A.pitch;
+  const size_t o0 = (size_t)j0 * pitch + i;
+  float sv[R];
+  size_t o[R];
+#pragma unroll
+  for (int q = 0; q < R; q++) {
+    o[q] = o0 + (size_t)min(q, A.T - j0) * pitch;  // (rows past the grid read the last one)
+    sv[q] = A.acc[o[q]];
+  }
+  float e2[R], n[R + 2], nl[R], nr[R];
+  if (update) {
+    float g[kRing][R];
+#pragma unroll
+    for (int s = 0; s < kRing; s++)
+#pragma unroll
+      for (int q = 0; q < R; q++) g[s][q] = A.ring[(size_t)s * A.plane + o[q]];
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+      n[q + 1] = A.n0[o[q]];
+      nl[q] = A.n0[o[q] - (i > A.L ? 1 : 0)];
+      nr[q] = A.n0[o[q] + (i < A.R ? 1 : 0)];
+    }
+    n[0] = A.n0[o0 - (j0 > A.B ? pitch : 0)];
+    n[R + 1] = A.n0[o[R - 1] + (j0 + R - 1 < A.T ? pitch : 0)];
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+      const float x = sv[q] * A.inv_spp;
+      e2[q] = 0.f;
+#pragma unroll
+      for (int s = 0; s < kRing; s++) e2[q] += (s == slot) ? x : g[s][q];
+    }
+  }
+  float D[R + 2];
+  if (update) {
+#pragma unroll
+    for (int q = 0; q < R + 2; q++) D[q] = d_eff(A, n[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < R; q++) {
+    const int j = j0 + q;
+    if (j > A.T) return;
+    const float x = sv[q] * A.inv_spp;
+    A.ring[(size_t)slot * A.plane + o[q]] = x;
+    A.acc[o[q]] = 0.f;
+    if (!update) {
+      if (!isfinite(x)) A.err[threadIdx.x & 63] = 1;
+      continue;
+    }
+    const float ni = n[q + 1], di = D[q + 1];
+    float flux = 0.f;
+    if (i > A.L) flux += face_flux(ni, di, nl[q], d_eff(A, nl[q]));
+    if (i < A.R) flux += face_flux(ni, di, nr[q], d_eff(A, nr[q]));
+    if (j > A.B) flux += face_flux(ni, di, n[q], D[q]);
+    if (j < A.T) flux += face_flux(ni, di, n[q + 2], D[q + 2]);
+    const float nn = cont_source(A, ni, flux, e2[q]);
+    A.n1[o[q]] = nn;
+    if (!isfinite(nn) || !isfinite(e2[q])) A.err[threadIdx.x & 63] = 1;
+  }
 }
 
 // MERGED (both levels in one launch, k_cont2): the coarse level leaves the
@@ -1888,13 +1966,18 @@ __global__ __launch_bounds__(kThreads) void k_cont(ContArgs A) {
   cont_body<FINE>(A, blockIdx.x, blockIdx.y, A.slot, A.update);
 }
 
+__global__ __launch_bounds__(kThreads) void k_cont_rows(ContArgs A) {
+  cont_rows(A, blockIdx.x, blockIdx.y, A.slot, A.update);
+}
+
 template <bool FINE>
 __global__ __launch_bounds__(kThreads) void k_cont_batch(const ContArgs* __restrict__ args,
                                                          const int2* __restrict__ blk,
                                                          int slot, int update) {
   const int2 bi = blk[blockIdx.x];
   const ContArgs& A = args[bi.x];
-  cont_body<FINE>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
+  if constexpr (FINE) cont_body<true>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
+  else cont_rows(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
 }
 
 // cell (i, j) of a fine level made of the active blocks of act
@@ -3189,7 +3272,12 @@ hipError_t launch_line_flags(const float* n, int pitch, int I0, int J0, int I1, 
 hipError_t launch_cont(const ContArgs& A, bool fine, hipStream_t st) {
   const int nx = A.R - A.L + 1, ny = A.T - A.B + 1;
   dim3 g((nx + kTX - 1) / kTX, (ny + kThreads / kTX - 1) / (kThreads / kTX));
-  if (fine) hipLaunchKernelGGL(k_cont<true>, g, dim3(kThreads), 0, st, A);
+  // four rows a thread on large grids (4096x2048: 67 -> 58 us), one on small
+  // ones, where the waves are too few for it (256x128: 5 -> 9 us)
+  if (!fine && (long)nx * ny >= (1L << 22)) {
+    g.y = (ny + kThreads / kTX * kContRows - 1) / (kThreads / kTX * kContRows);
+    hipLaunchKernelGGL(k_cont_rows, g, dim3(kThreads), 0, st, A);
+  } else if (fine) hipLaunchKernelGGL(k_cont<true>, g, dim3(kThreads), 0, st, A);
   else hipLaunchKernelGGL(k_cont<false>, g, dim3(kThreads), 0, st, A);
   return hipGetLastError();
 }
