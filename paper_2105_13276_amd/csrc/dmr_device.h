@@ -40,6 +40,14 @@ __device__ __forceinline__ float base_win(float acc, float xl, float xr, float y
   return acc + 0.5f * e2;
 }
 
+// the same for a node of row 0, which has one y-edge (above, yu)
+__device__ __forceinline__ float base_win0(float acc, float xl, float xr, float yu, float fx) {
+  float sx = xl * xl;
+  sx += xr * xr;
+  const float mx = 0.5f * fx * sx;
+  return acc + __builtin_fmaf(yu, yu, mx);
+}
+
 // ---------------------------------------------------------------------------
 // Per-entity arithmetic of the patch substep, shared by the one-substep and
 // the two-substep kernels so that all round identically.

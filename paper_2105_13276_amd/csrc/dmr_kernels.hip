@@ -1676,9 +1676,10 @@ __device__ inline float d_eff(const ContArgs &A, float n) {
   return (al * A.Da + A.De) / (1.f + al);
 }
 
-// flux of a node (density ni, diffusion di) through the face to a neighbour
-__device__ __forceinline__ float face_flux(float ni, float di, float v, float dv) {
-  return 0.5f * (di + dv) * (v - ni);
+// a node's flux sum (density ni, diffusion di) with the face to a neighbour
+// added (one expression: the last product and the sum round once)
+__device__ __forceinline__ float face_flux(float sum, float ni, float di, float v, float dv) {
+  return sum + 0.5f * (di + dv) * (v - ni);
 }
 // the new density of a node from its old value, the flux sum and E_rms^2
 __device__ __forceinline__ float cont_source(const ContArgs& A, float ni, float flux, float e2) {
@@ -1707,10 +1708,10 @@ __device__ __forceinline__ float cont_update(const ContArgs& A, size_t o, float 
   const float ni = A.n0[o];
   const float di = d_eff(A, ni);
   float flux = 0.f;
-  if (l) { const float v = A.n0[o - 1]; flux += face_flux(ni, di, v, d_eff(A, v)); }
-  if (r) { const float v = A.n0[o + 1]; flux += face_flux(ni, di, v, d_eff(A, v)); }
-  if (d) { const float v = A.n0[o - pitch]; flux += face_flux(ni, di, v, d_eff(A, v)); }
-  if (u) { const float v = A.n0[o + pitch]; flux += face_flux(ni, di, v, d_eff(A, v)); }
+  if (l) { const float v = A.n0[o - 1]; flux = face_flux(flux, ni, di, v, d_eff(A, v)); }
+  if (r) { const float v = A.n0[o + 1]; flux = face_flux(flux, ni, di, v, d_eff(A, v)); }
+  if (d) { const float v = A.n0[o - pitch]; flux = face_flux(flux, ni, di, v, d_eff(A, v)); }
+  if (u) { const float v = A.n0[o + pitch]; flux = face_flux(flux, ni, di, v, d_eff(A, v)); }
   return cont_source(A, ni, flux, e2);
 }
 
@@ -1773,10 +1774,10 @@ __device__ __forceinline__ void cont_rows(const ContArgs& A, int bx, int by, int
     }
     const float ni = n[q + 1], di = D[q + 1];
     float flux = 0.f;
-    if (i > A.L) flux += face_flux(ni, di, nl[q], d_eff(A, nl[q]));
-    if (i < A.R) flux += face_flux(ni, di, nr[q], d_eff(A, nr[q]));
-    if (j > A.B) flux += face_flux(ni, di, n[q], D[q]);
-    if (j < A.T) flux += face_flux(ni, di, n[q + 2], D[q + 2]);
+    if (i > A.L) flux = face_flux(flux, ni, di, nl[q], d_eff(A, nl[q]));
+    if (i < A.R) flux = face_flux(flux, ni, di, nr[q], d_eff(A, nr[q]));
+    if (j > A.B) flux = face_flux(flux, ni, di, n[q], D[q]);
+    if (j < A.T) flux = face_flux(flux, ni, di, n[q + 2], D[q + 2]);
     const float nn = cont_source(A, ni, flux, e2[q]);
     A.n1[o[q]] = nn;
     if (!isfinite(nn) || !isfinite(e2[q])) A.err[threadIdx.x & 63] = 1;
@@ -2495,7 +2496,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       const float exl0 = __shfl_up(ex0, 1, 64);
       if (own && eyc)
         str<O32>(A.acc1, row_addr(A, i, 0),
-                 base_win(acc0, i > 0 ? exl0 : 0.f, i < NX ? ex0 : 0.f, 0.f, eyn_p, fxe, 2.f));
+                 base_win0(acc0, i > 0 ? exl0 : 0.f, i < NX ? ex0 : 0.f, eyn_p, fxe));
     }
     // window at node (i, j)
     const float exl = __shfl_up(exn, 1, 64);

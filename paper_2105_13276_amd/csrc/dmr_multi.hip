@@ -85,7 +85,10 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
   // window of the wave's node row r, Ey of the row below it
   auto window = [&](int r, float yd) {
     const float fy = YE && (r == rb || r == rt) ? 2.f : 1.f;
-    return base_win(ac[r], lane_left(ex[r]), ex[r], yd, ey[r], fx, fy);
+    const float exl = lane_left(ex[r]);
+    const float v = base_win(ac[r], exl, ex[r], yd, ey[r], fx, fy);
+    const float v0 = base_win0(ac[r], exl, ex[r], ey[r], fx);
+    return YE && r == rb ? v0 : v;
   };
   // the wave's border rows to its neighbours
   auto publish = [&](int b) {
