@@ -1231,6 +1231,14 @@ __device__ __forceinline__ void fine2_tile(const EMArgs& A, int bx, int by, floa
 // phase tests its neighbours.  Every entity is computed with the operations
 // and operands of fine2_tile (the helpers above), so the results are
 // identical to it and to two one-substep launches.
+// A small patch is bound by this chain of phases, one wave or two per SIMD:
+// each phase reads all it needs from LDS before it tests anything (values
+// selected, not branched over: a branch per neighbour put up to four LDS round
+// trips in a row), and the coarse E of the boundary lines, which only some
+// tiles need, is the last waves' work, not all waves'.  Phases A to D of a
+// 16 x 4 tile on a 65 x 65 patch: 0.83, 0.73, 0.55, 0.71 us before, 0.59,
+// 0.61, 0.49, 0.58 us so (first use of the code in a launch included: repeated
+// in place, the old phases took 0.47, 0.54, 0.39, 0.46).
 // ---------------------------------------------------------------------------
 template <int TY, int NT, int TW, bool R4 = false>
 __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, float cey_src,
@@ -1245,8 +1253,8 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
   __shared__ float j2X[FN], j2Y[FN];  // J2 of the tile's own edges
   __shared__ float sN[FN];
   constexpr int CW = TW / 2 + 6, CH = TY / 2 + 6;
-  __shared__ float sC[5][CW > CH ? CW : CH];  // coarse E on the boundary lines after the step
-  __shared__ float sO[5][CW > CH ? CW : CH];  // and before it
+  __shared__ float sC[4][CW > CH ? CW : CH];  // coarse E on the boundary lines after the step
+  __shared__ float sO[4][CW > CH ? CW : CH];  // and before it
 
   const int i0 = A.L + bx * TW;
   const int j0 = A.B + by * TY;
@@ -1297,38 +1305,38 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
   // step there (as in fine2_tile)
   constexpr int RS = R4 ? 2 : 1;  // fine -> coarse index shift
   const int cx0 = ((i0 - 4) >> RS) - 1, cy0 = ((j0 - 4) >> RS) - 1;
-  int cg = -1, cc = 0;
+  // Lines 0 / 1: x-edges of rows B / T, 2 / 3: y-edges of columns L / R, one
+  // edge a thread, by the block's last waves: their frame positions take no
+  // part in phase A.
+  constexpr int NR = 2 * (CW + CH), CT = (NR + 63) / 64 * 64;
+  static_assert(CT <= NT, "boundary edges of a tile");
+  const int ct = tid - (NT - CT);
+  const int cg = ct < CW ? 0 : ct < 2 * CW ? 1 : ct < 2 * CW + CH ? 2 : 3;
+  const int cc = ct - (cg < 2 ? cg * CW : 2 * CW + (cg - 2) * CH);
+  const bool crow = cg < 2;
+  // the edge's lower cell / node (ca, cb); along the edge: (cu, 1 - cu)
+  const int cu = crow ? 1 : 0;
+  const int ca = crow ? cx0 + cc : (cg == 3 ? (R >> RS) : (L >> RS));
+  const int cb = crow ? (cg == 1 ? (T >> RS) : (B >> RS)) : cy0 + cc;
+  // 0..2: E along the line, one line back (across), on it, one ahead;
+  // 3..6: E across it, before and behind, at both ends; 7, 8: Hz before and
+  // behind; 9: J~; 10, 11: density at both ends
   float qc[12];
-  if (tid < CW) { cg = 0; cc = tid; }
-  else if (tid < 2 * CW) { cg = 1; cc = tid - CW; }
-  else if (tid < 2 * CW + CH) { cg = 2; cc = tid - 2 * CW; }
-  else if (tid < 2 * CW + 2 * CH) { cg = 3; cc = tid - 2 * CW - CH; }
-  {
+  if (ct >= 0) {
     const unsigned cp4 = (unsigned)A.cpitch * 4u;
-    const int NXc = A.cnx, NYc = A.cny;
+    const int NXc = A.cnx, NYc = A.cny, cv = 1 - cu;
     auto cidx = [=](int a, int b) {  // clamped coarse byte offset
       const int aa = a < 0 ? 0 : (a > NXc ? NXc : a), bb = b < 0 ? 0 : (b > NYc ? NYc : b);
       return __umul24((unsigned)bb, cp4) + ((unsigned)aa << 2);
     };
-    if (cg <= 1) {  // x-edge (ic, J) of a boundary row (threads without a role: cg = -1)
-      const int ic = cx0 + cc, J = cg == 1 ? (T >> RS) : (B >> RS);
-      qc[0] = ldo(A.cex0, cidx(ic, J - 1)); qc[1] = ldo(A.cex0, cidx(ic, J));
-      qc[2] = ldo(A.cex0, cidx(ic, J + 1));
-      qc[3] = ldo(A.cey0, cidx(ic, J - 1)); qc[4] = ldo(A.cey0, cidx(ic + 1, J - 1));
-      qc[5] = ldo(A.cey0, cidx(ic, J)); qc[6] = ldo(A.cey0, cidx(ic + 1, J));
-      qc[7] = ldo(A.chz0, cidx(ic, J - 1)); qc[8] = ldo(A.chz0, cidx(ic, J));
-      qc[9] = ldo(A.cjx0, cidx(ic, J)); qc[10] = ldo(A.cn0, cidx(ic, J));
-      qc[11] = ldo(A.cn0, cidx(ic + 1, J));
-    } else {        // y-edge (I, jc) of a boundary column
-      const int jc = cy0 + cc, I = cg == 3 ? (R >> RS) : (L >> RS);
-      qc[0] = ldo(A.cey0, cidx(I - 1, jc)); qc[1] = ldo(A.cey0, cidx(I, jc));
-      qc[2] = ldo(A.cey0, cidx(I + 1, jc));
-      qc[3] = ldo(A.cex0, cidx(I - 1, jc)); qc[4] = ldo(A.cex0, cidx(I - 1, jc + 1));
-      qc[5] = ldo(A.cex0, cidx(I, jc)); qc[6] = ldo(A.cex0, cidx(I, jc + 1));
-      qc[7] = ldo(A.chz0, cidx(I - 1, jc)); qc[8] = ldo(A.chz0, cidx(I, jc));
-      qc[9] = ldo(A.cjy0, cidx(I, jc)); qc[10] = ldo(A.cn0, cidx(I, jc));
-      qc[11] = ldo(A.cn0, cidx(I, jc + 1));
-    }
+    const float *eal = crow ? A.cex0 : A.cey0, *eac = crow ? A.cey0 : A.cex0;
+    const unsigned o0 = cidx(ca, cb), om = cidx(ca - cv, cb - cu), op = cidx(ca + cv, cb + cu);
+    const unsigned o1 = cidx(ca + cu, cb + cv), om1 = cidx(ca - cv + cu, cb - cu + cv);
+    qc[0] = ldo(eal, om); qc[1] = ldo(eal, o0); qc[2] = ldo(eal, op);
+    qc[3] = ldo(eac, om); qc[4] = ldo(eac, om1); qc[5] = ldo(eac, o0); qc[6] = ldo(eac, o1);
+    qc[7] = ldo(A.chz0, om); qc[8] = ldo(A.chz0, o0);
+    qc[9] = ldo(crow ? A.cjx0 : A.cjy0, o0);
+    qc[10] = ldo(A.cn0, o0); qc[11] = ldo(A.cn0, o1);
   }
   // region tests in frame coordinates (origin o, width TW + w, height TY + h)
   auto in_reg = [](int ci, int cj, int o, int w, int h) {
@@ -1341,7 +1349,10 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
   // entity's value)
 #pragma unroll
   for (int q = 0; q < NP; q++)
-    if (inf[q]) { rX[po[q]] = pex[q]; rY[po[q]] = pey[q]; }
+    if (inf[q]) {
+      rX[po[q]] = pex[q]; rY[po[q]] = pey[q];
+      sN[po[q]] = ndok[q] ? pn[q] : 0.f; sH0[po[q]] = phz[q];
+    }
   __syncthreads();
 
   // L(L(E)) of the filter at frame offset p of a padded field x: the
@@ -1382,36 +1393,38 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     return cfb(w0, w1, sO[g][x], sO[g][x + 1], sC[g][x], sC[g][x + 1], fr);
   };
   const float S = A.S;
+  // window increment of node (i, j) from its edges inside the patch
+  auto win = [=](int i, int j, float vl, float vr, float vd, float vu) {
+    const bool l = i > L, r = i < R, d = j > B, u = j < T;
+    const float l2 = vl * vl, d2 = vd * vd;
+    const float sl = l ? l2 : 0.f, sd = d ? d2 : 0.f;
+    const float r2 = sl + vr * vr, u2 = sd + vu * vu;
+    return win_e2(r ? r2 : sl, l + r, u ? u2 : sd, d + u);
+  };
 
-  // -- phase A: n, old Hz, coarse E after the step on the boundary lines;
-  // filtered E0 over origin -5
-#pragma unroll
-  for (int q = 0; q < NP; q++)
-    if (inf[q]) { sN[po[q]] = ndok[q] ? pn[q] : 0.f; sH0[po[q]] = phz[q]; }
-  {
-    float v;
+  // -- phase A: coarse E after the step on the boundary lines; filtered E0
+  // over origin -5
+  if (ct >= 0) {
     const float cS = A.cS, c1 = A.cc1;
-    if (cg <= 1) {
-      const int ic = cx0 + cc;
-      float hp = base_hz(qc[7], cS, qc[4], qc[3], qc[1], qc[0]);
-      if (ic == A.cis - 1) hp += cS * cey_src;
-      float h = base_hz(qc[8], cS, qc[6], qc[5], qc[2], qc[1]);
-      if (ic == A.cis - 1) h += cS * cey_src;
-      const float kap = base_kap(A.ckn, qc[10], qc[11]);
-      v = base_ex(qc[1], kap, cS, h, hp, c1, qc[9]);
-    } else {
-      const int I = cg == 3 ? (R >> RS) : (L >> RS);
-      float h = base_hz(qc[8], cS, qc[2], qc[1], qc[6], qc[5]);
-      if (I == A.cis - 1) h += cS * cey_src;
-      float hl = base_hz(qc[7], cS, qc[1], qc[0], qc[4], qc[3]);
-      if (I - 1 == A.cis - 1) hl += cS * cey_src;
-      float curl = -cS * (h - hl);
-      if (I == A.cis) curl += cS * chz_src;
-      const float kap = base_kap(A.ckn, qc[10], qc[11]);
-      v = base_ey(qc[1], kap, curl, c1, qc[9]);
+    const int hs = A.cis - 1;  // column of cells with the incident Ey
+    // Hz behind (h) and before (hp) the edge, from the E of the cells' sides
+    float h = base_hz(qc[8], cS, crow ? qc[6] : qc[2], crow ? qc[5] : qc[1],
+                      crow ? qc[2] : qc[6], crow ? qc[1] : qc[5]);
+    float hp = base_hz(qc[7], cS, crow ? qc[4] : qc[1], crow ? qc[3] : qc[0],
+                       crow ? qc[1] : qc[4], crow ? qc[0] : qc[3]);
+    const float hi = h + cS * cey_src, hpi = hp + cS * cey_src;
+    h = ca == hs ? hi : h;
+    hp = ca - (1 - cu) == hs ? hpi : hp;
+    const float kap = base_kap(A.ckn, qc[10], qc[11]);
+    float curl = -cS * (h - hp);
+    const float cui = curl + cS * chz_src;
+    curl = ca == A.cis ? cui : curl;
+    const float vx = base_ex(qc[1], kap, cS, h, hp, c1, qc[9]);
+    const float vy = base_ey(qc[1], kap, curl, c1, qc[9]);
+    if (ct < NR) {
+      sC[cg][cc] = crow ? vx : vy;
+      sO[cg][cc] = qc[1];  // the line's own coarse E entering
     }
-    sC[cg < 0 ? 4 : cg][cg < 0 ? 0 : cc] = v;
-    sO[cg < 0 ? 4 : cg][cg < 0 ? 0 : cc] = qc[1];  // the line's own coarse E entering
   }
 #pragma unroll
   for (int q = 0; q < NP; q++) {
@@ -1420,8 +1433,10 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const float ex = rX[p], ey = rY[p];
     float fx = ex, fy = ey;
     if (filt) {
-      if (j != B && j != T) fx = filter_e(ex, A.gamma, lap2(rX, p, i > L, i < R - 1, j > B, j < T));
-      if (i != L && i != R) fy = filter_e(ey, A.gamma, lap2(rY, p, i > L, i < R, j > B, j < T - 1));
+      const float gx = filter_e(ex, A.gamma, lap2(rX, p, i > L, i < R - 1, j > B, j < T));
+      const float gy = filter_e(ey, A.gamma, lap2(rY, p, i > L, i < R, j > B, j < T - 1));
+      fx = (j != B && j != T) ? gx : ex;
+      fy = (i != L && i != R) ? gy : ey;
     }
     fX[p] = exok[q] ? fx : 0.f;
     fY[p] = eyok[q] ? fy : 0.f;
@@ -1436,7 +1451,8 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const float y1 = fY[c + 1], y0 = fY[c], x1 = fX[c + FW], x0 = fX[c], ho = sH0[c];
     const float dey = y1 - y0;
     const float dex = x1 - x0;
-    return ok ? faraday(ho, S, dey, dex) : 0.f;
+    const float h = faraday(ho, S, dey, dex);
+    return ok ? h : 0.f;
   };
   float j1x[NP], j1y[NP];
 #pragma unroll
@@ -1479,13 +1495,7 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     if (!(inf[q] && own(ci_[q], cj_[q]))) continue;
     const int p = po[q], i = fi0 + ci_[q], j = fj0 + cj_[q];
     const float vl = e1X[p - 1], vr = e1X[p], vd = e1Y[p - FW], vu = e1Y[p];
-    float sx = 0.f, sy = 0.f;
-    int cx = 0, cy = 0;
-    if (i > L) { sx += vl * vl; cx++; }
-    if (i < R) { sx += vr * vr; cx++; }
-    if (j > B) { sy += vd * vd; cy++; }
-    if (j < T) { sy += vu * vu; cy++; }
-    acc1[q] = pacc[q] + win_e2(sx, cx, sy, cy);
+    acc1[q] = pacc[q] + win(i, j, vl, vr, vd, vu);
   }
 #pragma unroll
   for (int q = 0; q < NP; q++) {
@@ -1494,8 +1504,10 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const float ex = e1X[p], ey = e1Y[p];
     float fx = ex, fy = ey;
     if (filt) {
-      if (j != B && j != T) fx = filter_e(ex, A.gamma, lap2(e1X, p, i > L, i < R - 1, j > B, j < T));
-      if (i != L && i != R) fy = filter_e(ey, A.gamma, lap2(e1Y, p, i > L, i < R, j > B, j < T - 1));
+      const float gx = filter_e(ex, A.gamma, lap2(e1X, p, i > L, i < R - 1, j > B, j < T));
+      const float gy = filter_e(ey, A.gamma, lap2(e1Y, p, i > L, i < R, j > B, j < T - 1));
+      fx = (j != B && j != T) ? gx : ex;
+      fy = (i != L && i != R) ? gy : ey;
     }
     fX[p] = exok[q] ? fx : 0.f;
     fY[p] = eyok[q] ? fy : 0.f;
@@ -1508,7 +1520,8 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const float y1 = fY[c + 1], y0 = fY[c], x1 = fX[c + FW], x0 = fX[c], ho = sH1[c];
     const float dey = y1 - y0;
     const float dex = x1 - x0;
-    return ok ? faraday(ho, S, dey, dex) : 0.f;
+    const float h = faraday(ho, S, dey, dex);
+    return ok ? h : 0.f;
   };
 #pragma unroll
   for (int q = 0; q < NP; q++) {
@@ -1520,7 +1533,6 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const float h11 = far2(p, hzok[q]);
     const float h10 = far2(p - FW, cin && j - 1 >= B && j - 1 < T);
     const float h01 = far2(p - 1, i - 1 >= L && i - 1 < R && j >= B && j < T);
-    if (hzok[q] && ow) sto(tb.hz1, o, h11);
     sH2[p] = h11;
     const float ex = fX[p], ey = fY[p];
     const float n00 = sN[p], n10 = sN[p + 1], n01 = sN[p + FW];
@@ -1530,25 +1542,20 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const float dhx = h11 - h10;
     const float ax = ampere(ex, kx, S * dhx, A.c1, j1x[q]);
     const float exn = exok[q] ? ((j != B && j != T) ? ax : bx) : 0.f;
-    if (exok[q] && ow) {
-      const float jn = drude(A.a, j1x[q], kx, ex, exn);
-      sto(tb.ex1, o, exn);
-      sto(tb.jx1, o, jn);
-      j2X[p] = jn;
-    }
+    const float jnx = drude(A.a, j1x[q], kx, ex, exn);
     const float ney = 0.5f * (n00 + n01);
     const float ky = A.kn * ney;
     const float dhy = h11 - h01;
     const float ay = ampere(ey, ky, -S * dhy, A.c1, j1y[q]);
     const float eyn = eyok[q] ? ((i != L && i != R) ? ay : by) : 0.f;
-    if (eyok[q] && ow) {
-      const float jn = drude(A.a, j1y[q], ky, ey, eyn);
-      sto(tb.ey1, o, eyn);
-      sto(tb.jy1, o, jn);
-      j2Y[p] = jn;
-    }
+    const float jny = drude(A.a, j1y[q], ky, ey, eyn);
     e2X[p] = exn;
     e2Y[p] = eyn;
+    j2X[p] = jnx;
+    j2Y[p] = jny;
+    if (ow && hzok[q]) sto(tb.hz1, o, h11);
+    if (ow && exok[q]) { sto(tb.ex1, o, exn); sto(tb.jx1, o, jnx); }
+    if (ow && eyok[q]) { sto(tb.ey1, o, eyn); sto(tb.jy1, o, jny); }
   }
   __syncthreads();
 
@@ -1559,13 +1566,7 @@ __device__ __forceinline__ void fine2_fast(const EMArgs& A, int bx, int by, floa
     const int p = po[q], i = fi0 + ci_[q], j = fj0 + cj_[q];
     if (ndok[q]) {
       const float vl = e2X[p - 1], vr = e2X[p], vd = e2Y[p - FW], vu = e2Y[p];
-      float sx = 0.f, sy = 0.f;
-      int cx = 0, cy = 0;
-      if (i > L) { sx += vl * vl; cx++; }
-      if (i < R) { sx += vr * vr; cx++; }
-      if (j > B) { sy += vd * vd; cy++; }
-      if (j < T) { sy += vu * vu; cy++; }
-      sto(tb.acc, tb.off(i, j), acc1[q] + win_e2(sx, cx, sy, cy));
+      sto(tb.acc, tb.off(i, j), acc1[q] + win(i, j, vl, vr, vd, vu));
     }
     if constexpr (R4) {
       // r = 4, after the second pair: 4 x 4 cells at the half levels after
@@ -2436,7 +2437,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       if (i == A.is - 1) hzn += S * ey_src;
       if (store && own && !(skc && j >= A.sB && j < A.sT)) str<O32>(A.hz1, o, hzn);
     }
-    const float hzl = __shfl_up(hzn, 1, 64);  // Hz(i-1, j)
+    const float hzl = lane_left(hzn);  // Hz(i-1, j)
 
     // Ampere + Drude, Eqs. (1), (3): x-edges
     float exn = 0.f;
@@ -2471,8 +2472,8 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       eyn = base_ey(cur.ey, kapy, curl, c1, cur.jy);
     }
     if (j < NY && (wave_has_left || wave_has_right)) {
-      const float nr = __shfl_down(eyn, 1, 64), orr = __shfl_down(cur.ey, 1, 64);
-      const float nl = __shfl_up(eyn, 1, 64), ol = __shfl_up(cur.ey, 1, 64);
+      const float nr = lane_right(eyn), orr = lane_right(cur.ey);
+      const float nl = lane_left(eyn), ol = lane_left(cur.ey);
       if (i == 0) eyn = mur_x ? orr + cm * (nr - cur.ey) : 0.f;
       if (i == NX) eyn = mur_x ? ol + cm * (nl - cur.ey) : 0.f;
     }
@@ -2493,13 +2494,13 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
           str<O32>(A.jx1, row_addr(A, i, 0), a * jx0_old + 2.f * kap0 * (ex0_old + ex0));
         }
       }
-      const float exl0 = __shfl_up(ex0, 1, 64);
+      const float exl0 = lane_left(ex0);
       if (own && eyc)
         str<O32>(A.acc1, row_addr(A, i, 0),
                  base_win0(acc0, i > 0 ? exl0 : 0.f, i < NX ? ex0 : 0.f, eyn_p, fxe));
     }
     // window at node (i, j)
-    const float exl = __shfl_up(exn, 1, 64);
+    const float exl = lane_left(exn);
     if (j > 0) {
       if (store && own)
         str<O32>(A.acc1, o, base_win(cur.acc, i > 0 ? exl : 0.f, i < NX ? exn : 0.f, eyn_p,
@@ -2529,7 +2530,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
     const RowAddr o = row_addr(A, i, j);
     const float hzn = base_hz(cur.hz, S, cur.ey1, cur.ey, nxt.ex, cur.ex);
     if (store && own) str<O32>(A.hz1, o, hzn);
-    const float hzl = __shfl_up(hzn, 1, 64);
+    const float hzl = lane_left(hzn);
     const float kapx = base_kap(kn, cur.n, cur.n1);
     const float exn = base_ex(cur.ex, kapx, S, hzn, hzn_p, c1, cur.jx);
     if (store && own) {
@@ -2543,7 +2544,7 @@ __device__ __forceinline__ void em_stream_body(const EMArgs& A, int cw, int k, i
       str<O32>(A.ey1, o, eyn);
       str<O32>(A.jy1, o, a * cur.jy + 2.f * kapy * (cur.ey + eyn));
     }
-    const float exl = __shfl_up(exn, 1, 64);
+    const float exl = lane_left(exn);
     if (store && own) str<O32>(A.acc1, o, base_win(cur.acc, exl, exn, eyn_p, eyn));
     hzn_p = hzn;
     eyn_p = eyn;
