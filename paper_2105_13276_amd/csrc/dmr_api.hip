@@ -89,7 +89,7 @@ struct Layout {
   size_t plane0 = 0, plane1 = 0;
   int pitch0 = 0, pitch1 = 0;
   size_t off_l1 = 0, off_flag = 0, off_scan = 0, off_list = 0, off_desc = 0,
-         off_err = 0, off_stage = 0, off_hzp = 0, off_far = 0, total = 0;
+         off_err = 0, off_stage = 0, off_hzp = 0, off_far = 0, off_src = 0, total = 0;
   int NB = 0;
   // union-of-blocks fine level: two block maps, two tile lists (64 x 4 tiles
   // at most over the fine domain)
@@ -129,6 +129,7 @@ Layout layout_of(const dmr_params* p) {
   L.off_err = off;   off += 256;
   L.off_stage = off; off += align256(stage * sizeof(float));
   L.off_hzp = off;   off += align256(L.plane0 * sizeof(float));
+  L.off_src = off;   off += align256(kSrcSteps * sizeof(float2));
   L.off_far = off;
   if (refined(p)) off += align256(6 * L.plane0 * sizeof(float));
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
@@ -309,6 +310,21 @@ struct dmr_sim {
   int64_t near_gen = -1;    // growth (ugen) they were made for
   bool near_combine = true; // base step around the patch and substeps in one launch
   int h_desc[16] = {};
+  // one period of a refined run as a graph (period_steps); pg_key: what the
+  // recorded launches depend on, pg_seen: periods run with it
+  struct PeriodKey {
+    const void* ptr[32];
+    int ext[4], v[6];
+    int64_t ugen;
+  };
+  PeriodKey pg_key{};
+  hipGraphExec_t pg_exec = nullptr;
+  hipStream_t pg_st = nullptr;  // records it (default priority)
+  int pg_seen = 0;
+  bool pg_on = true;            // DMR_PERIOD=0: off
+  bool recording = false;
+  int period() const { return kRing * L0.spb; }
+  float2* d_src = nullptr;      // incident values of the period's steps
   // patch built at t = 0, and whether its density came from a fine seed
   bool had0 = false, keep_n0 = false;
   int ext0[4] = {0, 0, 0, 0};
@@ -986,9 +1002,10 @@ int run_copies(dmr_sim* s, const CopyJobs& J) {
   return e == hipSuccess ? DMR_OK : hipfail(s, e, "tape copy");
 }
 
-// What follows a base step: the window and continuity cadence and the growth
-// test (or, in the adjoint's replay, the recorded growth).
-int step_close(dmr_sim* s, StepCtx* cx) {
+// What follows a base step: the window and continuity cadence (step_cont) and
+// the growth test or, in the adjoint's replay, the recorded growth
+// (step_close: both).
+int step_cont(dmr_sim* s, StepCtx* cx) {
   const dmr_params& p = s->p;
   const bool st = cx && cx->store;
   hipError_t e = hipSuccess;
@@ -1051,6 +1068,12 @@ int step_close(dmr_sim* s, StepCtx* cx) {
     }
     if (update) s->ncur = 1 - s->ncur;
   }
+  return DMR_OK;
+}
+
+int step_close(dmr_sim* s, StepCtx* cx) {
+  const dmr_params& p = s->p;
+  if (int rc = step_cont(s, cx)) return rc;
   if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every == 0) {
     if (cx && cx->forced) {
       if (!cx->force_grow) return DMR_OK;
@@ -1150,7 +1173,8 @@ int em_part(dmr_sim* s, StepCtx* cx, const NearWin* win) {
   // coarse (or uniform) EM step n -> n+1
   EMArgs A;
   make_base_em(s, c, s->ncur, &A);
-  incident_values(s, s->step, &A.ey_src, &A.hz_src);
+  if (s->recording) A.src = s->d_src + s->step % s->period();
+  else incident_values(s, s->step, &A.ey_src, &A.hz_src);
   const int seg = win ? kNearSeg : s->seg0, depth = win ? 2 : s->depth0;
   const StreamWin sw = win ? win->stream : StreamWin();
   if (win) A.acc1 = win->acc1;
@@ -1181,7 +1205,7 @@ int em_part(dmr_sim* s, StepCtx* cx, const NearWin* win) {
     const Level& C = s->L0;
     G->chz0 = C.hz[c]; G->cjx0 = C.jx[c]; G->cjy0 = C.jy[c]; G->cn0 = C.n[s->ncur];
     G->cS = C.S; G->cc1 = C.c1; G->ckn = C.kn; G->cis = p.tfsf_i;
-    G->cey_src = A.ey_src; G->chz_src = A.hz_src;
+    G->cey_src = A.ey_src; G->chz_src = A.hz_src; G->src = A.src;
     G->cnx = p.nx; G->cny = p.ny;
   };
   if (combined) {  // base step and both patch substeps (r = 4: the first pair), one launch
@@ -1523,6 +1547,110 @@ float* array_of(dmr_sim* s, int field, int level, double* scale) {
   return nullptr;
 }
 
+// One period (8 window blocks) of a refined run whose steps are launch-bound,
+// as one graph.  A launch on its own costs the host 3.7 us and the device
+// about 0.7 us more than a graph's node does: 512x256 (r = 2) 7.0 us a step
+// launch by launch, 6.3 from a graph; 256x128 (r = 4, three launches) 13.8 and
+// 11.7.  Over a period every plane, ring slot and buffer parity returns to where
+// it was, so the recorded launches serve every later one; what changes, the
+// incident values, is in d_src.  Recording (2 us a launch) is left until the
+// device has a period's work queued and three periods or more are to come or
+// three have run.  Runs that are split around the fine level (can_split) and
+// uniform runs wait for the device, not for launches: 1.67 and 1.63 us a step on
+// uniform 256x128.  Not used while times are taken or while the caller records
+// the stream itself.
+int period_steps(dmr_sim* s, int64_t n, bool* ran) {
+  const dmr_params& p = s->p;
+  const int K = s->period(), spb = s->L0.spb;
+  if (!s->pg_on || !s->has_patch || !p.continuity_on || s->timing || n < K || K > kSrcSteps ||
+      (K & 1) || s->step % K || s->blocks < kRing || s->blocks % kRing)
+    return DMR_OK;
+  if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every + K > p.regrid_every) return DMR_OK;
+  if (s->uni && s->near_gen != s->ugen) return DMR_OK;
+  const int parts = (spb + s->multi_t - 1) / s->multi_t;
+  if (can_split(s, (spb + parts - 1) / parts)) return DMR_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return DMR_OK;
+  }
+  if (cap != hipStreamCaptureStatusNone) return DMR_OK;
+
+  dmr_sim::PeriodKey key;
+  memset(&key, 0, sizeof key);
+  int np = 0;
+  for (const Level* L : {&s->L0, &s->L1}) {
+    for (int b = 0; b < 2; b++)
+      for (float* q : {L->hz[b], L->ex[b], L->ey[b], L->jx[b], L->jy[b], L->n[b]}) key.ptr[np++] = q;
+    key.ptr[np++] = L->acc;
+  }
+  for (int q = 0; q < 4; q++) key.ext[q] = s->ext[q];
+  key.v[0] = s->ccur; key.v[1] = s->ncur; key.v[2] = s->ntiles; key.v[3] = s->tyu; key.v[4] = s->acur;
+  key.ugen = s->ugen;
+  if (memcmp(&key, &s->pg_key, sizeof key) != 0) {
+    if (s->pg_exec) {
+      HIPCHK(s, hipStreamSynchronize(s->st));
+      (void)hipGraphExecDestroy(s->pg_exec);
+      s->pg_exec = nullptr;
+    }
+    s->pg_key = key;
+    s->pg_seen = 0;
+  }
+  if (!s->pg_exec) {
+    const int seen = s->pg_seen++;
+    if (seen < 1 || (seen < 3 && n < 3 * (int64_t)K)) return DMR_OK;
+    hipPointerAttribute_t at{};
+    int dev = 0;
+    const bool here = hipPointerGetAttributes(&at, s->ws) == hipSuccess &&
+                      hipGetDevice(&dev) == hipSuccess && at.device == dev;
+    if (!here || (!s->pg_st && hipStreamCreateWithFlags(&s->pg_st, hipStreamNonBlocking) != hipSuccess) ||
+        hipStreamBeginCapture(s->pg_st, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+      (void)hipGetLastError();
+      s->pg_on = false;
+      return DMR_OK;
+    }
+    const Level c0 = s->L0, c1 = s->L1;
+    const int ccur = s->ccur, ncur = s->ncur;
+    const int64_t step = s->step, blocks = s->blocks;
+    const hipStream_t st = s->st;
+    const std::string err = s->err;
+    s->st = s->pg_st;
+    s->recording = true;
+    int rc = DMR_OK;
+    for (int q = 0; q < K && !rc; q++) {
+      rc = em_part(s, nullptr, nullptr);
+      if (!rc) rc = step_cont(s, nullptr);
+    }
+    s->recording = false;
+    s->st = st;
+    hipGraph_t g = nullptr;
+    bool ok = hipStreamEndCapture(s->pg_st, &g) == hipSuccess && !rc;
+    ok = ok && hipGraphInstantiate(&s->pg_exec, g, nullptr, nullptr, 0) == hipSuccess;
+    if (g) (void)hipGraphDestroy(g);
+    // the host's side as before: nothing has run yet
+    s->L0 = c0; s->L1 = c1;
+    s->ccur = ccur; s->ncur = ncur;
+    s->step = step; s->blocks = blocks;
+    if (!ok) {  // launch by launch from here on
+      (void)hipGetLastError();
+      s->pg_exec = nullptr;
+      s->pg_on = false;
+      s->err = err;
+      return DMR_OK;
+    }
+  }
+  SrcVals V;
+  V.n = K;
+  for (int q = 0; q < K; q++) incident_values(s, s->step + q, &V.v[q].x, &V.v[q].y);
+  HIPCHK(s, launch_src_put(V, s->d_src, s->st));
+  HIPCHK(s, hipGraphLaunch(s->pg_exec, s->st));
+  s->step += K;
+  s->blocks += kRing;
+  *ran = true;
+  if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every == 0) return regrid(s, false);
+  return DMR_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1603,6 +1731,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   s->d_err = (int*)(s->ws + lay.off_err);
   s->stage = (float*)(s->ws + lay.off_stage);
   s->hzp = (float*)(s->ws + lay.off_hzp);
+  s->d_src = (float2*)(s->ws + lay.off_src);
   if (refined(p))
     for (int q = 0; q < 6; q++) s->far[q] = (float*)(s->ws + lay.off_far) + q * lay.plane0;
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
@@ -1641,6 +1770,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     s->multi_w = s->multi_w < 5 ? 0 : std::min(s->multi_w, 16);
   }
   if (const char* f = getenv("DMR_SPLIT_MIN")) s->split_min = atol(f);
+  if (const char* f = getenv("DMR_PERIOD")) s->pg_on = atoi(f) != 0;
   if (const char* f = getenv("DMR_CONT_MERGE")) s->cont_merge = atoi(f) != 0 ? 1 : 0;
   if (const char* f = getenv("DMR_FINE_REG"))
     (void)sscanf(f, "%ld,%d", &s->reg_min, &s->reg_waves);
@@ -1714,6 +1844,8 @@ int dmr_create(const dmr_params* p, const double* seed_base,
 void dmr_destroy(dmr_sim* s) {
   if (!s) return;
   (void)hipStreamSynchronize(s->st);
+  if (s->pg_exec) (void)hipGraphExecDestroy(s->pg_exec);
+  if (s->pg_st) (void)hipStreamDestroy(s->pg_st);
   if (s->rep_st) {
     (void)hipStreamSynchronize(s->rep_st);
     (void)hipStreamDestroy(s->rep_st);
@@ -1733,6 +1865,12 @@ void dmr_destroy(dmr_sim* s) {
 int dmr_step(dmr_sim* s, int64_t n) {
   if (!s || n < 0) return fail(s, DMR_EINVAL, "bad step count");
   while (n > 0) {
+    bool ran = false;
+    if (int rc = period_steps(s, n, &ran)) return rc;
+    if (ran) {
+      n -= s->period();
+      continue;
+    }
     // up to the next window block, in launches of equal length
     const int blk = s->L0.spb - (int)(s->step % s->L0.spb);
     const int64_t left = std::min<int64_t>(n, blk);

@@ -83,6 +83,15 @@ struct EMArgs {
   float* cfb_next;
   const float* cfb_prev;
   const int2* utiles;  // batched union levels: the instance's tile list
+  // incident values on the device instead of ey_src / hz_src and cey_src /
+  // chz_src (steps recorded in a graph; null: by value)
+  const float2* src;
+};
+
+// incident Ey, eta0 Hz of consecutive steps, by value for one launch
+struct SrcVals {
+  int n;
+  float2 v[kSrcSteps];
 };
 
 // several base-level steps in one launch (dmr_multi.hip)
@@ -195,6 +204,8 @@ hipError_t launch_prolong_union(const ProlongArgs& A, const int2* tiles, int nti
 // writes buffer 1 (hz1..), A.frac = time fraction of substep 1, restriction on
 hipError_t launch_fine2(const EMArgs& A, int ty, int nt, hipStream_t st);
 hipError_t launch_fine2_fast(const EMArgs& A, int tw, hipStream_t st);
+// dst[k] = V.v[k], k < V.n
+hipError_t launch_src_put(const SrcVals& V, float2* dst, hipStream_t st);
 // the same in registers (dmr_fine.hip; r = 2 rectangle); waves per block 16, 12
 // or 8 (0: by size); blocks of a w x h-cell patch, and the waves for several
 hipError_t launch_fine_reg(const EMArgs& A, int waves, hipStream_t st);

@@ -68,6 +68,14 @@ __device__ __forceinline__ void sto(float* p, unsigned b, float v) {
   *(float*)((char*)p + b) = v;
 }
 
+// a step's incident values, from the device (src) or by value.  A scalar load:
+// every wave reads the same two words, which an earlier launch wrote.
+__device__ __forceinline__ float2 incident(const float2* src, float ey, float hz) {
+  if (!src) return make_float2(ey, hz);
+  const auto* q = (const __attribute__((address_space(4))) float*)src;
+  return make_float2(q[0], q[1]);
+}
+
 // LDS of one patch-substep tile (64 x TY nodes), declared by the kernel so
 // that the boundary and the interior forms of the tile share it
 template <int TY, bool UN>
@@ -1631,7 +1639,8 @@ __global__ __launch_bounds__(NT) void k_fine2(EMArgs A) {
 // combined launch.
 template <int TW, bool R4>
 __global__ __launch_bounds__(step_threads(false, 4)) void k_fine2_fast(EMArgs A) {
-  fine2_fast<4, step_threads(false, 4), TW, R4>(A, blockIdx.x, blockIdx.y, A.cey_src, A.chz_src);
+  const float2 in = incident(A.src, A.cey_src, A.chz_src);
+  fine2_fast<4, step_threads(false, 4), TW, R4>(A, blockIdx.x, blockIdx.y, in.x, in.y);
 }
 
 
@@ -2576,8 +2585,9 @@ template <int DEPTH, bool ST = false>
 __global__ __launch_bounds__(kThreads) void k_em_stream(EMArgs A, int seg, int nseg, int nbx,
                                                         int nk, int cw0, int k0) {
   const int b = xcd_band(blockIdx.x, nbx * nk);
+  const float2 in = incident(A.src, A.ey_src, A.hz_src);
   em_stream_body<DEPTH, ST>(A, cw0 + (b % nbx) * (kThreads / 64) + (threadIdx.x >> 6), k0 + b / nbx,
-                            seg, nseg, A.ey_src, A.hz_src);
+                            seg, nseg, in.x, in.y);
 }
 
 // over a list of (62-column wave, group of four segments)
@@ -2891,17 +2901,18 @@ __global__ __launch_bounds__(step_threads(ST, TY)) void k_dmr_step(EMArgs C, EMA
   // the dispatcher starts first
   const int ntl = gridDim.x - ncb;
   const int b = blockIdx.x;
+  const float2 in = incident(C.src, C.ey_src, C.hz_src);
   if (b >= ntl) {
     const int w = xcd_band(b - ntl, ncb) * (NTC / 64) + (threadIdx.x >> 6);
     const int k = w / waves_x;
     if (k < nk)
-      em_stream_body<DEPTH, ST>(C, cw0 + w % waves_x, k0 + k, seg, nseg, C.ey_src, C.hz_src);
+      em_stream_body<DEPTH, ST>(C, cw0 + w % waves_x, k0 + k, seg, nseg, in.x, in.y);
     return;
   }
   if constexpr (!ST && TY == 4)
-    fine2_fast<TY, NTC, TW, R4>(F, b % nbx_f, b / nbx_f, F.cey_src, F.chz_src);
+    fine2_fast<TY, NTC, TW, R4>(F, b % nbx_f, b / nbx_f, in.x, in.y);
   else
-    fine2_tile<TY, NTC, true, ST, R4, TW>(F, b % nbx_f, b / nbx_f, F.cey_src, F.chz_src);
+    fine2_tile<TY, NTC, true, ST, R4, TW>(F, b % nbx_f, b / nbx_f, in.x, in.y);
 }
 
 // Batched combined step: blk[b] = (instance, g), g >= 0 a group of 16 base
@@ -3312,6 +3323,16 @@ hipError_t launch_prolong(const ProlongArgs& A, hipStream_t st) {
   const int nx = A.R - A.L + 1, ny = A.T - A.B + 1;
   dim3 g((nx + kTX - 1) / kTX, (ny + kThreads / kTX - 1) / (kThreads / kTX));
   hipLaunchKernelGGL(k_prolong, g, dim3(kThreads), 0, st, A);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(kSrcSteps) void k_src_put(SrcVals V, float2* dst) {
+  const int k = threadIdx.x;
+  if (k < V.n) dst[k] = V.v[k];
+}
+hipError_t launch_src_put(const SrcVals& V, float2* dst, hipStream_t st) {
+  if (V.n < 0 || V.n > kSrcSteps) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_src_put, dim3(1), dim3(kSrcSteps), 0, st, V, dst);
   return hipGetLastError();
 }
 

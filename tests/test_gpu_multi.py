@@ -117,6 +117,63 @@ def test_steps_split_around_the_fine_level(kind, monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["rect", "r4", "union", "static", "wide"])
+def test_periods_from_a_graph(kind, monkeypatch):
+    """Whole periods of a refined run replayed from one graph against launch by
+    launch: over growth tests at a period's end and inside one, stretches that
+    start and end inside a period, eager work and reads between the replays,
+    and a restart: the same bits and saved states."""
+    cfg, (sb, sf) = _refined(kind)
+    K = cfg["steps_per_period"]
+    for every in (4 * (K // 8), 2 * K):
+        cfg["regrid_every"] = every
+        runs = []
+        for env in ("0", "1"):
+            monkeypatch.setenv("DMR_PERIOD", env)
+            s = B.Sim(cfg, sb, sf)
+            got = []
+            for n in (K + 3, 6 * K, 3, 2 * K - 6, 5 * K, K, K):
+                s.step(n)
+                got.append({(f, lv): s.get(f, lv) for lv in (0, 1) for f in FIELDS})
+                got[-1]["patch"] = np.array(s.patch())
+            got[-1]["state"] = s.save(np.zeros(s.state_bytes(), np.uint8))[256:]
+            s.load(s.save())
+            s.step(4 * K + 5)
+            got.append({(f, lv): s.get(f, lv) for lv in (0, 1) for f in FIELDS})
+            s.sync()
+            s.close()
+            runs.append(got)
+        for x, y in zip(*runs):
+            assert x.keys() == y.keys()
+            for f in x:
+                assert np.array_equal(x[f], y[f]), f
+
+
+@pytest.mark.gpu
+def test_periods_while_the_caller_records():
+    """A period whose stream the caller is recording goes launch by launch into
+    the caller's graph: replayed, it gives the bits of the steps themselves."""
+    import torch
+    cfg, (sb, sf) = _refined("static")
+    K = cfg["steps_per_period"]
+    with torch.cuda.stream(torch.cuda.Stream()):
+        s, ref = B.Sim(cfg, sb, sf), B.Sim(cfg, sb, sf)
+        for q in (s, ref):
+            q.step(6 * K)
+            q.sync()
+        g = torch.cuda.CUDAGraph()
+        g.capture_begin(capture_error_mode="thread_local")
+        s.step(K)
+        g.capture_end()
+        g.replay()
+        ref.step(K)
+        for f in FIELDS:
+            for lv in (0, 1):
+                assert np.array_equal(s.get(f, lv), ref.get(f, lv)), f
+        s.sync()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kind", ["rect", "r4", "union"])
 def test_batch_steps_split_around_the_fine_levels(kind, monkeypatch):
     """A batch whose steps are split (tuned configuration, a captured interval,
