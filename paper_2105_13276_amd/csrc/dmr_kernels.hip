@@ -2901,14 +2901,19 @@ __global__ __launch_bounds__(step_threads(ST, TY)) void k_dmr_step(EMArgs C, EMA
   // the dispatcher starts first
   const int ntl = gridDim.x - ncb;
   const int b = blockIdx.x;
-  const float2 in = incident(C.src, C.ey_src, C.hz_src);
+  // (the replay is never recorded; two more registers would spill there)
+  const float2* sp = ST ? nullptr : C.src;
   if (b >= ntl) {
     const int w = xcd_band(b - ntl, ncb) * (NTC / 64) + (threadIdx.x >> 6);
     const int k = w / waves_x;
     if (k < nk)
+      {
+      const float2 in = incident(sp, C.ey_src, C.hz_src);
       em_stream_body<DEPTH, ST>(C, cw0 + w % waves_x, k0 + k, seg, nseg, in.x, in.y);
+    }
     return;
   }
+  const float2 in = incident(sp, F.cey_src, F.chz_src);
   if constexpr (!ST && TY == 4)
     fine2_fast<TY, NTC, TW, R4>(F, b % nbx_f, b / nbx_f, in.x, in.y);
   else
