@@ -247,3 +247,17 @@ def test_register_patch_tiles(w, h, x, y, waves, gamma, monkeypatch):
     for a, b in zip(*runs):
         for f in a:
             assert np.array_equal(a[f], b[f]), (f, int((a[f] != b[f]).sum()))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ny", [4, 5, 6, 7, 255])
+def test_fields_read_back_as_written(ny):
+    """Read-out in groups of rows: every remainder of the row count."""
+    cfg = W.make(257, ny, 16, "uniform", 1)
+    s = B.Sim(cfg, None, None)
+    g = np.random.Generator(np.random.PCG64(ny))
+    for f in ("ex", "ey"):
+        v = g.uniform(-1, 1, s.dims(f, 0)).astype(np.float32)
+        s.set(f, 0, v)
+        assert np.array_equal(s.get(f, 0), v) and np.array_equal(s.get_device(f, 0).cpu(), v)
+    s.close()
