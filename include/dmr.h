@@ -266,7 +266,9 @@ int dmr_sync(dmr_sim *s);
  * (events between back-to-back launches would add their own latency to
  * each), so the time of a class is that of its launches and of the gaps
  * between them.  dmr_get_timing fills total milliseconds and launch counts
- * per class since the last reset and synchronises the stream. */
+ * per class since the last reset and synchronises the stream.  Class 0
+ * counts base steps: a launch of several of them counts as that many, and
+ * while times are taken no period runs from a graph. */
 int dmr_set_timing(dmr_sim *s, int on);
 int dmr_get_timing(dmr_sim *s, double ms[4], int64_t launches[4]);
 
