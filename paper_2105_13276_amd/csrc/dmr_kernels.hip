@@ -1725,12 +1725,14 @@ __device__ __forceinline__ float cont_update(const ContArgs& A, size_t o, float 
   return cont_source(A, ni, flux, e2);
 }
 
-// Base level, RPT rows a thread (64 columns x 4 RPT rows per block of 256
+// Base level, R rows a thread (64 columns x 4 R rows per block of 256
 // threads): every load of a thread comes before its stores, and the diffusion
-// of a row serves the rows beside it.
-constexpr int kContRows = 4;
+// of a row serves the rows beside it.  Two or four rows in a plain run
+// (launch_cont), four in a batch, whose grid is always large (its block table
+// has 16 rows a block).
+constexpr int kContRowsBatch = 4;
+template <int R>
 __device__ __forceinline__ void cont_rows(const ContArgs& A, int bx, int by, int slot, int update) {
-  constexpr int R = kContRows;
   const int i = A.L + bx * kTX + (int)(threadIdx.x % kTX);
   const int j0 = A.B + (by * (kThreads / kTX) + (int)(threadIdx.x / kTX)) * R;
   if (i > A.R || j0 > A.T) return;
@@ -1977,8 +1979,9 @@ __global__ __launch_bounds__(kThreads) void k_cont(ContArgs A) {
   cont_body<FINE>(A, blockIdx.x, blockIdx.y, A.slot, A.update);
 }
 
+template <int R>
 __global__ __launch_bounds__(kThreads) void k_cont_rows(ContArgs A) {
-  cont_rows(A, blockIdx.x, blockIdx.y, A.slot, A.update);
+  cont_rows<R>(A, blockIdx.x, blockIdx.y, A.slot, A.update);
 }
 
 template <bool FINE>
@@ -1988,7 +1991,7 @@ __global__ __launch_bounds__(kThreads) void k_cont_batch(const ContArgs* __restr
   const int2 bi = blk[blockIdx.x];
   const ContArgs& A = args[bi.x];
   if constexpr (FINE) cont_body<true>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
-  else cont_rows(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
+  else cont_rows<kContRowsBatch>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
 }
 
 // cell (i, j) of a fine level made of the active blocks of act
@@ -3305,11 +3308,18 @@ hipError_t launch_line_flags(const float* n, int pitch, int I0, int J0, int I1, 
 hipError_t launch_cont(const ContArgs& A, bool fine, hipStream_t st) {
   const int nx = A.R - A.L + 1, ny = A.T - A.B + 1;
   dim3 g((nx + kTX - 1) / kTX, (ny + kThreads / kTX - 1) / (kThreads / kTX));
-  // four rows a thread on large grids (4096x2048: 67 -> 58 us), one on small
-  // ones, where the waves are too few for it (256x128: 5 -> 9 us)
-  if (!fine && (long)nx * ny >= (1L << 22)) {
-    g.y = (ny + kThreads / kTX * kContRows - 1) / (kThreads / kTX * kContRows);
-    hipLaunchKernelGGL(k_cont_rows, g, dim3(kThreads), 0, st, A);
+  // two rows a thread from 2^18 nodes on, four from 2^22, one on smaller grids,
+  // where the waves are too few for it.  us a step of a uniform run with one,
+  // two and four rows: 512x256 1.69 / 1.69 / -, 724x486 2.69 / 2.66 / -, 1024x512
+  // 2.75 / 2.71 / 2.88, 1531x777 6.17 / 6.04 / 6.17, 2048x1024 7.28 / 7.11 / 7.32;
+  // 32 steps of 8192x4096 - / 3.82 / 3.80 ms, 64 of a refined 4096x2048 run 2.91
+  // / 2.80 / 2.80 ms
+  const long nodes = (long)nx * ny;
+  if (!fine && nodes >= (1L << 18)) {
+    const int rows = kThreads / kTX * (nodes >= (1L << 22) ? 4 : 2);
+    g.y = (ny + rows - 1) / rows;
+    if (nodes >= (1L << 22)) hipLaunchKernelGGL(k_cont_rows<4>, g, dim3(kThreads), 0, st, A);
+    else hipLaunchKernelGGL(k_cont_rows<2>, g, dim3(kThreads), 0, st, A);
   } else if (fine) hipLaunchKernelGGL(k_cont<true>, g, dim3(kThreads), 0, st, A);
   else hipLaunchKernelGGL(k_cont<false>, g, dim3(kThreads), 0, st, A);
   return hipGetLastError();

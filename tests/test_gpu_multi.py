@@ -261,3 +261,23 @@ def test_fields_read_back_as_written(ny):
         s.set(f, 0, v)
         assert np.array_equal(s.get(f, 0), v) and np.array_equal(s.get_device(f, 0).cpu(), v)
     s.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(592, 448), (1040, 256), (528, 512)])
+def test_continuity_rows_of_a_plain_run_and_a_batch(nx, ny):
+    """The base level's continuity with two rows a thread (plain run of 2^18
+    nodes and more; 449, 257 and 513 rows of nodes) against the batch's four
+    rows a thread, and both levels' window: the same bits."""
+    cfg = W.make(nx, ny, 16, "dynamic", 1, erms_over_ebd=2.0)
+    dx = W.C0 / 110e9 / 16
+    seeds = W.seeds(cfg, [(0.6 * nx * dx, 0.5 * ny * dx)], [1e17])
+    s, b = B.Sim(cfg, *seeds), B.Batch([cfg], [seeds])
+    for n in (33, 64):
+        s.step(n)
+        b.step(n)
+        b.sync()
+        for f, lv in (("n", 0), ("erms2", 0), ("ring", 0), ("n", 1)):
+            assert np.array_equal(s.get(f, lv), b.instances[0].get(f, lv)), f
+    s.close()
+    b.close()
