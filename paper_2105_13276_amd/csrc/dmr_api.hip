@@ -89,7 +89,7 @@ struct Layout {
   size_t plane0 = 0, plane1 = 0;
   int pitch0 = 0, pitch1 = 0;
   size_t off_l1 = 0, off_flag = 0, off_scan = 0, off_list = 0, off_desc = 0,
-         off_err = 0, off_stage = 0, off_hzp = 0, off_far = 0, off_src = 0, total = 0;
+         off_err = 0, off_stage = 0, stage_bytes = 0, off_hzp = 0, off_far = 0, off_src = 0, total = 0;
   int NB = 0;
   // union-of-blocks fine level: two block maps, two tile lists (64 x 4 tiles
   // at most over the fine domain)
@@ -127,7 +127,8 @@ Layout layout_of(const dmr_params* p) {
   L.off_list = off;  off += align256(nb * 4);
   L.off_desc = off;  off += 256;
   L.off_err = off;   off += 256;
-  L.off_stage = off; off += align256(stage * sizeof(float));
+  L.stage_bytes = align256(stage * sizeof(float));
+  L.off_stage = off; off += L.stage_bytes;
   L.off_hzp = off;   off += align256(L.plane0 * sizeof(float));
   L.off_src = off;   off += align256(kSrcSteps * sizeof(float2));
   L.off_far = off;
@@ -2867,7 +2868,7 @@ int dmr_weighted_sum(dmr_sim* s, int level, const float* d_w, double* out) {
     return fail(s, DMR_EINVAL, "level %d not present", level);
   const Level& L = level == 0 ? s->L0 : s->L1;
   double* part = (double*)s->stage;  // 1024 partials + the result
-  if (s->lay.off_stage + 1025 * sizeof(double) > s->lay.total)
+  if (s->lay.stage_bytes < 1025 * sizeof(double))
     return fail(s, DMR_ENOMEM, "staging area too small");
   hipError_t e = launch_wdot(d_w, L.n[s->ncur], L.pitch, 0, 0, L.NX + 1, L.NY + 1, part,
                              part + 1024, s->st);
