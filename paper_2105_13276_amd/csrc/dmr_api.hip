@@ -717,7 +717,6 @@ void union_extents(dmr_sim* s) {
 // make h_act the level as it stands (restart): map and tile list to the
 // device, extents; no prolongation (the state carries the fine data)
 int union_install(dmr_sim* s) {
-  s->near_gen = -1;
   pick_union_rows(s, s->h_act);
   union_tiles(s, s->tyu, [&](int b) { return s->h_act[b] != 0; }, &s->h_tiles);
   HIPCHK(s, hipMemcpyAsync(s->d_act[s->acur], s->h_act.data(), s->h_act.size(),
@@ -730,6 +729,9 @@ int union_install(dmr_sim* s) {
   HIPCHK(s, hipStreamSynchronize(s->st));
   return DMR_OK;
 }
+
+bool split_grid(const dmr_sim* s);
+int near_blocks(dmr_sim* s);
 
 // Add the blocks of add ([NBy][NBx]) to the level.  strict: a block outside
 // the margins is an error (else it is left out).
@@ -787,7 +789,7 @@ int grow_union(dmr_sim* s, const uint8_t* add, bool keep_n, bool strict) {
   s->ntiles = (int)s->h_tiles.size();
   s->ugen++;
   union_extents(s);
-  return DMR_OK;
+  return split_grid(s) ? near_blocks(s) : DMR_OK;
 }
 
 // the growth test of the union: the flagged blocks inside the margins join
@@ -1363,7 +1365,9 @@ StreamWin near_window(const dmr_sim* s, int t, int seg = kNearSeg) {
 
 // union of blocks: the blocks within two blocks' reach of t + 1 cells of an
 // active one, and the streaming blocks that cover those and the t cells
-// around them
+// around them.  Made where the level changes (growth, load), which waits for
+// the device anyway: a step in between only queues launches, so that a caller
+// can record it.
 int near_blocks(dmr_sim* s) {
   const dmr_params& p = s->p;
   const int Bk = p.block, NBx = p.nx / Bk, NBy = p.ny / Bk;
@@ -1406,8 +1410,8 @@ int near_blocks(dmr_sim* s) {
   return DMR_OK;
 }
 
-// whether t steps of a run with a fine level are split (split_steps)
-bool can_split(dmr_sim* s, int t) {
+// Whether the grid is one whose steps may be split (split_steps)
+bool split_grid(const dmr_sim* s) {
   const dmr_params& p = s->p;
   // Where the base level is what a step waits for; on smaller grids the patch's
   // chain is, and the far launch only adds to it.  Per step, one launch a step
@@ -1419,11 +1423,14 @@ bool can_split(dmr_sim* s, int t) {
                      : p.r == 4       ? 1L << 20
                      : s->uni         ? 1L << 19
                                       : 1L << 18;
-  if (t < 2 || !s->has_patch || (long)p.nx * p.ny < least) return false;
-  if (s->uni) {
-    if (log2i(p.block) > 30 || (p.block & (p.block - 1))) return false;
-    return s->near_gen == s->ugen && s->near_share <= 0.5;
-  }
+  return s->multi_t >= 2 && (long)p.nx * p.ny >= least;
+}
+
+// whether t steps of a run with a fine level are split
+bool can_split(const dmr_sim* s, int t) {
+  const dmr_params& p = s->p;
+  if (t < 2 || !s->has_patch || !split_grid(s)) return false;
+  if (s->uni) return s->near_gen == s->ugen && s->near_share <= 0.5;
   const StreamWin w = near_window(s, t);
   return (double)w.ncw * 62 * w.nk * kNearSeg <= 0.5 * (p.nx + 1.0) * (p.ny + 1.0);
 }
@@ -1567,7 +1574,6 @@ int period_steps(dmr_sim* s, int64_t n, bool* ran) {
       (K & 1) || s->step % K || s->blocks < kRing || s->blocks % kRing)
     return DMR_OK;
   if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every + K > p.regrid_every) return DMR_OK;
-  if (s->uni && s->near_gen != s->ugen) return DMR_OK;
   const int parts = (spb + s->multi_t - 1) / s->multi_t;
   if (can_split(s, (spb + parts - 1) / parts)) return DMR_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1881,8 +1887,6 @@ int dmr_step(dmr_sim* s, int64_t n) {
       const int64_t parts = (left + most - 1) / most;
       t = (int)((left + parts - 1) / parts);
     }
-    if (s->has_patch && s->uni && s->near_gen != s->ugen)
-      if (int rc = near_blocks(s)) return rc;
     const bool split = can_split(s, t);
     if (s->has_patch && !split) t = 1;
     const bool last = t == n || (s->p.mode == DMR_DYNAMIC && (s->step + t) % s->p.regrid_every == 0);
@@ -2859,7 +2863,9 @@ int dmr_load(dmr_sim* s, const void* src, size_t bytes, int src_on_device) {
   }
   if (!s->uni) return DMR_OK;
   memcpy(s->h_act.data(), act.data(), act.size());
-  return union_install(s);
+  s->near_gen = -1;
+  if (int rc = union_install(s)) return rc;
+  return split_grid(s) ? near_blocks(s) : DMR_OK;
 }
 
 int dmr_weighted_sum(dmr_sim* s, int level, const float* d_w, double* out) {
