@@ -185,7 +185,11 @@ void dmr_destroy(dmr_sim *s);
  * substeps with boundary transfer and the fine -> coarse transfer
  * (Sec. III.C), every 1/8 period the window and continuity step on both
  * levels plus density transfers, and every regrid_every steps the growth
- * test (which synchronises the stream to read back 16 bytes of extents). */
+ * test (which synchronises the stream to read back 16 bytes of extents).
+ * Steps without a growth test may be recorded into a graph of the caller's
+ * (stream capture); the graph holds their incident values.  From the first
+ * recorded step on the handle queues each step as launches of its own, so that
+ * the graph's planes stay the handle's after any even number of steps. */
 int dmr_step(dmr_sim *s, int64_t n);
 
 /* Run the growth test now (Sec. III.A-D); grows the patch if needed. */

@@ -324,6 +324,11 @@ struct dmr_sim {
   int pg_seen = 0;
   bool pg_on = true;            // DMR_PERIOD=0: off
   bool recording = false;
+  // The caller has recorded steps of this handle.  Its graph names planes and
+  // may run again, also between further steps: from then on a step is a launch
+  // of its own, after which the planes' places follow from the step's parity
+  // alone (several steps in a launch, and split steps, move them about).
+  bool recorded = false;
   int period() const { return kRing * L0.spb; }
   float2* d_src = nullptr;      // incident values of the period's steps
   // patch built at t = 0, and whether its density came from a fine seed
@@ -1005,6 +1010,16 @@ int run_copies(dmr_sim* s, const CopyJobs& J) {
   return e == hipSuccess ? DMR_OK : hipfail(s, e, "tape copy");
 }
 
+// whether the caller is recording the stream into a graph
+bool being_recorded(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+
 // What follows a base step: the window and continuity cadence (step_cont) and
 // the growth test or, in the adjoint's replay, the recorded growth
 // (step_close: both).
@@ -1575,13 +1590,7 @@ int period_steps(dmr_sim* s, int64_t n, bool* ran) {
     return DMR_OK;
   if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every + K > p.regrid_every) return DMR_OK;
   const int parts = (spb + s->multi_t - 1) / s->multi_t;
-  if (can_split(s, (spb + parts - 1) / parts)) return DMR_OK;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s->st, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return DMR_OK;
-  }
-  if (cap != hipStreamCaptureStatusNone) return DMR_OK;
+  if (!s->recorded && can_split(s, (spb + parts - 1) / parts)) return DMR_OK;
 
   dmr_sim::PeriodKey key;
   memset(&key, 0, sizeof key);
@@ -1871,9 +1880,12 @@ void dmr_destroy(dmr_sim* s) {
 
 int dmr_step(dmr_sim* s, int64_t n) {
   if (!s || n < 0) return fail(s, DMR_EINVAL, "bad step count");
+  const bool now = n > 0 && being_recorded(s->st);
+  s->recorded = s->recorded || now;
   while (n > 0) {
     bool ran = false;
-    if (int rc = period_steps(s, n, &ran)) return rc;
+    if (!now)
+      if (int rc = period_steps(s, n, &ran)) return rc;
     if (ran) {
       n -= s->period();
       continue;
@@ -1881,7 +1893,7 @@ int dmr_step(dmr_sim* s, int64_t n) {
     // up to the next window block, in launches of equal length
     const int blk = s->L0.spb - (int)(s->step % s->L0.spb);
     const int64_t left = std::min<int64_t>(n, blk);
-    const int most = s->multi_t;
+    const int most = s->recorded ? 1 : s->multi_t;
     int t = 1;
     if (left > 1 && most > 1) {
       const int64_t parts = (left + most - 1) / most;
@@ -2973,6 +2985,7 @@ struct dmr_batch {
   std::vector<EMArgs> h_nem, h_nfem, h_nfem2;
   std::vector<MultiArgs> h_multi;
   std::vector<int2> h_blk_near, h_blk_far;
+  bool recorded = false;  // by the caller: no groups from then on (see dmr_sim)
   hipGraphExec_t gexec = nullptr;
   bool graph_ok = false;
   int graph_gp = 0;  // gp it was captured at
@@ -3435,7 +3448,7 @@ void batch_advance_group(dmr_batch* b, int* slot, int* update) {
 // whether the next steps, `left` of which are to be done, are a split group
 bool batch_at_group(const dmr_batch* b, int64_t left) {
   const dmr_sim* s = b->sims[0];
-  return b->tg && s->ccur == 0 && left >= b->tg && s->step % s->L0.spb % b->tg == 0 &&
+  return b->tg && !b->recorded && s->ccur == 0 && left >= b->tg && s->step % s->L0.spb % b->tg == 0 &&
          s->step % s->L0.spb + b->tg <= s->L0.spb;
 }
 
@@ -3869,6 +3882,10 @@ int dmr_batch_step(dmr_batch* b, int64_t n) {
   if (!b || n < 0) return DMR_EINVAL;
   (void)hipEventRecord(b->ev_in, b->user);
   (void)hipStreamWaitEvent(b->st, b->ev_in, 0);
+  if (n > 0 && !b->recorded && being_recorded(b->st)) {
+    b->recorded = true;
+    b->graph_ok = false;  // the interval's graph holds groups
+  }
   const int rc = batch_step(b, n);
   (void)hipEventRecord(b->ev_out, b->st);
   (void)hipStreamWaitEvent(b->user, b->ev_out, 0);

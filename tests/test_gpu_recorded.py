@@ -62,3 +62,86 @@ def test_first_steps_of_a_union_level(split_min, monkeypatch):
             _same(s, ref)
         s.sync()
         ref.sync()
+
+
+def _replayable(kind):
+    """No source (whose values a graph would hold as they were when recorded)
+    but given fields: a period's graph can run again and again."""
+    if kind in ("uniform", "uniform_no_continuity"):
+        cfg = W.make(200, 90, 32, "uniform", 1, tfsf_i=0, continuity_on=kind == "uniform")
+    elif kind == "r4":
+        cfg = W.make(160, 112, 32, "static", 1, r=4, block=8, tfsf_i=0, static_ext=(70, 40, 90, 61))
+    else:
+        cfg = W.make(256, 160, 32, "static", 1, tfsf_i=0, static_ext=(112, 64, 144, 96),
+                     regrid_rule="union" if kind == "union" else "blocks")
+    nx, ny = cfg["nx"], cfg["ny"]
+    g = np.random.Generator(np.random.PCG64(nx + ny))
+    base = 10.0 ** g.uniform(17, 20, (ny + 1, nx + 1))
+    fields = {f: 4e6 * g.uniform(-1, 1, d) for f, d in
+              (("ex", (ny + 1, nx)), ("ey", (ny, nx + 1)))}
+    return cfg, base, fields
+
+
+@pytest.mark.parametrize("kind,n,start", [
+    ("uniform", 64, 3), ("uniform_no_continuity", 8, 0), ("rect", 64, 3), ("rect", 64, 0),
+    ("r4", 64, 5), ("union", 64, 3)])
+def test_a_recorded_stretch_runs_again(kind, n, start, monkeypatch):
+    """A graph of a whole period (without continuity: of an even number of
+    steps), replayed in a row and between steps of the handle itself, is those
+    steps each time, wherever in a window block it starts."""
+    import torch
+    cfg, base, fields = _replayable(kind)
+    monkeypatch.setenv("DMR_SPLIT_MIN", "0")
+    warm = 6 * cfg["steps_per_period"] + start
+    with torch.cuda.stream(torch.cuda.Stream()):
+        s, ref = B.Sim(cfg, base, None), B.Sim(cfg, base, None)
+        for q in (s, ref):
+            for f, v in fields.items():
+                q.set(f, 0, v)
+            q.step(warm)
+        g = _record(s, n)
+        for again, eager in ((1, n), (3, n), (1, 5), (0, n - 5), (2, 0)):
+            for _ in range(again):
+                g.replay()
+            s.step(eager)
+            ref.step(again * n + eager)
+            if eager != 5:
+                _same(s, ref)
+            torch.zeros(1000, device="cuda").sum().item()  # other work between
+        s.sync()
+        ref.sync()
+
+
+def test_a_recorded_stretch_of_a_batch_runs_again():
+    """The same of a tuned batch; then whole intervals from the batch's graph."""
+    import torch
+    cfgs, sims = [], []
+    with torch.cuda.stream(torch.cuda.Stream()):
+        for nx, ny in ((512, 256), (640, 448)):
+            cfgs.append(W.make(nx, ny, 32, "static", 1, tfsf_i=0,
+                               static_ext=(nx // 2 - 16, ny // 2 - 8, nx // 2 + 16, ny // 2 + 8)))
+        seeds = [W.seeds(c) for c in cfgs]
+        b = B.Batch(cfgs, seeds)
+        sims = [B.Sim(c, *q) for c, q in zip(cfgs, seeds)]
+        for k, c in enumerate(cfgs):
+            e = np.random.Generator(np.random.PCG64(k)).uniform(-4e6, 4e6, (c["ny"], c["nx"] + 1))
+            B.Sim.set(b.instances[k], "ey", 0, e)
+            sims[k].set("ey", 0, e)
+        b.step(512 + 3)
+        for s in sims:
+            s.step(512 + 3)
+        g = torch.cuda.CUDAGraph()
+        g.capture_begin(capture_error_mode="thread_local")
+        try:
+            b.step(64)
+        finally:
+            g.capture_end()
+        for again, eager in ((2, 64), (1, 0), (1, 61), (0, 576)):
+            for _ in range(again):
+                g.replay()
+            b.step(eager)
+            b.sync()
+            for h, s in zip(b.instances, sims):
+                s.step(64 * again + eager)
+                _same(h, s)
+        b.close()
