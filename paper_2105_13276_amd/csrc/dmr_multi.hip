@@ -22,9 +22,9 @@ namespace dmr {
 namespace {
 
 // The region is stepped by the interior update everywhere, also where it
-// reaches beyond the grid: E that does not exist (or is zero, PEC) takes the
-// factor 0 for 1 / (1 + kap), which also drops it from the window of the
-// boundary nodes.  XE: the region holds column 0 or NX or a source column;
+// reaches beyond the grid: E that does not exist (or is zero, PEC) is set to +0
+// by a bit mask, whatever its neighbours hold, which also drops it from the
+// window of the boundary nodes.  XE: the region holds column 0 or NX or a source column;
 // YE: the wave holds row 0 or NY.
 template <int R, bool XE, bool YE>
 __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const float2* in, float* hzp,
@@ -66,20 +66,27 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
   const bool src = A.is > 0 && A.is >= x0 && A.is - 1 <= x0 + 63;
   const float fx = XE && (c0 || cN) ? 2.f : 1.f;
 
-  // (conditions without branches: short-circuit forms of them were compiled
-  // to code that lost the factor 0)
+  // edges that exist (PEC walls left out): by column, and by row as bits r
+  // (x-edges) and 16 + r (y-edges)
   const bool colx = !XE | ((i >= 0) & (i < NX));
   const bool coly = !XE | ((i >= 0) & (i <= NX) & (mur_x | !(c0 | cN)));
+  int rows = 0;
+  if (YE) {
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      const int j = jt + r;
+      rows |= ((j >= 0) & (j <= NY) & (mur_y | ((j != 0) & (j != NY)))) << r;
+      rows |= ((j >= 0) & (j < NY)) << (16 + r);
+    }
+  }
+  rows = __builtin_amdgcn_readfirstlane(rows);
   float kx[R], ky[R], rx[R], ry[R];
 #pragma unroll
   for (int r = 0; r < R; r++) {
     kx[r] = base_kap(kn, n[r], lane_right(n[r]));
     ky[r] = base_kap(kn, n[r], n[r + 1]);
-    const int j = jt + r;
-    const bool rowx = (j >= 0) & (j <= NY) & (mur_y | ((j != 0) & (j != NY)));
-    const bool rowy = (j >= 0) & (j < NY);
-    rx[r] = (rowx & colx) ? base_rcp(kx[r]) : 0.f;
-    ry[r] = (rowy & coly) ? base_rcp(ky[r]) : 0.f;
+    rx[r] = base_rcp(kx[r]);
+    ry[r] = base_rcp(ky[r]);
   }
 
   // window of the wave's node row r, Ey of the row below it
@@ -108,6 +115,14 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
 
   for (int s = 0; s < t; s++) {
     const int b = (s & 1) * nw;
+    // (a mask of its own for every row, kept over the steps, spilled)
+    int rw = 0;
+    if (YE) asm volatile("s_mov_b32 %0, %1" : "=s"(rw) : "s"(rows));
+    auto keep = [&](float v, bool col, int bit) {
+      int q = __builtin_bit_cast(int, v);
+      if (YE) q &= (rw << (31 - bit)) >> 31;
+      return XE && !col ? 0.f : __builtin_bit_cast(float, q);
+    };
     publish(s & 1);
     __syncthreads();
     if (s == t - 1 && hzp) {  // Hz entering the last step
@@ -146,7 +161,8 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
     float en[R];
 #pragma unroll
     for (int r = 0; r < R; r++)
-      en[r] = base_ex(ex[r], kx[r], S, hz[r], r > 0 ? hz[r > 0 ? r - 1 : 0] : hm, c1, jx[r], rx[r]);
+      en[r] = keep(base_ex(ex[r], kx[r], S, hz[r], r > 0 ? hz[r > 0 ? r - 1 : 0] : hm, c1, jx[r], rx[r]),
+                   colx, r);
     if (YE && mur_y) {
 #pragma unroll
       for (int r = 0; r + 1 < R; r++) {
@@ -166,7 +182,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
       float curl = -S * (hz[r] - lane_left(hz[r]));
       if (XE && src) curl += add_e;
       const float eyo = ey[r];
-      en[r] = base_ey(eyo, ky[r], curl, c1, jy[r], ry[r]);
+      en[r] = keep(base_ey(eyo, ky[r], curl, c1, jy[r], ry[r]), coly, 16 + r);
       if (XE && mur0) {
         const float m = lane_right(eyo) + cm * (lane_right(en[r]) - eyo);
         en[r] = c0 ? m : en[r];

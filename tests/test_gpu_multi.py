@@ -281,3 +281,46 @@ def test_continuity_rows_of_a_plain_run_and_a_batch(nx, ny):
             assert np.array_equal(s.get(f, lv), b.instances[0].get(f, lv)), f
     s.close()
     b.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny,bc_x,bc_y", [(97, 70, "pec", "pec"), (97, 70, "mur", "mur"),
+                                             (64, 48, "pec", "mur"), (47, 33, "mur", "pec")])
+@pytest.mark.parametrize("multi", ["8", "5,6"])
+def test_walls_of_several_steps_bit_by_bit(nx, ny, bc_x, bc_y, multi, monkeypatch):
+    """Every bit of every field and of the saved state, the sign of zeros on
+    the walls among them, and with infinite values beside the walls, against
+    one launch a step: walls stay +0, nothing outside the grid reaches it."""
+    cfg = W.make(nx, ny, 16, "uniform", 1, bc_x=bc_x, bc_y=bc_y, tfsf_i=4)
+    g = np.random.Generator(np.random.PCG64(nx + ny))
+    base = 10.0 ** g.uniform(17, 20, (ny + 1, nx + 1))
+    E = 4e6
+    fields = dict(hz=E / 377 * g.uniform(-1, 1, (ny, nx)), ex=E * g.uniform(-1, 1, (ny + 1, nx)),
+                  ey=E * g.uniform(-1, 1, (ny, nx + 1)))
+    for infinite in (False, True):
+        if infinite:
+            for j, i in ((0, 20), (ny - 1, 30), (20, 0), (25, nx - 1), (0, 0), (ny - 1, nx - 1)):
+                fields["hz"][j, i] = np.inf
+        runs = []
+        for env in (multi, "1"):
+            monkeypatch.setenv("DMR_MULTI", env)
+            s = B.Sim(cfg, base, None)
+            for f, v in fields.items():
+                s.set(f, 0, v)
+            got = []
+            for n in (3, 8, 30):
+                s.step(n)
+                got.append({f: s.get(f, 0) for f in FIELDS})
+            runs.append((got, s.save(np.zeros(s.state_bytes(), np.uint8))))
+            s.close()
+        (a, sa), (b, sb) = runs
+        for x, y in zip(a, b):
+            for f in FIELDS:
+                nan = np.isnan(x[f])
+                assert np.array_equal(nan, np.isnan(y[f])), (f, infinite)
+                assert np.array_equal(x[f].view(np.uint32)[~nan], y[f].view(np.uint32)[~nan]), f
+        if not infinite:
+            assert np.array_equal(sa, sb)
+        nan = np.isnan(sa[256:].view(np.float32))
+        assert np.array_equal(nan, np.isnan(sb[256:].view(np.float32)))
+        assert np.array_equal(sa[256:].view(np.uint32)[~nan], sb[256:].view(np.uint32)[~nan])
