@@ -2874,10 +2874,10 @@ int dmr_load(dmr_sim* s, const void* src, size_t bytes, int src_on_device) {
     if (int rc = state_host_copy(s, body, false)) return rc;
   }
   if (!s->uni) return DMR_OK;
+  if (memcmp(s->h_act.data(), act.data(), act.size()) != 0) s->ugen++;
   memcpy(s->h_act.data(), act.data(), act.size());
-  s->near_gen = -1;
   if (int rc = union_install(s)) return rc;
-  return split_grid(s) ? near_blocks(s) : DMR_OK;
+  return split_grid(s) && s->near_gen != s->ugen ? near_blocks(s) : DMR_OK;
 }
 
 int dmr_weighted_sum(dmr_sim* s, int level, const float* d_w, double* out) {
@@ -2988,7 +2988,11 @@ struct dmr_batch {
   bool recorded = false;  // by the caller: no groups from then on (see dmr_sim)
   hipGraphExec_t gexec = nullptr;
   bool graph_ok = false;
-  int graph_gp = 0;  // gp it was captured at
+  int graph_key[3] = {0, 0, 0};  // gp, ccur, ncur it was captured at
+  // what the tables were built for, per instance: a load (or an addition of
+  // blocks) through its handle may change it between two batch steps
+  struct Built { int has, ext[4]; int64_t ugen; };
+  std::vector<Built> built;
   // host copies of the tables (kept alive until their upload completes)
   std::vector<EMArgs> h_em, h_fem;
   std::vector<ContArgs> h_cont, h_fcont;
@@ -3382,7 +3386,32 @@ int batch_tables(dmr_batch* b) {
       hipStreamSynchronize(b->st))
     return bfail(b, DMR_EHIP, "batch table upload failed");
   b->graph_ok = false;
+  b->built.clear();
+  for (const dmr_sim* s : b->sims)
+    b->built.push_back({s->has_patch, {s->ext[0], s->ext[1], s->ext[2], s->ext[3]}, s->ugen});
   return DMR_OK;
+}
+
+// Tables and places of the planes after what may have been done to single
+// instances since the last batch step: a load or an addition of blocks changes
+// the level the tables describe, and a load the step, whose parity the base
+// level's current planes are to have (groups, and a replayed interval, start
+// at parity 0).  Not the planes of a batch whose steps the caller records.
+int batch_refresh(dmr_batch* b) {
+  bool stale = false;
+  for (int k = 0; k < b->count; k++) {
+    dmr_sim* s = b->sims[k];
+    const dmr_batch::Built& q = b->built[k];
+    stale = stale || q.has != (int)s->has_patch || q.ugen != s->ugen ||
+            (s->has_patch && memcmp(q.ext, s->ext, sizeof(q.ext)) != 0);
+    if (b->recorded || s->ccur == (int)(s->step & 1)) continue;
+    Level& C = s->L0;
+    std::swap(C.hz[0], C.hz[1]); std::swap(C.ex[0], C.ex[1]); std::swap(C.ey[0], C.ey[1]);
+    std::swap(C.jx[0], C.jx[1]); std::swap(C.jy[0], C.jy[1]);
+    s->ccur = 1 - s->ccur;
+    stale = true;
+  }
+  return stale ? batch_tables(b) : DMR_OK;
 }
 
 // incident values of steps [base, base + kSrcSteps) for every instance
@@ -3655,13 +3684,14 @@ int batch_tune(dmr_batch* b, int64_t* used) {
         // to the next group (the candidates above stop anywhere); the faster
         // of two, since a kernel's first launch may wait for its set-up
         for (int rep = 0; rep < 2 && !rc; rep++) {
-          while (!rc && !batch_at_group(b, b->tg)) {
+          for (int q = 0; q < 2 * b->sims[0]->L0.spb && !rc && !batch_at_group(b, b->tg); q++) {
             if (b->sims[0]->step - b->src_base >= kSrcSteps) rc = batch_sources(b, b->sims[0]->step);
             if (!rc) rc = batch_launch_step(b, nullptr, nullptr);
             if (!rc) (*used)++;
           }
           if (!rc && b->sims[0]->step - b->src_base >= kSrcSteps)
             rc = batch_sources(b, b->sims[0]->step);
+          if (!rc && !batch_at_group(b, b->tg)) break;
           (void)hipEventRecord(tb[0], b->st);
           if (!rc) rc = batch_launch_group(b, true);
           if (!rc) *used += b->tg;
@@ -3736,8 +3766,9 @@ int batch_step(dmr_batch* b, int64_t n) {
     const bool whole = step % kSrcSteps == 0 && chunk == kSrcSteps &&
                        (!dyn || p.regrid_every % kSrcSteps == 0);
     if (b->use_graph && whole && steady) {
-      if (!b->graph_ok || b->graph_gp != b->gp) {
-        b->graph_gp = b->gp;
+      const int key[3] = {b->gp, s0->ccur, s0->ncur};
+      if (!b->graph_ok || memcmp(key, b->graph_key, sizeof(key)) != 0) {
+        memcpy(b->graph_key, key, sizeof(key));
         if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
         b->gexec = nullptr;
         hipGraph_t g = nullptr;
@@ -3886,7 +3917,8 @@ int dmr_batch_step(dmr_batch* b, int64_t n) {
     b->recorded = true;
     b->graph_ok = false;  // the interval's graph holds groups
   }
-  const int rc = batch_step(b, n);
+  int rc = n > 0 ? batch_refresh(b) : DMR_OK;
+  if (!rc) rc = batch_step(b, n);
   (void)hipEventRecord(b->ev_out, b->st);
   (void)hipStreamWaitEvent(b->user, b->ev_out, 0);
   return rc;
