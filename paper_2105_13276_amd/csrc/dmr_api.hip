@@ -3753,9 +3753,9 @@ int batch_step(dmr_batch* b, int64_t n) {
     if (b->src_base != base) rc = batch_sources(b, base);
     if (rc) return rc;
     if (!b->tuned && !b->forced && step % kSrcSteps == 0 && n >= kSrcSteps &&
-        (!dyn || p.regrid_every >= kSrcSteps)) {
+        (!dyn || p.regrid_every - step % p.regrid_every >= kSrcSteps)) {
       int64_t used = 0;
-      rc = batch_tune(b, &used);  // times real steps of the run
+      rc = batch_tune(b, &used);  // times real steps of the run (no growth test among them)
       if (rc) return rc;
       n -= used;
       continue;

@@ -1,0 +1,42 @@
+"""A batch against plain runs where its own cadences (256-step intervals, the
+steps it tunes on) and those of the run (growth tests, window blocks) do not
+fall together."""
+import numpy as np
+import pytest
+
+from paper_2105_13276_amd import binding as B
+from paper_2105_13276_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("hz", "ex", "ey", "jx", "jy", "n", "acc", "ring")
+
+
+def _same(h, s):
+    for lv in (0, 1) if s.cfg["mode"] != "uniform" else (0,):
+        for f in FIELDS:
+            assert np.array_equal(h.get(f, lv), s.get(f, lv)), (f, lv)
+
+
+def test_tuning_steps_over_no_growth_test():
+    """First steps in calls too short to tune on; then a long call 32 steps
+    before a growth test that grows the patch."""
+    cfgs, seeds = [], []
+    for side in (256, 384):
+        cfg = W.make(side, side // 2, 32, "dynamic", 1, erms_over_ebd=4.0, regrid_every=800)
+        dx = W.C0 / 110e9 / 32
+        cfgs.append(cfg)
+        seeds.append(W.seeds(cfg, [((side // 2 + 11.5) * dx, side // 4 * dx)], [3e17]))
+    b = B.Batch(cfgs, seeds)
+    plain = [B.Sim(c, *s) for c, s in zip(cfgs, seeds)]
+    old = [s.patch() for s in plain]
+    for n in (200, 200, 200, 168, 512, 300):
+        b.step(n)
+        b.sync()
+        for h, s in zip(b.instances, plain):
+            s.step(n)
+            assert h.patch() == s.patch()
+    assert any(s.patch() != o for s, o in zip(plain, old))
+    for h, s in zip(b.instances, plain):
+        _same(h, s)
+    b.close()
