@@ -360,7 +360,8 @@ int dmr_weighted_sum_static(dmr_sim *s, int level, const float *d_w, double *out
  * differ; steps per period, mode, continuity switch and regrid cadence must
  * agree) advanced in lockstep: each per-step kernel is one launch over the
  * tiles of all instances, the steps of every steady 256-step interval are
- * replayed from one captured HIP graph, and the streaming segment length,
+ * replayed from one captured HIP graph (where 256 steps hold whole periods, or
+ * without continuity), and the streaming segment length,
  * load depth, fine tile height and subcycle schedule are chosen by timing
  * real steps (all choices give bit-identical results; choices are cached
  * per size key).

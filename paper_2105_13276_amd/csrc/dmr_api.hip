@@ -3763,7 +3763,10 @@ int batch_step(dmr_batch* b, int64_t n) {
     int64_t chunk = std::min<int64_t>(n, base + kSrcSteps - step);
     if (dyn) chunk = std::min<int64_t>(chunk, p.regrid_every - step % p.regrid_every);
     const bool steady = s0->blocks >= kRing || !p.continuity_on;
+    // (a recorded interval holds the window blocks' places and ring slots, which
+    // come back every period)
     const bool whole = step % kSrcSteps == 0 && chunk == kSrcSteps &&
+                       (!p.continuity_on || kSrcSteps % s0->L0.spp == 0) &&
                        (!dyn || p.regrid_every % kSrcSteps == 0);
     if (b->use_graph && whole && steady) {
       const int key[3] = {b->gp, s0->ccur, s0->ncur};

@@ -40,3 +40,23 @@ def test_tuning_steps_over_no_growth_test():
     for h, s in zip(b.instances, plain):
         _same(h, s)
     b.close()
+
+
+@pytest.mark.parametrize("mode", ["uniform", "static"])
+@pytest.mark.parametrize("cpl", [36, 128, 256])
+def test_interval_that_holds_no_whole_periods(mode, cpl):
+    """Window blocks of 9, 32 and 64 steps: 256 steps hold no whole number of
+    them, one period, or half of one."""
+    cfgs = [W.make(nx, 96, cpl, mode, 1, erms_over_ebd=2.0, tfsf_i=9,
+                   static_ext=(nx // 2 - 8, 40, nx // 2 + 9, 57)) for nx in (96, 160)]
+    g = np.random.Generator(np.random.PCG64(cpl))
+    seeds = [(10.0 ** g.uniform(17, 20, (97, c["nx"] + 1)), None) for c in cfgs]
+    b = B.Batch(cfgs, seeds)
+    plain = [B.Sim(c, *s) for c, s in zip(cfgs, seeds)]
+    for n in (1024, 256, 512):
+        b.step(n)
+        b.sync()
+        for h, s in zip(b.instances, plain):
+            s.step(n)
+            _same(h, s)
+    b.close()
