@@ -161,7 +161,11 @@ typedef struct dmr_sim dmr_sim;
 int dmr_derived(const dmr_params *p, double *out, int n_out);
 
 /* Bytes of device workspace the problem needs, sized for a patch covering
- * the whole domain so that growth never reallocates.  EINVAL on bad params. */
+ * the whole domain so that growth never reallocates.  It holds planes that
+ * only take several steps a launch (a third Hz plane, a table of incident
+ * values, on large refined grids a third set of base-level planes); dmr_create
+ * takes a workspace without some or all of them and does without those forms
+ * (the same for dmr_batch_workspace_bytes).  EINVAL on bad params. */
 int dmr_workspace_bytes(const dmr_params *p, size_t *bytes);
 
 /* Create a simulation at t = 0: fields and current zero, density from the

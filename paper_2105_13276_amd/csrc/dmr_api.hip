@@ -89,7 +89,12 @@ struct Layout {
   size_t plane0 = 0, plane1 = 0;
   int pitch0 = 0, pitch1 = 0;
   size_t off_l1 = 0, off_flag = 0, off_scan = 0, off_list = 0, off_desc = 0,
-         off_err = 0, off_stage = 0, stage_bytes = 0, off_hzp = 0, off_far = 0, off_src = 0, total = 0;
+         off_err = 0, off_stage = 0, stage_bytes = 0, off_hzp = 0, off_far = 0, off_src = 0;
+  // what a run cannot do without; with the planes and tables of several steps a
+  // launch and recorded periods, and where the grid can split its steps with
+  // the third set of planes (what dmr_workspace_bytes reports); with that set
+  // in any case (a batch splits smaller grids too)
+  size_t need = 0, total = 0, full = 0;
   int NB = 0;
   // union-of-blocks fine level: two block maps, two tile lists (64 x 4 tiles
   // at most over the fine domain)
@@ -108,6 +113,19 @@ bool refined(const dmr_params* p) { return p->mode != DMR_UNIFORM; }
 constexpr int kNearSeg = 2;
 
 int stream_blocks_x(int NX) { return ((NX + 1 + 61) / 62 + kThreads / 64 - 1) / (kThreads / 64); }
+
+// Cells from which the steps of a refined run are split (split_steps): where
+// the base level is what a step waits for; on smaller grids the patch's chain
+// is, and the far launch only adds to it.  Per step, one launch a step against
+// split: patch r = 2: 512x256 7.6 / 8.6 us, 704x352 9.8 / 9.5, 1024x512 11.0 /
+// 10.2, 4096x2048 123 / 47; union of blocks: 704x352 22.6 / 23.3, 1024x512
+// 24.4 / 24.0, 4096x2048 137 / 67; r = 4: 1024x512 18.8 / 19.3, 1440x720 23.6 /
+// 21.3.  DMR_SPLIT_MIN=cells in its place.
+long split_least(const dmr_params* p) {
+  if (const char* f = getenv("DMR_SPLIT_MIN"))
+    if (atol(f) >= 0) return atol(f);
+  return p->r == 4 ? 1L << 20 : p->regrid_rule == DMR_RULE_UNION ? 1L << 19 : 1L << 18;
+}
 
 Layout layout_of(const dmr_params* p) {
   Layout L;
@@ -129,21 +147,27 @@ Layout layout_of(const dmr_params* p) {
   L.off_err = off;   off += 256;
   L.stage_bytes = align256(stage * sizeof(float));
   L.off_stage = off; off += L.stage_bytes;
-  L.off_hzp = off;   off += align256(L.plane0 * sizeof(float));
-  L.off_src = off;   off += align256(kSrcSteps * sizeof(float2));
-  L.off_far = off;
-  if (refined(p)) off += align256(6 * L.plane0 * sizeof(float));
-  if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
+  const bool uni = refined(p) && p->regrid_rule == DMR_RULE_UNION;
+  if (uni) {
     L.max_tiles = (size_t)((p->r * p->nx + 1 + kTX - 1) / kTX) * ((p->r * p->ny + 1 + 3) / 4);
     L.off_act = off;   off += 2 * align256(nb);
     L.off_tiles = off; off += 2 * align256(L.max_tiles * sizeof(int2));
     L.off_cfb = off;   off += align256(L.max_tiles * kCfbStride * sizeof(float));
+  }
+  L.need = off;
+  L.off_src = off;   off += align256(kSrcSteps * sizeof(float2));
+  L.off_hzp = off;   off += align256(L.plane0 * sizeof(float));
+  L.total = off;
+  L.off_far = off;
+  if (refined(p)) off += align256(6 * L.plane0 * sizeof(float));
+  if (uni) {
     L.max_nblk = (size_t)((p->nx + 1 + 61) / 62) *
                  ((stream_segments(p->ny, kNearSeg) + kThreads / 64 - 1) / (kThreads / 64));
     L.off_near = off;  off += align256(nb);
     L.off_nblk = off;  off += align256(L.max_nblk * sizeof(int2));
   }
-  L.total = off;
+  L.full = off;
+  if (refined(p) && (long)p->nx * p->ny >= split_least(p)) L.total = L.full;
   return L;
 }
 
@@ -300,7 +324,7 @@ struct dmr_sim {
   // refined runs: a third set of the base level's planes (Hz, Ex, Ey, Jx, Jy,
   // window) for the split groups, and the grids they are used on
   float* far[6] = {};
-  long split_min = -1;  // DMR_SPLIT_MIN (cells; -1: by kind)
+  long split_min = 0;  // cells (split_least)
   // union-of-blocks level: the blocks around it (host, device) and the
   // base-level streaming blocks that cover them
   std::vector<uint8_t> h_near;
@@ -868,7 +892,7 @@ void em_args_level(EMArgs* A, const Level& L, int src, int dst, const float* n,
   A->jx0 = L.jx[src]; A->jy0 = L.jy[src];
   A->hz1 = L.hz[dst]; A->ex1 = L.ex[dst]; A->ey1 = L.ey[dst];
   A->jx1 = L.jx[dst]; A->jy1 = L.jy[dst];
-  A->n = n; A->acc = acc; A->acc1 = acc;
+  A->n = n; A->acc = acc;
   A->pitch = L.pitch;
   A->S = L.S; A->c1 = L.c1; A->a = L.a; A->kn = L.kn; A->cmur = L.cmur;
 }
@@ -880,6 +904,7 @@ void make_base_em(const dmr_sim* s, int c, int nc, EMArgs* A) {
   const dmr_params& p = s->p;
   *A = EMArgs{};
   em_args_level(A, C, c, 1 - c, C.n[nc], C.acc);
+  A->acc1 = C.acc;
   A->L = 0; A->B = 0; A->R = p.nx; A->T = p.ny;
   A->bc_x = p.bc_x; A->bc_y = p.bc_y;
   A->is = p.tfsf_i;
@@ -1427,18 +1452,7 @@ int near_blocks(dmr_sim* s) {
 
 // Whether the grid is one whose steps may be split (split_steps)
 bool split_grid(const dmr_sim* s) {
-  const dmr_params& p = s->p;
-  // Where the base level is what a step waits for; on smaller grids the patch's
-  // chain is, and the far launch only adds to it.  Per step, one launch a step
-  // against split: patch r = 2: 512x256 7.6 / 8.6 us, 704x352 9.8 / 9.5,
-  // 1024x512 11.0 / 10.2, 4096x2048 123 / 47; union of blocks: 704x352 22.6 /
-  // 23.3, 1024x512 24.4 / 24.0, 4096x2048 137 / 67; r = 4: 1024x512 18.8 /
-  // 19.3, 1440x720 23.6 / 21.3.
-  const long least = s->split_min >= 0 ? s->split_min
-                     : p.r == 4       ? 1L << 20
-                     : s->uni         ? 1L << 19
-                                      : 1L << 18;
-  return s->multi_t >= 2 && (long)p.nx * p.ny >= least;
+  return s->far[0] && s->multi_t >= 2 && (long)s->p.nx * s->p.ny >= s->split_min;
 }
 
 // whether t steps of a run with a fine level are split
@@ -1717,7 +1731,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     return rc;
   }
   const Layout lay = layout_of(p);
-  if (!d_workspace || bytes < lay.total) return DMR_ENOMEM;
+  if (!d_workspace || bytes < lay.need) return DMR_ENOMEM;
   dmr_sim* s = new (std::nothrow) dmr_sim();
   if (!s) return DMR_ENOMEM;
   s->p = *p;
@@ -1746,9 +1760,14 @@ int dmr_create(const dmr_params* p, const double* seed_base,
   s->d_desc = (int*)(s->ws + lay.off_desc);
   s->d_err = (int*)(s->ws + lay.off_err);
   s->stage = (float*)(s->ws + lay.off_stage);
-  s->hzp = (float*)(s->ws + lay.off_hzp);
-  s->d_src = (float2*)(s->ws + lay.off_src);
-  if (refined(p))
+  // a workspace below the reported size does without what does not fit
+  const size_t used = bytes >= lay.full ? lay.full : bytes >= lay.off_far ? lay.off_far : lay.need;
+  if (used >= lay.off_far) {
+    s->d_src = (float2*)(s->ws + lay.off_src);
+    s->hzp = (float*)(s->ws + lay.off_hzp);
+  }
+  const bool far = refined(p) && used == lay.full;
+  if (far)
     for (int q = 0; q < 6; q++) s->far[q] = (float*)(s->ws + lay.off_far) + q * lay.plane0;
   if (refined(p) && p->regrid_rule == DMR_RULE_UNION) {
     s->uni = true;
@@ -1758,8 +1777,8 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     s->d_tiles = (int2*)(s->ws + lay.off_tiles);
     s->d_ptiles = s->d_tiles + align256(lay.max_tiles * sizeof(int2)) / sizeof(int2);
     s->d_cfb = (float*)(s->ws + lay.off_cfb);
-    s->d_near = (uint8_t*)(s->ws + lay.off_near);
-    s->d_nblk = (int2*)(s->ws + lay.off_nblk);
+    s->d_near = far ? (uint8_t*)(s->ws + lay.off_near) : nullptr;
+    s->d_nblk = far ? (int2*)(s->ws + lay.off_nblk) : nullptr;
     s->h_act.assign(nb, 0);
     if (const char* f = getenv("DMR_UTY")) {
       const int v = atoi(f);
@@ -1785,15 +1804,16 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     s->multi_t = std::min(std::max(s->multi_t, 1), kMultiSteps);
     s->multi_w = s->multi_w < 5 ? 0 : std::min(s->multi_w, 16);
   }
-  if (const char* f = getenv("DMR_SPLIT_MIN")) s->split_min = atol(f);
+  s->split_min = split_least(p);
   if (const char* f = getenv("DMR_PERIOD")) s->pg_on = atoi(f) != 0;
+  if (!s->d_src) s->pg_on = false;
   if (const char* f = getenv("DMR_CONT_MERGE")) s->cont_merge = atoi(f) != 0 ? 1 : 0;
   if (const char* f = getenv("DMR_FINE_REG"))
     (void)sscanf(f, "%ld,%d", &s->reg_min, &s->reg_waves);
   if (const char* f = getenv("DMR_FINE_SEG")) s->fseg = atoi(f) >= 2 ? atoi(f) : 0;
   if (const char* f = getenv("DMR_FINE_DEPTH")) s->fdepth = atoi(f) >= 4 ? 4 : 2;
   s->depth0 = stream_depth(s->seg0);
-  hipError_t e = hipMemsetAsync(s->ws, 0, lay.total, s->st);
+  hipError_t e = hipMemsetAsync(s->ws, 0, used, s->st);
   if (e != hipSuccess) { rc = hipfail(s, e, "workspace clear"); delete s; return rc; }
   // seeds: float32 on the pitched node grid
   std::vector<float> h;
@@ -1900,7 +1920,7 @@ int dmr_step(dmr_sim* s, int64_t n) {
       t = (int)((left + parts - 1) / parts);
     }
     const bool split = can_split(s, t);
-    if (s->has_patch && !split) t = 1;
+    if (!split && (s->has_patch || !s->hzp)) t = 1;
     const bool last = t == n || (s->p.mode == DMR_DYNAMIC && (s->step + t) % s->p.regrid_every == 0);
     const int rc = split ? split_steps(s, t, last) : t > 1 ? multi_steps(s, t, last) : base_step(s);
     if (rc) { ev_close(s); return rc; }
@@ -2971,6 +2991,7 @@ struct dmr_batch {
   // table is built for both.  Steps of a group: phase 0 the first, 1 the odd
   // ones, 2 the others (which planes they read and write).
   int tg = 0, gp = 0, far_waves = 12;
+  int sets = 2;  // of the tables (1: a workspace without room for groups)
   EMArgs* d_nem = nullptr;    // [2 gp][2 density][3 phases][count] base level, near
   EMArgs* d_nfem = nullptr;   // [2][2][3][rf][count] patch, one launch a substep
   EMArgs* d_nfem2 = nullptr;  // [2][2][3][2][count] patch, two substeps a launch
@@ -3016,7 +3037,8 @@ struct BatchLayout {
   size_t cap_base = 0, cap_fine = 0, cap_cont = 0, cap_fcont = 0, cap_comb = 0;
 };
 
-int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* why) {
+// lean: without what the split groups need (one set of argument tables)
+int batch_layout(const dmr_params* p, int count, bool lean, BatchLayout* L, std::string* why) {
   if (!p || count < 1) { *why = "count must be >= 1"; return DMR_EINVAL; }
   size_t off = 0;
   for (int k = count - 1; k >= 0; k--)
@@ -3044,7 +3066,8 @@ int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* wh
       *why = "instances must share steps per period, mode, continuity and regrid cadence";
       return DMR_EINVAL;
     }
-    const size_t b = layout_of(&p[k]).total;
+    const Layout one = layout_of(&p[k]);
+    const size_t b = lean ? one.need : one.full;
     L->off.push_back(off);
     L->size.push_back(b);
     off += align256(b);
@@ -3061,10 +3084,11 @@ int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* wh
     L->cap_far += (size_t)((nx + 1 + 47) / 48) * ((ny + 1 + 15) / 16);
   }
   // (two of each argument table: see dmr_batch::gp)
-  L->off_em = off;    off += align256(sizeof(EMArgs) * 2 * 4 * count);
-  L->off_fem = off;   off += align256(sizeof(EMArgs) * 2 * 4 * L->rf * count);
-  L->off_cont = off;  off += align256(sizeof(ContArgs) * 2 * 2 * count);
-  L->off_fcont = off; off += align256(sizeof(ContArgs) * 2 * 2 * count);
+  const size_t sets = lean ? 1 : 2;
+  L->off_em = off;    off += align256(sizeof(EMArgs) * sets * 4 * count);
+  L->off_fem = off;   off += align256(sizeof(EMArgs) * sets * 4 * L->rf * count);
+  L->off_cont = off;  off += align256(sizeof(ContArgs) * sets * 2 * count);
+  L->off_fcont = off; off += align256(sizeof(ContArgs) * sets * 2 * count);
   L->off_blk_base = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_base, 1));
   L->off_blk_fine = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_fine, 1));
   L->off_blk_cont = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_cont, 1));
@@ -3072,17 +3096,19 @@ int batch_layout(const dmr_params* p, int count, BatchLayout* L, std::string* wh
   L->off_src = off;       off += align256(sizeof(float2) * kSrcSteps * count);
   // the two-substep and combined schedules: their argument tables, and the
   // combined table (groups of 16 base waves <= 4-wave blocks, plus the tiles)
-  L->off_fem2 = off;      off += align256(sizeof(EMArgs) * 2 * 4 * 2 * count);
-  L->off_cem = off;       off += align256(sizeof(EMArgs) * 2 * 4 * count);
-  L->off_floc = off;      off += align256(sizeof(EMArgs) * 2 * 4 * count);
+  L->off_fem2 = off;      off += align256(sizeof(EMArgs) * sets * 4 * 2 * count);
+  L->off_cem = off;       off += align256(sizeof(EMArgs) * sets * 4 * count);
+  L->off_floc = off;      off += align256(sizeof(EMArgs) * sets * 4 * count);
   // split groups
-  L->off_nem = off;       off += align256(sizeof(EMArgs) * 2 * 2 * 3 * count);
-  L->off_nfem = off;      off += align256(sizeof(EMArgs) * 2 * 2 * 3 * L->rf * count);
-  L->off_nfem2 = off;     off += align256(sizeof(EMArgs) * 2 * 2 * 3 * 2 * count);
-  L->off_multi = off;     off += align256(sizeof(MultiArgs) * 2 * 2 * count);
-  L->off_blk_near = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_base, 1));
-  L->off_blk_far = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_far, 1));
-  L->off_blk_reg = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_fine, 1));
+  if (!lean) {
+    L->off_nem = off;       off += align256(sizeof(EMArgs) * 2 * 2 * 3 * count);
+    L->off_nfem = off;      off += align256(sizeof(EMArgs) * 2 * 2 * 3 * L->rf * count);
+    L->off_nfem2 = off;     off += align256(sizeof(EMArgs) * 2 * 2 * 3 * 2 * count);
+    L->off_multi = off;     off += align256(sizeof(MultiArgs) * 2 * 2 * count);
+    L->off_blk_near = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_base, 1));
+    L->off_blk_far = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_far, 1));
+    L->off_blk_reg = off;   off += align256(sizeof(int2) * std::max<size_t>(L->cap_fine, 1));
+  }
   L->cap_comb = L->cap_base + L->cap_fine;
   L->off_blk_comb = off;  off += align256(sizeof(int2) * std::max<size_t>(L->cap_comb, 1));
   L->total = off;
@@ -3102,7 +3128,7 @@ int bfail(dmr_batch* b, int code, const char* what) {
 int batch_group(const dmr_batch* b) {
   const dmr_sim* s0 = b->sims[0];
   const int spb = s0->L0.spb;
-  if (b->forced || !refined(&s0->p) || s0->multi_t < 2) return 0;
+  if (b->forced || b->sets < 2 || !refined(&s0->p) || s0->multi_t < 2) return 0;
   const int t = std::min(s0->multi_t, spb) & ~1;
   if (t < 2 || spb % 2 || kSrcSteps % spb || (kSrcSteps / spb) * (spb / t) % 2) return 0;
   if (4 * b->far_waves - 2 * t < 16) return 0;  // (the table's capacity)
@@ -3267,13 +3293,13 @@ void batch_args(dmr_batch* b, int k, int g) {
 int batch_tables(dmr_batch* b) {
   const int n = b->count;
   b->gp = 0;
-  b->h_em.assign(2 * 4 * n, EMArgs{});
-  b->h_fem.assign(2 * 4 * b->rf * n, EMArgs{});
-  b->h_cont.assign(2 * 2 * n, ContArgs{});
-  b->h_fcont.assign(2 * 2 * n, ContArgs{});
-  b->h_fem2.assign(2 * 4 * 2 * n, EMArgs{});
-  b->h_cem.assign(2 * 4 * n, EMArgs{});
-  b->h_floc.assign(2 * 4 * n, EMArgs{});
+  b->h_em.assign(b->sets * 4 * n, EMArgs{});
+  b->h_fem.assign(b->sets * 4 * b->rf * n, EMArgs{});
+  b->h_cont.assign(b->sets * 2 * n, ContArgs{});
+  b->h_fcont.assign(b->sets * 2 * n, ContArgs{});
+  b->h_fem2.assign(b->sets * 4 * 2 * n, EMArgs{});
+  b->h_cem.assign(b->sets * 4 * n, EMArgs{});
+  b->h_floc.assign(b->sets * 4 * n, EMArgs{});
   b->h_nem.assign(2 * 2 * 3 * n, EMArgs{});
   b->h_nfem.assign(2 * 2 * 3 * b->rf * n, EMArgs{});
   b->h_nfem2.assign(2 * 2 * 3 * 2 * n, EMArgs{});
@@ -3307,9 +3333,9 @@ int batch_tables(dmr_batch* b) {
     }
     if (b->tg && s->uni && s->has_patch && s->near_gen != s->ugen)
       if (int rc = near_blocks(s)) return bfail(b, rc, s->err.c_str());
-    for (int g = 0; g < 2; g++) {
+    for (int g = 0; g < b->sets; g++) {
       batch_args(b, k, g);
-      if (refined(&s->p)) swap_far(s);  // (twice: back as it was)
+      if (b->sets == 2 && refined(&s->p)) swap_far(s);  // (twice: back as it was)
     }
     const EMArgs& A = b->h_em[k];
     for (int t = 0; t < A.nbx * A.nseg; t++) b->h_blk_base.push_back(make_int2(k, t));
@@ -3818,7 +3844,7 @@ extern "C" {
 int dmr_batch_workspace_bytes(const dmr_params* p, int count, size_t* bytes) {
   BatchLayout L;
   std::string why;
-  const int rc = batch_layout(p, count, &L, &why);
+  const int rc = batch_layout(p, count, false, &L, &why);
   if (rc) return rc;
   if (!bytes) return DMR_EINVAL;
   *bytes = L.total;
@@ -3832,15 +3858,22 @@ int dmr_batch_create(const dmr_params* p, int count, const double* const* seed_b
   *out = nullptr;
   BatchLayout L;
   std::string why;
-  int rc = batch_layout(p, count, &L, &why);
+  int rc = batch_layout(p, count, false, &L, &why);
   if (rc) {
     fprintf(stderr, "dmr_batch_create: %s\n", why.c_str());
     return rc;
+  }
+  const bool lean = bytes < L.total;
+  if (lean) {  // without room for split groups: one launch a step and level
+    L = BatchLayout();
+    rc = batch_layout(p, count, true, &L, &why);
+    if (rc) return rc;
   }
   if (!d_workspace || bytes < L.total) return DMR_ENOMEM;
   dmr_batch* b = new (std::nothrow) dmr_batch();
   if (!b) return DMR_ENOMEM;
   b->count = count;
+  b->sets = lean ? 1 : 2;
   b->user = (hipStream_t)stream;
   b->ws = (char*)d_workspace;
   if (hipStreamCreateWithFlags(&b->st, hipStreamNonBlocking) != hipSuccess ||
