@@ -2991,6 +2991,7 @@ struct dmr_batch {
   // table is built for both.  Steps of a group: phase 0 the first, 1 the odd
   // ones, 2 the others (which planes they read and write).
   int tg = 0, gp = 0, far_waves = 12;
+  int split = -1;  // whether to (0, 1: as timed; -1: by size, split_least)
   int sets = 2;  // of the tables (1: a workspace without room for groups)
   EMArgs* d_nem = nullptr;    // [2 gp][2 density][3 phases][count] base level, near
   EMArgs* d_nfem = nullptr;   // [2][2][3][rf][count] patch, one launch a substep
@@ -3120,35 +3121,49 @@ int bfail(dmr_batch* b, int code, const char* what) {
   return code;
 }
 
-// Steps of a split group (0: the batch steps one launch a step).  A forced
-// launch configuration is taken as it is.  Even, so that a group ends in the
-// planes (and patch buffers) it started from but for the exchanged sets, and
-// the interval holds whole window blocks with an even number of groups, which
-// lets a captured interval be replayed.
-int batch_group(const dmr_batch* b) {
+// Steps of a split group the cadences allow (0: none).  A forced launch
+// configuration is taken as it is.  Even, so that a group ends in the planes
+// (and patch buffers) it started from but for the exchanged sets, and the
+// interval holds whole window blocks with an even number of groups, which lets a
+// captured interval be replayed.
+int group_steps(const dmr_batch* b) {
   const dmr_sim* s0 = b->sims[0];
   const int spb = s0->L0.spb;
-  if (b->forced || b->sets < 2 || !refined(&s0->p) || s0->multi_t < 2) return 0;
+  if (b->forced || b->recorded || b->sets < 2 || !refined(&s0->p) || s0->multi_t < 2) return 0;
   const int t = std::min(s0->multi_t, spb) & ~1;
   if (t < 2 || spb % 2 || kSrcSteps % spb || (kSrcSteps / spb) * (spb / t) % 2) return 0;
   if (4 * b->far_waves - 2 * t < 16) return 0;  // (the table's capacity)
-  // worth it where the fine levels' surroundings are a small part of the cells
+  return t;
+}
+
+// the same where the fine levels' surroundings are a small part of the cells
+int group_room(dmr_batch* b, int* tg) {
+  *tg = 0;
+  const int t = group_steps(b);
   double near = 0, all = 0;
-  for (const dmr_sim* s : b->sims) {
+  for (dmr_sim* s : b->sims) {
     const double cells = (s->p.nx + 1.0) * (s->p.ny + 1.0);
     all += cells;
-    if (!s->has_patch) continue;
-    if (s->uni && (s->p.block & (s->p.block - 1))) return 0;
+    if (!t || !s->has_patch) continue;
     if (s->uni) {
-      double act = 0;
-      for (uint8_t v : s->h_act) act += v;
-      near += std::min(cells, act * s->p.block * s->p.block * 25.0);
+      if (s->near_gen != s->ugen)
+        if (int rc = near_blocks(s)) return bfail(b, rc, s->err.c_str());
+      near += cells * s->near_share;
       continue;
     }
     const StreamWin w = near_window(s, t);
     near += std::min(cells, w.ncw * 62.0 * w.nk * kNearSeg);
   }
-  return near <= 0.5 * all ? t : 0;
+  if (t && near <= 0.5 * all) *tg = t;
+  return DMR_OK;
+}
+
+// whether the batch's grids together are of the size from which a plain run
+// splits its steps (what a batch does until it has timed both)
+bool split_by_size(const dmr_batch* b) {
+  long cells = 0;
+  for (const dmr_sim* s : b->sims) cells += (long)s->p.nx * s->p.ny;
+  return cells >= b->sims[0]->split_min;
 }
 
 // Rows per segment of the near launches of rectangles: the longest that leave
@@ -3317,7 +3332,9 @@ int batch_tables(dmr_batch* b) {
   b->can_combine = b->can_fuse && b->rf == 2;
   if ((b->sched == kSchedFused && !b->can_fuse) || (b->sched == kSchedCombined && !b->can_combine))
     b->sched = kSchedSeparate;
-  b->tg = batch_group(b);
+  b->tg = 0;
+  if (b->split < 0 ? split_by_size(b) : b->split > 0)
+    if (int rc = group_room(b, &b->tg)) return rc;
   std::vector<int> pw, ph, pk;  // patches: cells, instance
   b->h_blk_reg.clear();
   b->near_seg = batch_near_seg(b);
@@ -3331,8 +3348,6 @@ int batch_tables(dmr_batch* b) {
       s->tyu_env = true;
       if (int rc = union_install(s)) return bfail(b, rc, s->err.c_str());
     }
-    if (b->tg && s->uni && s->has_patch && s->near_gen != s->ugen)
-      if (int rc = near_blocks(s)) return bfail(b, rc, s->err.c_str());
     for (int g = 0; g < b->sets; g++) {
       batch_args(b, k, g);
       if (b->sets == 2 && refined(&s->p)) swap_far(s);  // (twice: back as it was)
@@ -3500,11 +3515,15 @@ void batch_advance_group(dmr_batch* b, int* slot, int* update) {
   b->gp ^= 1;
 }
 
-// whether the next steps, `left` of which are to be done, are a split group
-bool batch_at_group(const dmr_batch* b, int64_t left) {
+// whether a group of t steps may start here, with `left` steps to be done
+bool group_place(const dmr_batch* b, int t, int64_t left) {
   const dmr_sim* s = b->sims[0];
-  return b->tg && !b->recorded && s->ccur == 0 && left >= b->tg && s->step % s->L0.spb % b->tg == 0 &&
-         s->step % s->L0.spb + b->tg <= s->L0.spb;
+  return s->ccur == 0 && left >= t && s->step % s->L0.spb % t == 0 && s->step % s->L0.spb + t <= s->L0.spb;
+}
+
+// whether the next steps are a split group
+bool batch_at_group(const dmr_batch* b, int64_t left) {
+  return b->tg && !b->recorded && group_place(b, b->tg, left);
 }
 
 // window block / continuity of both levels, density buffers nc + 2 gp
@@ -3619,8 +3638,8 @@ int batch_regrid(dmr_batch* b) {
 
 // pick the streaming segment/depth and the fine tile height by timing real
 // steps (all candidates give bit-identical results)
-std::vector<std::pair<std::string, std::array<int, 4>>>& tune_cache() {
-  static std::vector<std::pair<std::string, std::array<int, 4>>> c;
+std::vector<std::pair<std::string, std::array<int, 5>>>& tune_cache() {
+  static std::vector<std::pair<std::string, std::array<int, 5>>> c;
   return c;
 }
 
@@ -3632,6 +3651,12 @@ std::string batch_key(const dmr_batch* b) {
              s->ext[2], s->ext[3]);
     k += buf;
   }
+  // (the level's kind, and whether groups are open to choice)
+  const dmr_sim* s0 = b->sims[0];
+  char buf[64];
+  snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d", b->rf, (int)s0->uni, group_steps(b),
+           getenv("DMR_SPLIT_MIN") ? 1 : 0, (int)split_by_size(b));
+  k += buf;
   return k;
 }
 
@@ -3642,6 +3667,7 @@ int batch_tune(dmr_batch* b, int64_t* used) {
     if (kv.first == key) {
       b->seg = kv.second[0]; b->depth = kv.second[1]; b->ty = kv.second[2];
       b->sched = kv.second[3];
+      b->split = kv.second[4];
       b->tuned = true;
       return batch_tables(b);
     }
@@ -3655,7 +3681,10 @@ int batch_tune(dmr_batch* b, int64_t* used) {
   const int nseg = sizeof(kSegCand) / sizeof(int), nty = sizeof(kTyCand) / sizeof(int);
   const int ncand = std::max(nseg, nty);
   int rc = DMR_OK;
+  // DMR_SPLIT_MIN decides about groups where it is set, the times where not
+  const int by_size = getenv("DMR_SPLIT_MIN") ? (int)split_by_size(b) : -1;
   b->sched = kSchedSeparate;
+  b->split = 0;
   for (int c = 0; c < ncand && !rc; c++) {
     b->seg = kSegCand[c % nseg];
     b->depth = stream_depth(b->seg);
@@ -3685,51 +3714,20 @@ int batch_tune(dmr_batch* b, int64_t* used) {
     b->sched = sched;
     b->ty = ty;
     int r = batch_tables(b);
-    *ms = 0.f;
+    *ms = 1e30f;
     for (int rep = 0; rep < 2 && !r; rep++) {
       if (b->sims[0]->step - b->src_base >= kSrcSteps) r = batch_sources(b, b->sims[0]->step);
       if (!r) r = batch_launch_step(b, tb, tf);
       if (!r) (*used)++;
       if (!r && hipStreamSynchronize(b->st) != hipSuccess) r = DMR_EHIP;
-      float x = 0.f;
+      float x = 1e30f;
       (void)hipEventElapsedTime(&x, tb[0], tf[1]);
-      *ms += x;
+      *ms = std::min(*ms, x);  // (a kernel's first launch may wait for its set-up)
     }
     return r;
   };
   float best = 1e30f;
-  if (!rc && b->tg) {
-    // split groups: the patch launches of a group (separate or two substeps a
-    // launch) and their tile height, by timing a group of each
-    for (int sched = kSchedSeparate; sched <= kSchedFused && !rc; sched++) {
-      if (sched == kSchedFused && !b->can_fuse) continue;
-      for (int c = 0; c < nty && !rc; c++) {
-        b->sched = sched;
-        b->ty = kTyCand[c];
-        rc = batch_tables(b);
-        // to the next group (the candidates above stop anywhere); the faster
-        // of two, since a kernel's first launch may wait for its set-up
-        for (int rep = 0; rep < 2 && !rc; rep++) {
-          for (int q = 0; q < 2 * b->sims[0]->L0.spb && !rc && !batch_at_group(b, b->tg); q++) {
-            if (b->sims[0]->step - b->src_base >= kSrcSteps) rc = batch_sources(b, b->sims[0]->step);
-            if (!rc) rc = batch_launch_step(b, nullptr, nullptr);
-            if (!rc) (*used)++;
-          }
-          if (!rc && b->sims[0]->step - b->src_base >= kSrcSteps)
-            rc = batch_sources(b, b->sims[0]->step);
-          if (!rc && !batch_at_group(b, b->tg)) break;
-          (void)hipEventRecord(tb[0], b->st);
-          if (!rc) rc = batch_launch_group(b, true);
-          if (!rc) *used += b->tg;
-          (void)hipEventRecord(tf[1], b->st);
-          if (!rc && hipStreamSynchronize(b->st) != hipSuccess) rc = DMR_EHIP;
-          float t = 0.f;
-          (void)hipEventElapsedTime(&t, tb[0], tf[1]);
-          if (!rc && t < best) { best = t; bsched = sched; bty = kTyCand[c]; }
-        }
-      }
-    }
-  } else if (!rc && (b->can_fuse || b->can_combine)) {
+  if (!rc && (b->can_fuse || b->can_combine)) {
     float t = 0.f;
     rc = step_ms(kSchedSeparate, bty, &t);
     best = t;
@@ -3742,14 +3740,63 @@ int batch_tune(dmr_batch* b, int64_t* used) {
       }
     }
   }
+  // split groups: a group of each form of the patch launches (separate or two
+  // substeps a launch, tile height) against as many unsplit steps of the chosen
+  // schedule, from the same place in a window block; the faster of two
+  auto stretch_ms = [&](int sched, int ty, int split, float* ms) {
+    b->sched = sched;
+    b->ty = ty;
+    b->split = split;
+    int r = batch_tables(b);
+    const int t = group_steps(b);
+    *ms = 1e30f;
+    if (split && !b->tg) return r;
+    auto src = [&]() {
+      return b->sims[0]->step - b->src_base >= kSrcSteps ? batch_sources(b, b->sims[0]->step) : DMR_OK;
+    };
+    for (int rep = 0; rep < 2 && !r; rep++) {
+      for (int q = 0; q < 2 * b->sims[0]->L0.spb && !r && !group_place(b, t, t); q++) {
+        r = src();
+        if (!r) r = batch_launch_step(b, nullptr, nullptr);
+        if (!r) (*used)++;
+      }
+      if (!r) r = src();
+      if (!r && !group_place(b, t, t)) break;
+      (void)hipEventRecord(tb[0], b->st);
+      if (split && !r) r = batch_launch_group(b, true);
+      for (int q = 0; q < t && !split && !r; q++) r = batch_launch_step(b, nullptr, nullptr);
+      if (!r) *used += t;
+      (void)hipEventRecord(tf[1], b->st);
+      if (!r && hipStreamSynchronize(b->st) != hipSuccess) r = DMR_EHIP;
+      float x = 1e30f;
+      (void)hipEventElapsedTime(&x, tb[0], tf[1]);
+      *ms = std::min(*ms, x);
+    }
+    return r;
+  };
+  int bsplit = by_size;
+  if (!rc && group_steps(b) && by_size != 0) {
+    float least = 1e30f, t = 0.f;
+    if (by_size < 0) {
+      rc = stretch_ms(bsched, bty, 0, &least);
+      bsplit = 0;
+    }
+    for (int sched = kSchedSeparate; sched <= kSchedFused && !rc; sched++) {
+      if (sched == kSchedFused && !b->can_fuse) continue;
+      for (int c = 0; c < nty && !rc; c++) {
+        rc = stretch_ms(sched, kTyCand[c], 1, &t);
+        if (!rc && t < least) { least = t; bsched = sched; bty = kTyCand[c]; bsplit = 1; }
+      }
+    }
+  }
   for (int q = 0; q < 2; q++) {
     (void)hipEventDestroy(tb[q]);
     (void)hipEventDestroy(tf[q]);
   }
   if (rc) return rc;
-  b->seg = bseg; b->depth = bdep; b->ty = bty; b->sched = bsched;
+  b->seg = bseg; b->depth = bdep; b->ty = bty; b->sched = bsched; b->split = bsplit;
   b->tuned = true;
-  tune_cache().push_back({key, {bseg, bdep, bty, bsched}});
+  tune_cache().push_back({key, {bseg, bdep, bty, bsched, bsplit}});
   return batch_tables(b);
 }
 
