@@ -2965,6 +2965,7 @@ struct dmr_batch {
   int2 *d_blk_base = nullptr, *d_blk_fine = nullptr, *d_blk_cont = nullptr,
        *d_blk_fcont = nullptr;
   int nblk_base = 0, nblk_fine = 0, nblk_cont = 0, nblk_fcont = 0;
+  int cont_rows = 1;  // rows a thread of the base levels' continuity
   size_t cap_base = 0, cap_fine = 0, cap_cont = 0, cap_fcont = 0;  // table entries
   float2* d_src = nullptr;
   float2* h_src = nullptr;
@@ -3338,6 +3339,14 @@ int batch_tables(dmr_batch* b) {
   std::vector<int> pw, ph, pk;  // patches: cells, instance
   b->h_blk_reg.clear();
   b->near_seg = batch_near_seg(b);
+  // Two rows a thread but for the smallest batches.  us a step of uniform
+  // instances with one, two and four rows: 1 x 128x64 6.74 / 6.97 / 7.50, 1 x
+  // 256x128 7.03 / 6.99 / 7.74, 3 x 256x128 7.58 / 7.55 / 7.86, 4 x 512x512 17.74 /
+  // 17.43 / 17.70, 16 x 512x512 61.8 / 58.5 / 58.9, 6 x 1024x1024 100.5 / 96.4 /
+  // 96.8; 512 steps of 64 mixed refined runs 70.2 / 66.6 / 70.4 ms
+  long nodes = 0;
+  for (const dmr_sim* s : b->sims) nodes += (s->p.nx + 1L) * (s->p.ny + 1L);
+  b->cont_rows = nodes >= (1L << 15) ? 2 : 1;
   for (int k = 0; k < n; k++) {
     dmr_sim* s = b->sims[k];
     s->seg0 = b->seg;
@@ -3355,7 +3364,8 @@ int batch_tables(dmr_batch* b) {
     const EMArgs& A = b->h_em[k];
     for (int t = 0; t < A.nbx * A.nseg; t++) b->h_blk_base.push_back(make_int2(k, t));
     const ContArgs& K = b->h_cont[k];
-    const int cny = (K.T - K.B + 1 + 15) / 16;
+    const int crow = kThreads / kTX * b->cont_rows;
+    const int cny = (K.T - K.B + 1 + crow - 1) / crow;
     for (int t = 0; t < K.nbx * cny; t++) b->h_blk_cont.push_back(make_int2(k, t));
     if (s->has_patch && s->uni) {  // the instance's tile list
       for (int t = 0; t < s->ntiles; t++) {
@@ -3530,14 +3540,14 @@ bool batch_at_group(const dmr_batch* b, int64_t left) {
 int batch_cont(dmr_batch* b, int nc, int slot, int update) {
   if (slot < 0) return DMR_OK;
   const int n = b->count;
-  hipError_t e = launch_cont_batch(b->d_cont + nc * n, b->d_blk_cont, b->nblk_cont, false, slot,
-                                   update, b->st);
+  hipError_t e = launch_cont_batch(b->d_cont + nc * n, b->d_blk_cont, b->nblk_cont, false,
+                                   b->cont_rows, slot, update, b->st);
   if (e == hipSuccess && b->sims[0]->uni)
     e = launch_cont_union_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, b->ty, slot,
                                 update, b->st);
   else if (e == hipSuccess)
-    e = launch_cont_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, true, slot, update,
-                          b->st);
+    e = launch_cont_batch(b->d_fcont + nc * n, b->d_blk_fcont, b->nblk_fcont, true, 1, slot,
+                          update, b->st);
   return e == hipSuccess ? DMR_OK : bfail(b, DMR_EHIP, "batched continuity launch");
 }
 

@@ -262,7 +262,9 @@ hipError_t launch_fine2_batch(const EMArgs* args, const int2* blk, int nblk, int
 hipError_t launch_dmr_step_batch(const EMArgs* cargs, const EMArgs* fargs, const int2* blk,
                                  int nblk, const float2* src, int k, int depth, int ty,
                                  hipStream_t st);
-hipError_t launch_cont_batch(const ContArgs* args, const int2* blk, int nblk, bool fine,
+// base level (fine false): rows a thread 1 or 2; a block covers 64 columns x 4
+// rows of threads
+hipError_t launch_cont_batch(const ContArgs* args, const int2* blk, int nblk, bool fine, int rows,
                              int slot, int update, hipStream_t st);
 // the near launches of a batch's split groups: blk[b] = (instance, entry), the
 // block's four waves take four segments of one column wave; of args, the

@@ -1727,10 +1727,8 @@ __device__ __forceinline__ float cont_update(const ContArgs& A, size_t o, float 
 
 // Base level, R rows a thread (64 columns x 4 R rows per block of 256
 // threads): every load of a thread comes before its stores, and the diffusion
-// of a row serves the rows beside it.  Two or four rows in a plain run
-// (launch_cont), four in a batch, whose grid is always large (its block table
-// has 16 rows a block).
-constexpr int kContRowsBatch = 4;
+// of a row serves the rows beside it.  One, two or four rows by the nodes of the
+// launch (launch_cont, batch_tables).
 template <int R>
 __device__ __forceinline__ void cont_rows(const ContArgs& A, int bx, int by, int slot, int update) {
   const int i = A.L + bx * kTX + (int)(threadIdx.x % kTX);
@@ -1984,14 +1982,14 @@ __global__ __launch_bounds__(kThreads) void k_cont_rows(ContArgs A) {
   cont_rows<R>(A, blockIdx.x, blockIdx.y, A.slot, A.update);
 }
 
-template <bool FINE>
+template <bool FINE, int R = 1>
 __global__ __launch_bounds__(kThreads) void k_cont_batch(const ContArgs* __restrict__ args,
                                                          const int2* __restrict__ blk,
                                                          int slot, int update) {
   const int2 bi = blk[blockIdx.x];
   const ContArgs& A = args[bi.x];
-  if constexpr (FINE) cont_body<true>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
-  else cont_rows<kContRowsBatch>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
+  if constexpr (R == 1) cont_body<FINE>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
+  else cont_rows<R>(A, bi.y % A.nbx, bi.y / A.nbx, slot, update);
 }
 
 // cell (i, j) of a fine level made of the active blocks of act
@@ -3230,11 +3228,13 @@ hipError_t launch_em_batch(const EMArgs* args, const int2* blk, int nblk, int ty
   return hipGetLastError();
 }
 
-hipError_t launch_cont_batch(const ContArgs* args, const int2* blk, int nblk, bool fine,
+hipError_t launch_cont_batch(const ContArgs* args, const int2* blk, int nblk, bool fine, int rows,
                              int slot, int update, hipStream_t st) {
   if (nblk <= 0) return hipSuccess;
-  if (fine) hipLaunchKernelGGL(k_cont_batch<true>, dim3(nblk), dim3(kThreads), 0, st, args, blk, slot, update);
-  else hipLaunchKernelGGL(k_cont_batch<false>, dim3(nblk), dim3(kThreads), 0, st, args, blk, slot, update);
+  const dim3 g(nblk), bl(kThreads);
+  if (fine) hipLaunchKernelGGL(k_cont_batch<true>, g, bl, 0, st, args, blk, slot, update);
+  else if (rows == 2) hipLaunchKernelGGL((k_cont_batch<false, 2>), g, bl, 0, st, args, blk, slot, update);
+  else hipLaunchKernelGGL(k_cont_batch<false>, g, bl, 0, st, args, blk, slot, update);
   return hipGetLastError();
 }
 
@@ -3315,10 +3315,11 @@ hipError_t launch_cont(const ContArgs& A, bool fine, hipStream_t st) {
   // 32 steps of 8192x4096 - / 3.82 / 3.80 ms, 64 of a refined 4096x2048 run 2.91
   // / 2.80 / 2.80 ms
   const long nodes = (long)nx * ny;
-  if (!fine && nodes >= (1L << 18)) {
-    const int rows = kThreads / kTX * (nodes >= (1L << 22) ? 4 : 2);
+  const int per = fine || nodes < (1L << 18) ? 1 : nodes < (1L << 22) ? 2 : 4;
+  if (per > 1) {
+    const int rows = kThreads / kTX * per;
     g.y = (ny + rows - 1) / rows;
-    if (nodes >= (1L << 22)) hipLaunchKernelGGL(k_cont_rows<4>, g, dim3(kThreads), 0, st, A);
+    if (per == 4) hipLaunchKernelGGL(k_cont_rows<4>, g, dim3(kThreads), 0, st, A);
     else hipLaunchKernelGGL(k_cont_rows<2>, g, dim3(kThreads), 0, st, A);
   } else if (fine) hipLaunchKernelGGL(k_cont<true>, g, dim3(kThreads), 0, st, A);
   else hipLaunchKernelGGL(k_cont<false>, g, dim3(kThreads), 0, st, A);
