@@ -324,3 +324,33 @@ def test_walls_of_several_steps_bit_by_bit(nx, ny, bc_x, bc_y, multi, monkeypatc
         nan = np.isnan(sa[256:].view(np.float32))
         assert np.array_equal(nan, np.isnan(sb[256:].view(np.float32)))
         assert np.array_equal(sa[256:].view(np.uint32)[~nan], sb[256:].view(np.uint32)[~nan])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["rect", "r4", "union", "wall"])
+@pytest.mark.parametrize("bc_x,bc_y", [("pec", "pec"), ("mur", "pec")])
+def test_split_steps_between_walls_with_the_full_source(kind, bc_x, bc_y, monkeypatch):
+    """Split steps with conducting walls, also within the reach of the fine level
+    (wall), and the Townsend source with recombination: the bits of one launch
+    a step, saved states included."""
+    cfg, (sb, sf) = _refined("static" if kind == "wall" else kind)
+    cfg.update(bc_x=bc_x, bc_y=bc_y, source_model="townsend", beta_rec=2e-13)
+    if kind == "wall":
+        cfg["static_ext"] = (200, 3, 253, 40)
+    runs = []
+    for env in ("1", "8", "5"):
+        monkeypatch.setenv("DMR_MULTI", env)
+        monkeypatch.setenv("DMR_SPLIT_MIN", "0")
+        s = B.Sim(cfg, sb, sf)
+        got = []
+        for n in (5, 130, 61):
+            s.step(n)
+            got.append({(f, lv): s.get(f, lv) for lv in (0, 1) for f in FIELDS})
+        runs.append((got, s.save(np.zeros(s.state_bytes(), np.uint8))))
+        s.sync()
+        s.close()
+    for got, state in runs[1:]:
+        for x, y in zip(runs[0][0], got):
+            for f in x:
+                assert np.array_equal(x[f].view(np.uint32), y[f].view(np.uint32)), f
+        assert np.array_equal(state, runs[0][1])
