@@ -209,8 +209,6 @@ hipError_t launch_prolong_union(const ProlongArgs& A, const int2* tiles, int nti
 // writes buffer 1 (hz1..), A.frac = time fraction of substep 1, restriction on
 hipError_t launch_fine2(const EMArgs& A, int ty, int nt, hipStream_t st);
 hipError_t launch_fine2_fast(const EMArgs& A, int tw, hipStream_t st);
-// dst[k] = V.v[k], k < V.n
-hipError_t launch_src_put(const SrcVals& V, float2* dst, hipStream_t st);
 // the same in registers (dmr_fine.hip; r = 2 rectangle); waves per block 16, 12
 // or 8 (0: by size); blocks of a w x h-cell patch, and the waves for several
 hipError_t launch_fine_reg(const EMArgs& A, int waves, hipStream_t st);
@@ -226,7 +224,7 @@ hipError_t launch_dmr_step(const EMArgs& C, const EMArgs& F, int seg, int depth,
 // base level, column-streaming kernel; seg = rows per segment (>= 2)
 hipError_t launch_em_stream(const EMArgs& A, int seg, int depth, hipStream_t st,
                             StreamWin win = StreamWin());
-// the same over a list of (group of four 62-column waves, segment); 2 rows of
+// the same over a list of (62-column wave, group of four segments); 2 rows of
 // loads in flight
 hipError_t launch_em_stream_list(const EMArgs& A, const int2* blk, int nblk, int seg,
                                  hipStream_t st);
@@ -238,6 +236,8 @@ hipError_t launch_fine_stream(const EMArgs& A, int seg, int depth, hipStream_t s
 hipError_t launch_line_flags(const float* n, int pitch, int I0, int J0, int I1, int J1,
                              float thr, int* flags, hipStream_t st);
 int stream_segments(int NY, int seg);
+// dst[k] = V.v[k], k < V.n
+hipError_t launch_src_put(const SrcVals& V, float2* dst, hipStream_t st);
 // M.t base-level steps in one launch, blocks of 64 columns x 4 waves rows
 hipError_t launch_em_multi(MultiArgs& M, int waves, hipStream_t st);
 // its blocks along x and y for M->t steps (false: no such launch)
