@@ -114,17 +114,35 @@ constexpr int kNearSeg = 2;
 
 int stream_blocks_x(int NX) { return ((NX + 1 + 61) / 62 + kThreads / 64 - 1) / (kThreads / 64); }
 
-// Cells from which the steps of a refined run are split (split_steps): where
-// the base level is what a step waits for; on smaller grids the patch's chain
-// is, and the far launch only adds to it.  Per step, one launch a step against
-// split: patch r = 2: 512x256 7.6 / 8.6 us, 704x352 9.8 / 9.5, 1024x512 11.0 /
-// 10.2, 4096x2048 123 / 47; union of blocks: 704x352 22.6 / 23.3, 1024x512
-// 24.4 / 24.0, 4096x2048 137 / 67; r = 4: 1024x512 18.8 / 19.3, 1440x720 23.6 /
-// 21.3.  DMR_SPLIT_MIN=cells in its place.
-long split_least(const dmr_params* p) {
-  if (const char* f = getenv("DMR_SPLIT_MIN"))
-    if (atol(f) >= 0) return atol(f);
-  return p->r == 4 ? 1L << 20 : p->regrid_rule == DMR_RULE_UNION ? 1L << 19 : 1L << 18;
+// DMR_SPLIT_MIN=cells in place of split_least's (-1: not set)
+long split_forced() {
+  const char* f = getenv("DMR_SPLIT_MIN");
+  return f ? std::max(atol(f), -1L) : -1;
+}
+
+// Cells from which t steps of a refined run are split (split_steps): where the
+// base level is what a step waits for; on smaller grids the patch's chain is,
+// and the far launch, which a short group pays for with few steps, only adds to
+// it.  us a step, one launch a step against split, windows of 8 steps: patch r =
+// 2: 512x256 6.6 / 8.6, 704x352 9.1 / 9.1, 1024x512 10.5 / 9.7, 4096x2048 116 /
+// 38; union of blocks: 704x352 21.5 / 21.8, 1024x512 23.4 / 21.9, 4096x2048 137 /
+// 67; r = 4: 1024x512 17.9 / 18.6, 1024x1024 22.4 / 18.1.  Windows of 2, 3, 4, 5
+// steps: r = 2, 512x512 12.6 / 14.1, 11.1 / 11.6, 10.3 / 10.3, 9.8 / 9.5;
+// 1024x512 16.6 / 17.7, 13.9 / 14.1, 12.5 / 12.2, 11.7 / 11.3; 1440x720 21.5 /
+// 21.2, 18.6 / 16.6; union 1024x512 29.4 / 30.3, 26.7 / 26.5, 25.4 / 24.6; r = 4
+// 1024x1024 29.0 / 28.8, 26.1 / 23.8.
+long split_least(const dmr_params* p, int t, long forced) {
+  if (forced >= 0) return forced;
+  if (p->r == 4) return 1L << 20;
+  if (p->regrid_rule == DMR_RULE_UNION) return t < 3 ? 1L << 20 : 1L << 19;
+  return t < 4 ? 1L << 20 : 1L << 18;
+}
+
+// the longest of the equal launches that take the steps of a window block, at
+// most `most` each
+int longest_group(int spb, int most) {
+  const int parts = (spb + most - 1) / most;
+  return (spb + parts - 1) / parts;
 }
 
 Layout layout_of(const dmr_params* p) {
@@ -167,7 +185,8 @@ Layout layout_of(const dmr_params* p) {
     L.off_nblk = off;  off += align256(L.max_nblk * sizeof(int2));
   }
   L.full = off;
-  if (refined(p) && (long)p->nx * p->ny >= split_least(p)) L.total = L.full;
+  const int t = longest_group((int)std::lround(p->cells_per_lambda / p->courant) / kRing, kMultiSteps);
+  if (refined(p) && t > 1 && (long)p->nx * p->ny >= split_least(p, t, split_forced())) L.total = L.full;
   return L;
 }
 
@@ -324,7 +343,7 @@ struct dmr_sim {
   // refined runs: a third set of the base level's planes (Hz, Ex, Ey, Jx, Jy,
   // window) for the split groups, and the grids they are used on
   float* far[6] = {};
-  long split_min = 0;  // cells (split_least)
+  long split_min = -1;  // split_forced
   // union-of-blocks level: the blocks around it (host, device) and the
   // base-level streaming blocks that cover them
   std::vector<uint8_t> h_near;
@@ -1452,13 +1471,15 @@ int near_blocks(dmr_sim* s) {
 
 // Whether the grid is one whose steps may be split (split_steps)
 bool split_grid(const dmr_sim* s) {
-  return s->far[0] && s->multi_t >= 2 && (long)s->p.nx * s->p.ny >= s->split_min;
+  const int t = longest_group(s->L0.spb, s->multi_t);
+  return s->far[0] && t > 1 && (long)s->p.nx * s->p.ny >= split_least(&s->p, t, s->split_min);
 }
 
 // whether t steps of a run with a fine level are split
 bool can_split(const dmr_sim* s, int t) {
   const dmr_params& p = s->p;
-  if (t < 2 || !s->has_patch || !split_grid(s)) return false;
+  if (t < 2 || !s->has_patch || !s->far[0] || (long)p.nx * p.ny < split_least(&p, t, s->split_min))
+    return false;
   if (s->uni) return s->near_gen == s->ugen && s->near_share <= 0.5;
   const StreamWin w = near_window(s, t);
   return (double)w.ncw * 62 * w.nk * kNearSeg <= 0.5 * (p.nx + 1.0) * (p.ny + 1.0);
@@ -1594,7 +1615,16 @@ float* array_of(dmr_sim* s, int field, int level, double* scale) {
 // device has a period's work queued and three periods or more are to come or
 // three have run.  Runs that are split around the fine level (can_split) and
 // uniform runs wait for the device, not for launches: 1.67 and 1.63 us a step on
-// uniform 256x128.  Not used while times are taken or while the caller records
+// uniform 256x128.  So do refined runs on larger grids, and in a short period the
+// graph's own launch and that of the table outweigh the rest.  us a step launch by
+// launch and from a graph, window blocks of 2, 3, 4, 8 steps: r = 2, 512x256 8.80 /
+// 8.94, 7.86 / 7.78, 7.39 / 7.22, 6.64 / 6.36; 576x320 9.57 / 9.75, 8.55 / 8.58,
+// 8.05 / 7.95, 7.28 / 7.05; 704x352 12.66 / 13.03, 11.08 / 11.22, 10.29 / 10.37,
+// 9.09 / 9.04; 768x384 - , - , 10.45 / 10.63, 9.19 / 9.22; r = 4, 512x256 17.34 /
+// 17.44, 16.10 / 16.02, 15.48 / 15.30, 14.56 / 14.22; 704x352 - , - , 17.03 / 17.13,
+// 15.60 / 15.57; union 512x256 24.0 / 23.2, 22.5 / 21.5, 21.6 / 20.7, 20.4 / 19.3;
+// 704x352 25.7 / 25.5, - , - , 21.5 / 21.0; 768x512 28.0 / 28.6, - , - , 22.4 / 22.5.
+// Not used while times are taken or while the caller records
 // the stream itself.
 int period_steps(dmr_sim* s, int64_t n, bool* ran) {
   const dmr_params& p = s->p;
@@ -1603,8 +1633,9 @@ int period_steps(dmr_sim* s, int64_t n, bool* ran) {
       (K & 1) || s->step % K || s->blocks < kRing || s->blocks % kRing)
     return DMR_OK;
   if (p.mode == DMR_DYNAMIC && s->step % p.regrid_every + K > p.regrid_every) return DMR_OK;
-  const int parts = (spb + s->multi_t - 1) / s->multi_t;
-  if (!s->recorded && can_split(s, (spb + parts - 1) / parts)) return DMR_OK;
+  const long cells = (long)p.nx * p.ny;
+  if (cells >= 1L << 18 || (!s->uni && (spb < 3 || cells > spb * 48000L))) return DMR_OK;
+  if (!s->recorded && can_split(s, longest_group(spb, s->multi_t))) return DMR_OK;
 
   dmr_sim::PeriodKey key;
   memset(&key, 0, sizeof key);
@@ -1804,7 +1835,7 @@ int dmr_create(const dmr_params* p, const double* seed_base,
     s->multi_t = std::min(std::max(s->multi_t, 1), kMultiSteps);
     s->multi_w = s->multi_w < 5 ? 0 : std::min(s->multi_w, 16);
   }
-  s->split_min = split_least(p);
+  s->split_min = split_forced();
   if (const char* f = getenv("DMR_PERIOD")) s->pg_on = atoi(f) != 0;
   if (!s->d_src) s->pg_on = false;
   if (const char* f = getenv("DMR_CONT_MERGE")) s->cont_merge = atoi(f) != 0 ? 1 : 0;
@@ -3164,7 +3195,9 @@ int group_room(dmr_batch* b, int* tg) {
 bool split_by_size(const dmr_batch* b) {
   long cells = 0;
   for (const dmr_sim* s : b->sims) cells += (long)s->p.nx * s->p.ny;
-  return cells >= b->sims[0]->split_min;
+  const dmr_sim* s0 = b->sims[0];
+  const int t = group_steps(b);
+  return t && cells >= split_least(&s0->p, t, s0->split_min);
 }
 
 // Rows per segment of the near launches of rectangles: the longest that leave
