@@ -29,6 +29,19 @@ struct EMArgs {
   float *hz1, *ex1, *ey1, *jx1, *jy1;        // state at step n+1 (written)
   const float* n;                            // density at the nodes
   float* acc;                                // window accumulator (in place)
+  // Read by every launch: kept with the other pointers it starts from (a launch
+  // on its own reads its arguments from host memory, a cache line more is 0.5 us)
+  union {
+    float* acc1;      // base level: where the accumulator is written
+    float* cfb_next;  // union of blocks, see below
+  };
+  union {
+    // base level and rectangular patch: incident values on the device instead of
+    // ey_src / hz_src and cey_src / chz_src (steps recorded in a graph; null: by
+    // value)
+    const float2* src;
+    const int2* utiles;  // batched union levels: the instance's tile list
+  };
   int pitch;
   int L, B, R, T;  // active cells [L,R) x [B,T); nodes [L,R] x [B,T]
   float S;         // c dt / dx
@@ -79,18 +92,8 @@ struct EMArgs {
   // union, r = 2: substep 1 writes the Eq. (5b) values of the last substep
   // (frac = 1) per listed tile (cfb_next), which reads them back (cfb_prev)
   // instead of the coarse E its own fine -> coarse transfer rewrites
-  union {
-    float* cfb_next;
-    float* acc1;  // base level: where the window accumulator is written
-  };
+  // (cfb_next shares acc1's place)
   const float* cfb_prev;
-  union {
-    const int2* utiles;  // batched union levels: the instance's tile list
-    // base level and rectangular patch: incident values on the device instead of
-    // ey_src / hz_src and cey_src / chz_src (steps recorded in a graph; null: by
-    // value)
-    const float2* src;
-  };
 };
 
 // incident Ey, eta0 Hz of consecutive steps, by value for one launch
