@@ -22,11 +22,17 @@ namespace dmr {
 namespace {
 
 // The region is stepped by the interior update everywhere, also where it
-// reaches beyond the grid: E that does not exist (or is zero, PEC) is set to +0
-// by a bit mask, whatever its neighbours hold, which also drops it from the
-// window of the boundary nodes.  XE: the region holds column 0 or NX or a source column;
-// YE: the wave holds row 0 or NY.
-template <int R, bool XE, bool YE>
+// reaches beyond the grid.  Of E that does not exist, x-edges beside columns 0 and
+// NX and y-edges of row NY reach an entity of the grid (the window of its boundary
+// nodes) and are left out there, whatever they hold; all others end in entities
+// that do not exist either, or in walls, which are set by themselves.  With PEC
+// walls (P) E on them and beyond is set to +0 by bit masks.  XE: the region holds
+// column 0 or NX or a source column; YE: the wave holds row 0 or NY.  A factor 0
+// in place of 1 / (1 + kap) was cheaper, but left -0 and, beside an infinite value,
+// NaN.  us a step of a uniform run, factor / masks in all forms / these: 256x128
+// 1.91 / 1.97 / 1.89, 1024x512 3.27 / 3.33 / 3.30, 2048x1024 8.18 / 8.35 / 8.20,
+// 8192x4096 103.4 / 105.0 / 102.9.
+template <int R, bool XE, bool YE, bool P>
 __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const float2* in, float* hzp,
                                            int x0, int y0, int own_x, int own_lo, int own_hi,
                                            float (*sE)[3][64]) {
@@ -60,7 +66,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
     hm = row(A.hz0, jt - 1);
   }
   const int rb = -jt, rt = NY - jt;  // rows 0 and NY of the grid in the wave
-  const bool mur_x = A.bc_x == kBcMur, mur_y = A.bc_y == kBcMur;
+  const bool mur_x = !P || A.bc_x == kBcMur, mur_y = !P || A.bc_y == kBcMur;
   const bool c0 = i == 0, cN = i == NX;
   const bool mur0 = mur_x && x0 <= 0, murN = mur_x && x0 + 63 >= NX;
   const bool src = A.is > 0 && A.is >= x0 && A.is - 1 <= x0 + 63;
@@ -71,7 +77,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
   const bool colx = !XE | ((i >= 0) & (i < NX));
   const bool coly = !XE | ((i >= 0) & (i <= NX) & (mur_x | !(c0 | cN)));
   int rows = 0;
-  if (YE) {
+  if (YE && P) {
 #pragma unroll
     for (int r = 0; r < R; r++) {
       const int j = jt + r;
@@ -92,8 +98,9 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
   // window of the wave's node row r, Ey of the row below it
   auto window = [&](int r, float yd) {
     const float fy = YE && (r == rb || r == rt) ? 2.f : 1.f;
+    const float yu = YE && !P && r == rt ? 0.f : ey[r];
     const float exl = lane_left(ex[r]);
-    const float v = base_win(ac[r], exl, ex[r], yd, ey[r], fx, fy);
+    const float v = base_win(ac[r], exl, ex[r], yd, yu, fx, fy);
     const float v0 = base_win0(ac[r], exl, ex[r], ey[r], fx);
     return YE && r == rb ? v0 : v;
   };
@@ -117,10 +124,10 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
     const int b = (s & 1) * nw;
     // (a mask of its own for every row, kept over the steps, spilled)
     int rw = 0;
-    if (YE) asm volatile("s_mov_b32 %0, %1" : "=s"(rw) : "s"(rows));
+    if (YE && P) asm volatile("s_mov_b32 %0, %1" : "=s"(rw) : "s"(rows));
     auto keep = [&](float v, bool col, int bit) {
       int q = __builtin_bit_cast(int, v);
-      if (YE) q &= (rw << (31 - bit)) >> 31;
+      if (YE && P) q &= (rw << (31 - bit)) >> 31;
       return XE && !col ? 0.f : __builtin_bit_cast(float, q);
     };
     publish(s & 1);
@@ -163,7 +170,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
     for (int r = 0; r < R; r++)
       en[r] = keep(base_ex(ex[r], kx[r], S, hz[r], r > 0 ? hz[r > 0 ? r - 1 : 0] : hm, c1, jx[r], rx[r]),
                    colx, r);
-    if (YE && mur_y) {
+    if (YE && (!P || mur_y)) {
 #pragma unroll
       for (int r = 0; r + 1 < R; r++) {
         const float eb = ex[r + 1] + cm * (en[r + 1] - ex[r]);
@@ -182,7 +189,8 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
       float curl = -S * (hz[r] - lane_left(hz[r]));
       if (XE && src) curl += add_e;
       const float eyo = ey[r];
-      en[r] = keep(base_ey(eyo, ky[r], curl, c1, jy[r], ry[r]), coly, 16 + r);
+      en[r] = base_ey(eyo, ky[r], curl, c1, jy[r], ry[r]);
+      if (P) en[r] = keep(en[r], coly, 16 + r);
       if (XE && mur0) {
         const float m = lane_right(eyo) + cm * (lane_right(en[r]) - eyo);
         en[r] = c0 ? m : en[r];
@@ -191,7 +199,7 @@ __device__ __forceinline__ void multi_tile(const MultiArgs& M, int t, const floa
         const float m = lane_left(eyo) + cm * (lane_left(en[r]) - eyo);
         en[r] = cN ? m : en[r];
       }
-      if (XE && YE && (jt + r < 0 || jt + r >= NY)) en[r] = 0.f;
+      if (P && XE && YE && (jt + r < 0 || jt + r >= NY)) en[r] = 0.f;
       jy[r] = a * jy[r] + 2.f * ky[r] * (eyo + en[r]);
       ey[r] = en[r];
     }
@@ -254,10 +262,19 @@ __device__ __forceinline__ void multi_block(const MultiArgs& M, int t, const flo
   // (chosen per wave; every form passes the same barriers)
   const int jt = y0 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * R;
   const bool ye = jt < 1 || jt + R > NY;
-  if (xe && ye) multi_tile<R, true, true>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
-  else if (xe) multi_tile<R, true, false>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
-  else if (ye) multi_tile<R, false, true>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
-  else multi_tile<R, false, false>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE);
+  const bool pec = A.bc_x != kBcMur || A.bc_y != kBcMur;
+#define TILE(X, Y, P) multi_tile<R, X, Y, P>(M, t, in, hzp, x0, y0, own_x, own_lo, own_hi, sE)
+  if (!xe && !ye) TILE(false, false, false);
+  else if (pec) {
+    if (xe && ye) TILE(true, true, true);
+    else if (xe) TILE(true, false, true);
+    else TILE(false, true, true);
+  } else {
+    if (xe && ye) TILE(true, true, false);
+    else if (xe) TILE(true, false, false);
+    else TILE(false, true, false);
+  }
+#undef TILE
 }
 
 // R rows a wave, at most NW waves a block, EU waves per SIMD
