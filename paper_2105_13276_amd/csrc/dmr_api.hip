@@ -3023,7 +3023,7 @@ struct dmr_batch {
   // table is built for both.  Steps of a group: phase 0 the first, 1 the odd
   // ones, 2 the others (which planes they read and write).
   int tg = 0, gp = 0, far_waves = 12;
-  int split = -1;  // whether to (0, 1: as timed; -1: by size, split_least)
+  int split = -1;  // whether to (0, 1: as timed; -1: split_untimed)
   int sets = 2;  // of the tables (1: a workspace without room for groups)
   EMArgs* d_nem = nullptr;    // [2 gp][2 density][3 phases][count] base level, near
   EMArgs* d_nfem = nullptr;   // [2][2][3][rf][count] patch, one launch a substep
@@ -3190,14 +3190,16 @@ int group_room(dmr_batch* b, int* tg) {
   return DMR_OK;
 }
 
-// whether the batch's grids together are of the size from which a plain run
-// splits its steps (what a batch does until it has timed both)
-bool split_by_size(const dmr_batch* b) {
+// Whether a batch splits its steps until it has timed both ways: with its first
+// schedule (one launch a substep) groups take fewer launches at every size (us a
+// step in calls of 100, unsplit / split: one 256x128 run 25.3 / 22.5, four of
+// 512x256 31.3 / 25.5, eight of 1024x512 72.4 / 39.5); where DMR_SPLIT_MIN is set,
+// by the grids' cells together.
+bool split_untimed(const dmr_batch* b) {
+  const long least = b->sims[0]->split_min;
   long cells = 0;
   for (const dmr_sim* s : b->sims) cells += (long)s->p.nx * s->p.ny;
-  const dmr_sim* s0 = b->sims[0];
-  const int t = group_steps(b);
-  return t && cells >= split_least(&s0->p, t, s0->split_min);
+  return cells >= least;
 }
 
 // Rows per segment of the near launches of rectangles: the longest that leave
@@ -3367,7 +3369,7 @@ int batch_tables(dmr_batch* b) {
   if ((b->sched == kSchedFused && !b->can_fuse) || (b->sched == kSchedCombined && !b->can_combine))
     b->sched = kSchedSeparate;
   b->tg = 0;
-  if (b->split < 0 ? split_by_size(b) : b->split > 0)
+  if (b->split < 0 ? split_untimed(b) : b->split > 0)
     if (int rc = group_room(b, &b->tg)) return rc;
   std::vector<int> pw, ph, pk;  // patches: cells, instance
   b->h_blk_reg.clear();
@@ -3698,7 +3700,7 @@ std::string batch_key(const dmr_batch* b) {
   const dmr_sim* s0 = b->sims[0];
   char buf[64];
   snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d", b->rf, (int)s0->uni, group_steps(b),
-           getenv("DMR_SPLIT_MIN") ? 1 : 0, (int)split_by_size(b));
+           s0->split_min >= 0 ? 1 : 0, (int)split_untimed(b));
   k += buf;
   return k;
 }
@@ -3725,7 +3727,7 @@ int batch_tune(dmr_batch* b, int64_t* used) {
   const int ncand = std::max(nseg, nty);
   int rc = DMR_OK;
   // DMR_SPLIT_MIN decides about groups where it is set, the times where not
-  const int by_size = getenv("DMR_SPLIT_MIN") ? (int)split_by_size(b) : -1;
+  const int by_size = b->sims[0]->split_min >= 0 ? (int)split_untimed(b) : -1;
   b->sched = kSchedSeparate;
   b->split = 0;
   for (int c = 0; c < ncand && !rc; c++) {
