@@ -1607,9 +1607,7 @@ float* array_of(dmr_sim* s, int field, int level, double* scale) {
 
 // One period (8 window blocks) of a refined run whose steps are launch-bound,
 // as one graph.  A launch on its own costs the host 3.7 us and the device
-// about 0.7 us more than a graph's node does: 512x256 (r = 2) 7.0 us a step
-// launch by launch, 6.3 from a graph; 256x128 (r = 4, three launches) 13.8 and
-// 11.7.  Over a period every plane, ring slot and buffer parity returns to where
+// 0.3 us and more above a graph's node.  Over a period every plane, ring slot and buffer parity returns to where
 // it was, so the recorded launches serve every later one; what changes, the
 // incident values, is in d_src.  Recording (2 us a launch) is left until the
 // device has a period's work queued and three periods or more are to come or
