@@ -3681,8 +3681,26 @@ int batch_regrid(dmr_batch* b) {
 
 // pick the streaming segment/depth and the fine tile height by timing real
 // steps (all candidates give bit-identical results)
-std::vector<std::pair<std::string, std::array<int, 5>>>& tune_cache() {
-  static std::vector<std::pair<std::string, std::array<int, 5>>> c;
+// what earlier batches of the process chose, by batch_key (any thread)
+struct TuneCache {
+  std::mutex m;
+  std::vector<std::pair<std::string, std::array<int, 5>>> v;
+  bool get(const std::string& key, std::array<int, 5>* out) {
+    std::lock_guard<std::mutex> l(m);
+    for (const auto& kv : v)
+      if (kv.first == key) {
+        *out = kv.second;
+        return true;
+      }
+    return false;
+  }
+  void put(const std::string& key, const std::array<int, 5>& c) {
+    std::lock_guard<std::mutex> l(m);
+    v.push_back({key, c});
+  }
+};
+TuneCache& tune_cache() {
+  static TuneCache c;
   return c;
 }
 
@@ -3706,14 +3724,14 @@ std::string batch_key(const dmr_batch* b) {
 int batch_tune(dmr_batch* b, int64_t* used) {
   *used = 0;
   const std::string key = batch_key(b);
-  for (auto& kv : tune_cache())
-    if (kv.first == key) {
-      b->seg = kv.second[0]; b->depth = kv.second[1]; b->ty = kv.second[2];
-      b->sched = kv.second[3];
-      b->split = kv.second[4];
-      b->tuned = true;
-      return batch_tables(b);
-    }
+  std::array<int, 5> known;
+  if (tune_cache().get(key, &known)) {
+    b->seg = known[0]; b->depth = known[1]; b->ty = known[2];
+    b->sched = known[3];
+    b->split = known[4];
+    b->tuned = true;
+    return batch_tables(b);
+  }
   hipEvent_t tb[2], tf[2];
   for (int q = 0; q < 2; q++) {
     (void)hipEventCreate(&tb[q]);
@@ -3839,7 +3857,7 @@ int batch_tune(dmr_batch* b, int64_t* used) {
   if (rc) return rc;
   b->seg = bseg; b->depth = bdep; b->ty = bty; b->sched = bsched; b->split = bsplit;
   b->tuned = true;
-  tune_cache().push_back({key, {bseg, bdep, bty, bsched, bsplit}});
+  tune_cache().put(key, {bseg, bdep, bty, bsched, bsplit});
   return batch_tables(b);
 }
 

@@ -60,3 +60,36 @@ def test_interval_that_holds_no_whole_periods(mode, cpl):
             s.step(n)
             _same(h, s)
     b.close()
+
+
+def test_batches_tune_in_several_threads():
+    """Batches that come to tune at the same time, in a thread each (the choices
+    are kept for the whole process): the bits of the plain runs."""
+    import threading
+    cases, out = [], {}
+    for k, nx in enumerate((160, 192, 224, 256)):
+        cfg = W.make(nx, 96, 32, "dynamic", 1, erms_over_ebd=2.0)
+        cases.append(([cfg, cfg], [W.seeds(cfg)] * 2))
+
+    def run(k):
+        import torch
+        with torch.cuda.stream(torch.cuda.Stream()):
+            b = B.Batch(*cases[k])
+            for n in (256, 300, 44):
+                b.step(n)
+            b.sync()
+            out[k] = [{f: h.get(f, 0) for f in FIELDS} for h in b.instances]
+            b.close()
+
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(len(cases))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, (cfgs, seeds) in enumerate(cases):
+        s = B.Sim(cfgs[0], *seeds[0])
+        s.step(600)
+        for got in out[k]:
+            for f in FIELDS:
+                assert np.array_equal(got[f], s.get(f, 0)), (k, f)
+        s.close()
