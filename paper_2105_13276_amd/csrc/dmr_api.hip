@@ -1054,12 +1054,12 @@ int run_copies(dmr_sim* s, const CopyJobs& J) {
   return e == hipSuccess ? DMR_OK : hipfail(s, e, "tape copy");
 }
 
-// whether the caller is recording the stream into a graph
-bool being_recorded(hipStream_t st) {
+// whether the caller is recording the stream into a graph (-1: not known)
+int being_recorded(hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
     (void)hipGetLastError();
-    return false;
+    return -1;
   }
   return cap != hipStreamCaptureStatusNone;
 }
@@ -1606,12 +1606,12 @@ float* array_of(dmr_sim* s, int field, int level, double* scale) {
 }
 
 // One period (8 window blocks) of a refined run whose steps are launch-bound,
-// as one graph.  A launch on its own costs the host 3.7 us and the device
-// 0.3 us and more above a graph's node.  Over a period every plane, ring slot and buffer parity returns to where
-// it was, so the recorded launches serve every later one; what changes, the
-// incident values, is in d_src.  Recording (2 us a launch) is left until the
-// device has a period's work queued and three periods or more are to come or
-// three have run.  Runs that are split around the fine level (can_split) and
+// as one graph.  A launch on its own costs the host 3.7 us and the device 0.3 us
+// and more above a graph's node.  Over a period every plane, ring slot and buffer
+// parity returns to where it was, so the recorded launches serve every later one;
+// what changes, the incident values, is in d_src.  Recording (2 us a launch) is
+// left until the device has a period's work queued and three periods or more are
+// to come or three have run.  Runs that are split around the fine level (can_split) and
 // uniform runs wait for the device, not for launches: 1.67 and 1.63 us a step on
 // uniform 256x128.  So do refined runs on larger grids, and in a short period the
 // graph's own launch and that of the table outweigh the rest.  us a step launch by
@@ -1622,8 +1622,7 @@ float* array_of(dmr_sim* s, int field, int level, double* scale) {
 // 17.44, 16.10 / 16.02, 15.48 / 15.30, 14.56 / 14.22; 704x352 - , - , 17.03 / 17.13,
 // 15.60 / 15.57; union 512x256 24.0 / 23.2, 22.5 / 21.5, 21.6 / 20.7, 20.4 / 19.3;
 // 704x352 25.7 / 25.5, - , - , 21.5 / 21.0; 768x512 28.0 / 28.6, - , - , 22.4 / 22.5.
-// Not used while times are taken or while the caller records
-// the stream itself.
+// Not used while times are taken or while the caller records the stream itself.
 int period_steps(dmr_sim* s, int64_t n, bool* ran) {
   const dmr_params& p = s->p;
   const int K = s->period(), spb = s->L0.spb;
@@ -1929,8 +1928,8 @@ void dmr_destroy(dmr_sim* s) {
 
 int dmr_step(dmr_sim* s, int64_t n) {
   if (!s || n < 0) return fail(s, DMR_EINVAL, "bad step count");
-  const bool now = n > 0 && being_recorded(s->st);
-  s->recorded = s->recorded || now;
+  const int now = n > 0 ? being_recorded(s->st) : 0;
+  s->recorded = s->recorded || now > 0;
   while (n > 0) {
     bool ran = false;
     if (!now)
@@ -4057,7 +4056,7 @@ int dmr_batch_step(dmr_batch* b, int64_t n) {
   if (!b || n < 0) return DMR_EINVAL;
   (void)hipEventRecord(b->ev_in, b->user);
   (void)hipStreamWaitEvent(b->st, b->ev_in, 0);
-  if (n > 0 && !b->recorded && being_recorded(b->st)) {
+  if (n > 0 && !b->recorded && being_recorded(b->st) > 0) {
     b->recorded = true;
     b->graph_ok = false;  // the interval's graph holds groups
   }
